@@ -113,7 +113,7 @@ Layout layout_of(const fsl_config *c, size_t stage_cap = (size_t)64 << 20) {
     L.bub = take(L.S * 2);
     L.pid = take(L.S * 4);
     L.claim = take(L.S * 4);
-    L.counters = take(64 * 4);
+    L.counters = take(C_WORDS * 4);
     L.ctl = take(64 * 8);  // [0] err word, [8] ledger, [16..] mass sums
     L.ptab = take((size_t)L.maxP * P_STRIDE * 8);
     L.pacc = take((size_t)L.maxP * ACC_COPIES * ACC_STRIDE * 8);
@@ -135,7 +135,7 @@ Layout layout_of(const fsl_config *c, size_t stage_cap = (size_t)64 << 20) {
     L.klist = take((size_t)L.nKT * 4);
     L.kcount = take(c->sigma != 0.0 ? 4 : 0);
     L.wallu = take(18 * 4);
-    L.wallF = take(18 * 8);
+    L.wallF = take(2 * 18 * 8);
     L.nTiles = ((c->n[0] + TX - 1) / TX) * ((c->n[1] + TY - 1) / TY) * c->n[2];
     L.winBytes = adjoint_window_bytes(c->window_steps, c->window_every, (size_t)L.S, c->max_particles,
                                       L.nTiles);
@@ -190,6 +190,7 @@ struct fsl_ctx {
     int profiling;
     int have_prev;  // a previous step's hydrodynamic force exists (particle update)
     int stamp;      // stamp of the next stream-collide launch (>= 1)
+    int counters_clear;  // the counters of the next step are zero
     int rhow_ok;    // the density words of stamp - 1 hold the densities of the populations in A
     // two steps captured as a HIP graph from a steady state (stored densities valid, the
     // particle update past its first step): fsl_step replays it while lattice A is the
@@ -307,7 +308,6 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
     int nzc = NZC;
     while (nzc > 2 && cols * ((c->G.nz + nzc - 1) / nzc) < 2048) nzc /= 2;
     const int nChunks = (c->G.nz + nzc - 1) / nzc;
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->st, ngen, 1LL, 0);
     hipLaunchKernelGGL((k_stream_collide<ST, MW, PER>), dim3(c->tilesX * c->tilesY * nChunks), dim3(256), 0, c->st,
                        c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen);
     hipLaunchKernelGGL((k_general<ST, MW>), dim3(std::min(c->nTiles, 4096)), dim3(256), 0, c->st, c->G, c->Ph, Dv,
@@ -332,44 +332,43 @@ template <int ST> int enqueue_integration(fsl_ctx *c);
 template <int ST> int enqueue_pair_forces(fsl_ctx *c);
 template <int ST> int enqueue_coverage_step(fsl_ctx *c);
 template <int ST> int enqueue_coverage_full(fsl_ctx *c);
-template <int ST> int enqueue_bubbles(fsl_ctx *c, double *phi, int init);
+template <int ST> int enqueue_bubbles(fsl_ctx *c, double *phi, int init, int test);
+
+// boxes whose list phases and labelling go into one launch with barriers between the
+// phases: up to 4 M cells, where a step takes a few hundred microseconds and the launches
+// saved (2 and 5, at 4.5 us) show; beyond, the labelling of a split wants the whole device
+// (SYNC_BLOCKS blocks take several times as long on the 268 M cells of the column)
+bool fused_phases(const fsl_ctx *c) { return c->G.N <= (1ll << 22); }
 
 template <int ST>
-int enqueue_bubbles(fsl_ctx *c, double *phi, int init) {
+int enqueue_bubbles(fsl_ctx *c, double *phi, int init, int test) {
     ProfScope ps(c, 2);
     Dev &D = c->D;
-    hipLaunchKernelGGL(k_bubble_zero, dim3(1), dim3(256), 0, c->st, D, (const int *)nullptr);
-    hipLaunchKernelGGL(k_bubble_accum, dim3(grid_for((c->G.N + 15) / 16, 256, 2048)), dim3(256), 0,
-                       c->st, c->G, D, (const double *)phi, (const int *)nullptr);
-    hipLaunchKernelGGL(k_bubble_finalize, dim3(1), dim3(64), 0, c->st, D, init, (const int *)nullptr,
-                       c->Ph.open_atm);
+    hipLaunchKernelGGL(k_bubbles, dim3(std::max(32, grid_for((c->G.N + 15) / 16, 256, 2048))), dim3(256), 0, c->st, c->G,
+                       D, (const double *)phi, init, test, c->Ph.open_atm);
     LAUNCHCHK(c);
     return FSL_OK;
 }
 
 // bubble splitting at the end of a step (force = 0: labelling only where the local
-// test of a cell that left the gas fails) or of the current state (force = 1);
-// phi is the state's fill level.  Every kernel after the test reads the flag the
-// test leaves and returns at once when there is nothing to do.
+// test of a cell that left the gas failed) or of the current state (force = 1);
+// phi is the state's fill level
 template <int ST>
 int enqueue_split(fsl_ctx *c, const double *phi, int force) {
     ProfScope ps(c, 7);
     const Dev &D = c->D;
     const SplitBuf &B = c->SB;
-    const dim3 gl(LIST_BLOCKS), b(256), gn(grid_for(c->G.N, 256, 2048));
-    if (force) hipLaunchKernelGGL(k_split_force, dim3(1), dim3(64), 0, c->st, D);
-    else hipLaunchKernelGGL(k_split_test, gl, b, 0, c->st, c->G, D);
-    hipLaunchKernelGGL(k_ccl_init, gn, b, 0, c->st, c->G, D, B);
-    hipLaunchKernelGGL(k_ccl_union, gn, b, 0, c->st, c->G, D, B);
-    hipLaunchKernelGGL(k_ccl_flatten, gn, b, 0, c->st, c->G, D, B);
-    hipLaunchKernelGGL(k_split_plan, dim3(1), dim3(1024), 0, c->st, D, B, c->Ph.open_atm);
-    hipLaunchKernelGGL(k_split_ifc, gn, b, 0, c->st, c->G, D, B, phi);
-    hipLaunchKernelGGL(k_split_gas, dim3(grid_for((c->G.N + 15) / 16, 256, 2048)), b, 0, c->st, c->G, D, B);
-    hipLaunchKernelGGL(k_split_mass, dim3(1), dim3(256), 0, c->st, D, B);
-    const int *gate = D.counters + C_SPLIT;  // 2: some bubble split, volumes again
-    hipLaunchKernelGGL(k_bubble_accum, dim3(grid_for((c->G.N + 15) / 16, 256, 2048)), dim3(256), 0,
-                       c->st, c->G, D, phi, gate);
-    hipLaunchKernelGGL(k_bubble_finalize, dim3(1), dim3(64), 0, c->st, D, 0, gate, c->Ph.open_atm);
+    const dim3 b(256), gn(grid_for(c->G.N, 256, 2048)), gc(grid_for((c->G.N + 15) / 16, 256, 2048));
+    if (fused_phases(c)) {
+        hipLaunchKernelGGL(k_split, dim3(SYNC_BLOCKS), b, 0, c->st, c->G, D, B, phi, force, c->Ph.open_atm);
+    } else {
+        hipLaunchKernelGGL(k_split_start, gn, b, 0, c->st, c->G, D, B, force);
+        hipLaunchKernelGGL(k_ccl_union, gn, b, 0, c->st, c->G, D, B, force);
+        hipLaunchKernelGGL(k_ccl_flatten, gn, b, 0, c->st, c->G, D, B, force, c->Ph.open_atm);
+        hipLaunchKernelGGL(k_split_ifc, gn, b, 0, c->st, c->G, D, B, phi);
+        hipLaunchKernelGGL(k_split_gas, gc, b, 0, c->st, c->G, D, B);
+        hipLaunchKernelGGL(k_split_volumes, gc, b, 0, c->st, c->G, D, phi, c->Ph.open_atm);
+    }
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -379,14 +378,13 @@ int enqueue_conversions(fsl_ctx *c) {
     ProfScope ps(c, 1);
     Dev &D = c->D;
     dim3 g(LIST_BLOCKS), b(256);
-    hipLaunchKernelGGL(k_conv_mark, g, b, 0, c->st, D);
-    hipLaunchKernelGGL(k_conv_closure, g, b, 0, c->st, c->G, D);
-    hipLaunchKernelGGL(k_conv_init<ST>, g, b, 0, c->st, c->G, c->Ph, D);
-    hipLaunchKernelGGL(k_conv_finalize, g, b, 0, c->st, D);
-    hipLaunchKernelGGL(k_conv_excess<ST>, g, b, 0, c->st, c->G, c->Ph, D);
-    hipLaunchKernelGGL(k_conv_fill<ST>, g, b, 0, c->st, c->G, c->Ph, D);
-    hipLaunchKernelGGL(k_bubble_merge, dim3(1), dim3(64), 0, c->st, D);
-    hipLaunchKernelGGL(k_bubble_relabel, dim3(grid_for(c->G.N, 256, 2048)), b, 0, c->st, c->G, D);
+    if (fused_phases(c)) {
+        hipLaunchKernelGGL(k_conversions<ST>, dim3(SYNC_BLOCKS), b, 0, c->st, c->G, c->Ph, D);
+    } else {
+        hipLaunchKernelGGL(k_conv_closure<ST>, g, b, 0, c->st, c->G, c->Ph, D);
+        hipLaunchKernelGGL(k_conv_change<ST>, g, b, 0, c->st, c->G, c->Ph, D);
+        hipLaunchKernelGGL(k_conv_fill<ST>, g, b, 0, c->st, c->G, c->Ph, D);
+    }
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -502,8 +500,7 @@ template <int ST>
 int enqueue_steps(fsl_ctx *c, int n, int split) {
     for (int s = 0; s < n; ++s) {
         Dev &D = c->D;
-        hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, D);
-        if (D.wallF) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, c->st, D.wallF, 18LL, 0.0);
+        if (!c->counters_clear) hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, D);
         if (c->FS.n > 0 && D.wallF)  // face forces from the state at t
             hipLaunchKernelGGL(k_wall_forces<ST>, dim3(grid_for(c->FS.start[c->FS.n], 256, 1024)), dim3(256), 0, c->st,
                                c->G, c->Ph, D, c->FS);
@@ -538,7 +535,7 @@ int enqueue_steps(fsl_ctx *c, int n, int split) {
             rc = enqueue_particles<ST>(c);
             if (rc) return rc;
         }
-        rc = enqueue_bubbles<ST>(c, D.phi_nxt, 0);
+        rc = enqueue_bubbles<ST>(c, D.phi_nxt, 0, split);
         if (rc) return rc;
         if (split) {
             rc = enqueue_split<ST>(c, D.phi_nxt, 0);
@@ -546,6 +543,9 @@ int enqueue_steps(fsl_ctx *c, int n, int split) {
         }
         std::swap(D.fA, D.fB);
         std::swap(D.phi_cur, D.phi_nxt);
+        std::swap(D.counters, D.counters_nxt);  // cleared by this step's first kernel
+        std::swap(D.wallF, D.wallF_nxt);
+        c->counters_clear = 1;
     }
     return FSL_OK;
 }
@@ -555,6 +555,7 @@ template <int ST>
 int enqueue_coverage_full(fsl_ctx *c) {
     Dev Dv = c->D;
     Dv.fB = c->D.fA;  // the current state is in lattice A between steps
+    c->counters_clear = 0;
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, Dv);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
@@ -565,7 +566,7 @@ int enqueue_coverage_full(fsl_ctx *c) {
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
     LAUNCHCHK(c);
-    rc = enqueue_bubbles<ST>(c, Dv.phi_cur, 0);
+    rc = enqueue_bubbles<ST>(c, Dv.phi_cur, 0, 0);
     if (rc) return rc;
     return enqueue_split<ST>(c, Dv.phi_cur, 1);
 }
@@ -579,7 +580,7 @@ int dispatch_init(fsl_ctx *c, const InitGeo &I) {
     hipLaunchKernelGGL(k_init_closure_mark, dim3(g), dim3(256), 0, c->st, c->G, D);
     hipLaunchKernelGGL(k_init_pdf<ST>, dim3(g), dim3(256), 0, c->st, c->G, c->Ph, D, I);
     LAUNCHCHK(c);
-    int rc = enqueue_bubbles<ST>(c, D.phi_cur, 1);
+    int rc = enqueue_bubbles<ST>(c, D.phi_cur, 1, 0);
     if (rc) return rc;
     return enqueue_split<ST>(c, D.phi_cur, 1);
 }
@@ -603,6 +604,7 @@ int read_error(fsl_ctx *c) {
     if (e & ERR_LG) return fail(c, FSL_E_INVARIANT, "a liquid cell has a gas neighbour");
     if (e & ERR_PART)
         return fail(c, FSL_E_INVARIANT, "a sphere centre left the box or is not finite");
+    if (e & ERR_SYNC) return fail(c, FSL_E_HIP, "a grid barrier gave up: its blocks did not come to run together");
     return fail(c, FSL_E_NUMERIC, "device error");
 }
 
@@ -669,6 +671,7 @@ int window_backward(fsl_ctx *c, double dJ, double *dJ_dtau, double *dJ_dg) {
     Dev Dr = c->D;
     Dr.st_prev = Dr.st_cur = -1;  // recomputed segments neither use nor leave stored densities
     Dr.pacc = A.dummy;
+    Dr.counters_nxt = nullptr;  // no step: nothing to clear
     hipLaunchKernelGGL(k_fill_f64, dim3(grid_for((long long)A.nTiles * ADJ_NPART)), dim3(256), 0, c->st, A.part,
                        (long long)A.nTiles * ADJ_NPART, 0.0);
     hipLaunchKernelGGL(k_fill_f64, dim3(grid_for((long long)c->L.maxP * ACC_COPIES * ACC_STRIDE)), dim3(256), 0, c->st, A.dummy,
@@ -803,6 +806,9 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
     D.merges = (int2 *)(x + L.merges);
     D.pairs = (int2 *)(x + L.pairs);
     D.counters = (int *)(w + L.counters);
+    D.counters_nxt = D.counters + C_SET;
+    D.bused = D.counters + C_BUSED;
+    c->counters_clear = 0;
     D.err = (unsigned *)(w + L.ctl);
     D.ledger = (double *)(w + L.ctl + 8);
     D.ptab = (double *)(w + L.ptab);
@@ -822,6 +828,7 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
     D.kappa = cfg->sigma != 0.0 ? (float *)(w + L.kappa) : nullptr;
     D.wallu = (float *)(w + L.wallu);
     D.wallF = cfg->no_face_forces ? nullptr : (double *)(w + L.wallF);
+    D.wallF_nxt = D.wallF ? D.wallF + 18 : nullptr;
     D.rhow = cfg->max_particles > 0 ? (unsigned *)(w + L.rhow) : nullptr;
     D.st_prev = D.st_cur = -1;
     c->stamp = 1;
@@ -878,11 +885,12 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
 
     // control block, tables, accumulators
     hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, c->st, (double *)(w + L.ctl), 64LL, 0.0);
-    if (D.wallF) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, c->st, D.wallF, 18LL, 0.0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->st, D.counters, 64LL, 0);
+    if (D.wallF) hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, c->st, D.wallF, 36LL, 0.0);
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->st, D.counters, (long long)C_WORDS, 0);
+    hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, c->st, D.bacc, (long long)L.maxB * BACC_STRIDE, 0.0);
     {
         const int used = cfg->n_gas_spheres + 1;  // bubble ids in use: atmosphere and gas spheres
-        if (hipMemcpyAsync(D.counters + C_BUSED, &used, 4, hipMemcpyHostToDevice, c->st) != hipSuccess ||
+        if (hipMemcpyAsync(D.bused, &used, 4, hipMemcpyHostToDevice, c->st) != hipSuccess ||
             hipStreamSynchronize(c->st) != hipSuccess) {
             delete c;
             return FSL_E_HIP;
@@ -1104,8 +1112,9 @@ int fsl_particles_set(fsl_ctx *c, int n, const double *x, const double *u, const
 
 int fsl_walls_get(fsl_ctx *c, double F[18]) {
     if (!c || !F) return FSL_E_ARG;
+    // a step hands its accumulator over to the next one: the last step's is the other
     if (!c->D.wallF) return fail(c, FSL_E_ARG, "walls_get: the context was made with no_face_forces");
-    HIPCHK(c, hipMemcpyAsync(F, c->D.wallF, 18 * sizeof(double), hipMemcpyDeviceToHost, c->st));
+    HIPCHK(c, hipMemcpyAsync(F, c->D.wallF_nxt, 18 * sizeof(double), hipMemcpyDeviceToHost, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
     return read_error(c);
 }
@@ -1138,7 +1147,7 @@ int fsl_bubbles_get(fsl_ctx *c, fsl_bubble *out, int cap, int *n) {
     HIPCHK(c, hipMemcpyAsync(tab.data(), c->D.btab, tab.size() * 8, hipMemcpyDeviceToHost, c->st));
     HIPCHK(c, hipMemcpyAsync(root.data(), c->D.broot, nt * 4, hipMemcpyDeviceToHost, c->st));
     HIPCHK(c, hipMemcpyAsync(alive.data(), c->D.balive, nt * 4, hipMemcpyDeviceToHost, c->st));
-    HIPCHK(c, hipMemcpyAsync(&nb, c->D.counters + C_BUSED, 4, hipMemcpyDeviceToHost, c->st));
+    HIPCHK(c, hipMemcpyAsync(&nb, c->D.bused, 4, hipMemcpyDeviceToHost, c->st));
     int rc = read_error(c);
     nb = std::min(std::max(nb, 0), nt);
     if (n) *n = nb;
@@ -1181,12 +1190,13 @@ int fsl_bubbles_set(fsl_ctx *c, int n, const double *M, const int *root, const i
     HIPCHK(c, hipMemcpyAsync(c->D.btab, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipMemcpyAsync(c->D.broot, rt.data(), nt * 4, hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipMemcpyAsync(c->D.balive, al.data(), nt * 4, hipMemcpyHostToDevice, c->st));
-    HIPCHK(c, hipMemcpyAsync(c->D.counters + C_BUSED, &n, 4, hipMemcpyHostToDevice, c->st));
+    HIPCHK(c, hipMemcpyAsync(c->D.bused, &n, 4, hipMemcpyHostToDevice, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
     // the lists a step leaves are not read again: the splitting pass below clears no marks
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, c->D);
+    c->counters_clear = 0;
     int rc = by_storage(c, [&](auto st) {
-        int r = enqueue_bubbles<decltype(st)::value>(c, c->D.phi_cur, 0);
+        int r = enqueue_bubbles<decltype(st)::value>(c, c->D.phi_cur, 0, 0);
         return r ? r : enqueue_split<decltype(st)::value>(c, c->D.phi_cur, 1);
     });
     if (rc) return rc;

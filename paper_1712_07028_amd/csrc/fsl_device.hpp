@@ -52,6 +52,8 @@ constexpr unsigned ERR_LG = 1u, ERR_NAN = 2u, ERR_CAP = 4u, ERR_VOL = 8u;
 // a sphere centre left the box, or came closer than R + 1 to a periodic face (the
 // coverage, pair search and lever arms do not wrap)
 constexpr unsigned ERR_PART = 16u;
+// a grid barrier gave up (the blocks of one launch did not come to run together)
+constexpr unsigned ERR_SYNC = 32u;
 
 // conversion marks (one byte per cell, zero outside the conversion phase)
 constexpr uint8_t CV_F = 1, CV_E0 = 2, CV_E = 4, CV_NEWG = 8, CV_NEWL = 16;
@@ -68,10 +70,18 @@ enum Counter {
     C_NCOMP,  // gas components listed by the splitting pass
     C_MERGED, // some bubbles merged in this step: cells are relabelled to their roots
     C_NGEN,   // tiles listed for the general path of the stream-collide step
+    C_BAR,    // arrivals at the grid barriers of the fused conversion phases
+    C_BARS,   // ... of the fused labelling
+    C_DONEC,  // blocks of the last conversion phase that are done
+    C_DONEB,  // blocks of the bubble pass that are done
+    C_DONES,  // blocks of a splitting phase that are done
     C_COUNT
 };
-// persistent slot (not reset per step): number of bubble ids in use
-constexpr int C_BUSED = 63;
+// Two sets of counters take turns: a step uses one and its first kernel clears the
+// other for the next step, so that clearing costs no launch.  The persistent word after
+// them (not cleared per step) is the number of bubble ids in use.
+constexpr int C_SET = 48, C_BUSED = 127, C_WORDS = 128;
+static_assert(C_COUNT <= C_SET && 2 * C_SET <= C_BUSED, "counter sets");
 
 // particle table: 16 doubles per particle
 // P_OVL: 1 when the coverage update must resolve overlaps through claims (a sphere
@@ -161,10 +171,12 @@ struct Dev {
     double *uncRho;                  // per uncover event: decided density
     int *uncDec;                     // per uncover event: type | bubble << 8
     int2 *merges, *pairs;
-    int *counters;
+    int *counters, *counters_nxt;    // this step's set of counters and the next step's
+    int *bused;                      // number of bubble ids in use
     unsigned *err;
     double *ledger;                  // [0] ledger
-    double *wallF;                   // force on each no-slip face over the last step [18]
+    double *wallF, *wallF_nxt;       // force on each no-slip face in this step [18], and the
+                                     // next step's accumulator
     double *ptab, *pacc, *pFT, *pFTp, *pFl; // particles (pFTp: previous step's F, T)
     float4 *pmir;                    // FP32 mirror per particle (PMir: anchor, fraction, u, omega)
     int *gridStart, *gridCount, *gridIdx;
@@ -269,6 +281,79 @@ __device__ __forceinline__ void wave_append(bool pred, int value, int *list, int
         if (slot < cap) list[slot] = value;
         else atomicOr(err, ERR_CAP);
     }
+}
+
+// the D3Q19 components of a direction that differs between lanes: two bits each
+// (value + 1) in a 64-bit constant, where the arrays of cx, cy, cz would be loads
+constexpr unsigned long long pack_dirs(int a) {
+    unsigned long long m = 0;
+    for (int q = 0; q < Q; ++q) m |= (unsigned long long)((a == 0 ? cx(q) : a == 1 ? cy(q) : cz(q)) + 1) << (2 * q);
+    return m;
+}
+template <int A> __device__ __forceinline__ int dir_comp(int q) {
+    constexpr unsigned long long m = pack_dirs(A);
+    return (int)((m >> (2 * q)) & 3ull) - 1;
+}
+
+// a barrier between two phases of one block that hand each other global memory, atomics
+// among it: the loads that follow see what every wave of the block wrote before
+__device__ __forceinline__ void block_phase() {
+    __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// A barrier between two phases over the first nblk blocks of a launch.  The callers launch
+// at most SYNC_BLOCKS blocks of 256 threads, a sixteenth of what the device holds, so the
+// blocks come to run together whatever else is running (kernels in other streams end, and
+// sixteen launches of this kind at once would still fit); one block needs no device
+// barrier.  bar counts arrivals since the step's counters were cleared, target the
+// arrivals the next barrier waits for.  Every wave's stores have left the wave before its
+// block arrives; one thread releases them to the device and acquires the others'.  The
+// wait is bounded: a launch that lost a block reports an error instead of hanging.
+constexpr int SYNC_BLOCKS = 128;
+struct GridBarrier {
+    int *bar;
+    int nblk, target;
+    unsigned *err;
+    __device__ __forceinline__ void wait() {
+        if (nblk == 1) {
+            block_phase();
+            return;
+        }
+        target += nblk;
+        __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            __threadfence();
+            __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int spin = 0; __hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++spin) {
+                __builtin_amdgcn_s_sleep(1);
+                if (spin > (1 << 23)) {
+                    atomicOr(err, ERR_SYNC);
+                    break;
+                }
+            }
+            __threadfence();
+        }
+        __syncthreads();
+    }
+};
+
+// true in every thread of the block that finishes last of nblk (its reads then see what
+// the others wrote); done counts the blocks and is left at zero
+__device__ __forceinline__ bool last_block(int *done, int nblk) {
+    __shared__ int last;
+    __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
+        __threadfence();
+        if (last) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    return last != 0;
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

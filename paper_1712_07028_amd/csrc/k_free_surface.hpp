@@ -1,22 +1,27 @@
 // k_free_surface.hpp -- list-driven cell conversions (Sec. 2.2, Fig.
 // cellConversions) and the bubble model (end of Sec. 2.2).
 //
-// The stream-collide kernel leaves two lists of interface cells: filled
-// (phi >= 1 - eps_c) and emptied (phi <= eps_c).  The kernels below, in order:
-//   mark     : conversion marks of the listed cells
-//   closure  : conflict rule (an emptied cell next to a filled one stays interface),
-//              gas neighbours of filled cells and liquid neighbours of emptied cells
-//              become new interface cells (one winner per cell by an atomic OR)
-//   init     : new interface cells from gas take the equilibrium at the mean density
-//              and velocity of their liquid/interface neighbours, m = 0; new
-//              interface cells from liquid keep m = rho and take the bubble id of
-//              their first emptied neighbour
-//   finalize : cell types
-//   excess   : excess mass (m - rho, or m) shared equally by the neighbours that are
-//              interface now (FP64 atomics), or paid into the ledger
-//   fill     : fill levels of the recipients, marks cleared, invariant checked,
-//              bubble merges recorded
-// Every step of this phase touches only the listed cells and their neighbours.
+// The stream-collide kernel leaves two lists of interface cells, filled (phi >= 1 -
+// eps_c) and emptied (phi <= eps_c), and marks them (CV_F, CV_E0).  Three phases follow:
+//   closure : conflict rule (an emptied cell next to a filled one stays interface);
+//             gas neighbours of filled cells and liquid neighbours of emptied cells
+//             become new interface cells (one winner per cell by an atomic OR), the
+//             former with m = 0, the latter with m = rho
+//   change  : new interface cells from gas take the equilibrium at the mean density and
+//             velocity of their liquid/interface neighbours; those from liquid the
+//             bubble id of their first emptied neighbour; cell types; excess mass (m -
+//             rho, or m) shared equally by the neighbours that are interface now (FP64
+//             atomics), or paid into the ledger
+//   fill    : fill levels of the recipients, marks cleared, invariant checked, bubble
+//             merges recorded and carried out
+// Every phase touches only the listed cells and their neighbours.  Cell types change in
+// the phase that also needs the old and the new types of neighbours: both follow from
+// the type a neighbour shows, old or new, and its mark, which that phase does not change.
+//
+// A listed cell is worked by 32 lanes, lane q taking the neighbour along direction q: the
+// lists are short (tens of cells on a 128^3 pool, thousands on a 500 x 500 surface), so
+// a phase costs the latency of its dependent loads, which one thread per cell paid 18
+// times over (128^3 pool with 1,400 spheres: 19 to 22 us per phase, six phases).
 #pragma once
 
 #include "fsl_device.hpp"
@@ -117,123 +122,6 @@ __device__ __forceinline__ void list_push(const Dev &D, int *list, int which, in
 
 #define GRID_STRIDE(i, n) for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += gridDim.x * blockDim.x)
 
-__global__ void k_conv_mark(Dev D) {
-    int nF = list_len(D, C_NF), nE = list_len(D, C_NE0);
-    GRID_STRIDE(i, nF) D.cv[D.lF[i]] = CV_F;
-    GRID_STRIDE(i, nE) D.cv[D.lE0[i]] = CV_E0;
-}
-
-__global__ void k_conv_closure(Geom G, Dev D) {
-    int nF = list_len(D, C_NF), nE = list_len(D, C_NE0);
-    GRID_STRIDE(i, nE) {
-        int c = D.lE0[i], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        bool keep = true;
-        for (int q = 1; q < Q && keep; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n >= 0 && D.cv[n] == CV_F) keep = false;
-        }
-        if (!keep) continue;
-        cv_or(D.cv, c, CV_E);
-        list_push(D, D.lE, C_NE, c);
-        for (int q = 1; q < Q; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n < 0 || D.flags[n] != LIQ) continue;
-            if (!(cv_or(D.cv, n, CV_NEWL) & CV_NEWL)) list_push(D, D.lNL, C_NNL, n);
-        }
-    }
-    GRID_STRIDE(i, nF) {
-        int c = D.lF[i], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        for (int q = 1; q < Q; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n < 0 || D.flags[n] != GAS) continue;
-            if (!(cv_or(D.cv, n, CV_NEWG) & CV_NEWG)) list_push(D, D.lNG, C_NNG, n);
-        }
-    }
-}
-
-template <int ST>
-__global__ void k_conv_init(Geom G, Phys Ph, Dev D) {
-    int nG = list_len(D, C_NNG), nL = list_len(D, C_NNL);
-    GRID_STRIDE(i, nG) {
-        int c = D.lNG[i], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        float rs = 0.f, s0 = 0.f, s1 = 0.f, s2 = 0.f;
-        int cnt = 0;
-        for (int q = 1; q < Q; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n < 0) continue;
-            uint8_t f = D.flags[n];
-            if (f != LIQ && f != IFC) continue;
-            float r, a, b, e;
-            cell_rho_u<ST>(G, Ph, D.fB, n, r, a, b, e);
-            rs += r;
-            s0 += a;
-            s1 += b;
-            s2 += e;
-            ++cnt;
-        }
-        float inv = 1.0f / (float)cnt;
-        store_equilibrium<ST>(G, Ph, D.fB, c, (double)(rs * inv), s0 * inv, s1 * inv, s2 * inv);
-        D.m[c] = 0.0;
-    }
-    GRID_STRIDE(i, nL) {
-        int c = D.lNL[i], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        D.m[c] = cell_rho<ST>(G, D, Ph, D.fB, c);
-        for (int q = 1; q < Q; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n >= 0 && (D.cv[n] & CV_E)) { D.bub[c] = D.bub[n]; break; }
-        }
-    }
-}
-
-__global__ void k_conv_finalize(Dev D) {
-    int nF = list_len(D, C_NF), nE = list_len(D, C_NE), nG = list_len(D, C_NNG), nL = list_len(D, C_NNL);
-    GRID_STRIDE(i, nF) D.flags[D.lF[i]] = LIQ;
-    GRID_STRIDE(i, nE) D.flags[D.lE[i]] = GAS;
-    GRID_STRIDE(i, nG) D.flags[D.lNG[i]] = IFC;
-    GRID_STRIDE(i, nL) D.flags[D.lNL[i]] = IFC;
-}
-
-template <int ST>
-__device__ __forceinline__ void share_excess(const Geom &G, const Dev &D, int c, double ex) {
-    int x, y, z;
-    cell_xyz(G, c, x, y, z);
-    int k = 0;
-    for (int q = 1; q < Q; ++q) {
-        int n = nbr_idx(G, x, y, z, q, 1);
-        if (n >= 0 && D.flags[n] == IFC) ++k;
-    }
-    if (k == 0) {
-        unsafeAtomicAdd(D.ledger, ex);
-        return;
-    }
-    double part = ex / k;
-    for (int q = 1; q < Q; ++q) {
-        int n = nbr_idx(G, x, y, z, q, 1);
-        if (n >= 0 && D.flags[n] == IFC) unsafeAtomicAdd(D.m + n, part);
-    }
-}
-
-template <int ST>
-__global__ void k_conv_excess(Geom G, Phys Ph, Dev D) {
-    int nF = list_len(D, C_NF), nE = list_len(D, C_NE);
-    GRID_STRIDE(i, nF) {
-        int c = D.lF[i];
-        double ex = D.m[c] - cell_rho<ST>(G, D, Ph, D.fB, c);
-        D.m[c] = 0.0;
-        share_excess<ST>(G, D, c, ex);
-    }
-    GRID_STRIDE(i, nE) {
-        int c = D.lE[i];
-        double ex = D.m[c];
-        D.m[c] = 0.0;
-        share_excess<ST>(G, D, c, ex);
-    }
-}
-
 // root of a bubble id through the merge table; ids outside the table map to 0
 __device__ __forceinline__ int bubble_root(const Dev &D, int b) {
     for (int it = 0; it < 64; ++it) {
@@ -245,46 +133,184 @@ __device__ __forceinline__ int bubble_root(const Dev &D, int b) {
     return b < 0 || b >= D.maxB ? 0 : b;
 }
 
+// item i of a phase is worked by 32 lanes; grp and ngrp: this half wave's number and how
+// many there are.  The loop runs the same rounds in both halves of a wave.
+struct Items {
+    int grp, ngrp, q, half;
+    __device__ __forceinline__ Items(int block, int nblocks) {
+        q = (int)(threadIdx.x & 31u);
+        half = (int)((threadIdx.x >> 5) & 1u);
+        const int per = (int)(blockDim.x >> 5);
+        grp = block * per + (int)(threadIdx.x >> 5);
+        ngrp = nblocks * per;
+    }
+    // the lanes of this half wave with pred, as a 32-bit set (bit q: lane q)
+    __device__ __forceinline__ unsigned any(bool pred) const { return (unsigned)(__ballot(pred) >> (32 * half)); }
+    __device__ __forceinline__ int from(int v, int lane) const { return __shfl(v, 32 * half + lane); }
+    __device__ __forceinline__ float from(float v, int lane) const { return __shfl(v, 32 * half + lane); }
+    __device__ __forceinline__ double from(double v, int lane) const { return __shfl(v, 32 * half + lane); }
+};
+#define ITEM_LOOP(W, i, n) for (int i = (W).grp, i##0 = (W).grp - (W).half; i##0 < (n); i += (W).ngrp, i##0 += (W).ngrp)
+
+// neighbour of cell c along the lane's direction q (-1 beyond a wall; lanes whose q is
+// no direction, or without a cell: -1)
+__device__ __forceinline__ int lane_nbr(const Geom &G, int c, int q, bool has) {
+    if (!has || q < 1 || q >= Q) return -1;
+    int x, y, z;
+    cell_xyz(G, c, x, y, z);
+    int a = x + dir_comp<0>(q), b = y + dir_comp<1>(q), d = z + dir_comp<2>(q);
+    if (a < 0 || a >= G.nx) { if (!G.per[0]) return -1; a = wrapc(a, G.nx); }
+    if (b < 0 || b >= G.ny) { if (!G.per[1]) return -1; b = wrapc(b, G.ny); }
+    if (d < 0 || d >= G.nz) { if (!G.per[2]) return -1; d = wrapc(d, G.nz); }
+    return a + G.nx * (b + G.ny * d);
+}
+
 template <int ST>
-__global__ void k_conv_fill(Geom G, Phys Ph, Dev D) {
-    int nF = list_len(D, C_NF), nE = list_len(D, C_NE);
-    int nE0 = list_len(D, C_NE0), nG = list_len(D, C_NNG), nL = list_len(D, C_NNL);
-    GRID_STRIDE(i, nF + nE) {
-        const bool filled = i < nF;
-        int c = filled ? D.lF[i] : D.lE[i - nF], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        D.phi_nxt[c] = filled ? 1.0 : 0.0;
+__device__ __forceinline__ void conv_closure(const Geom &G, const Phys &Ph, const Dev &D, const Items &W) {
+    const int nF = list_len(D, C_NF), nE = list_len(D, C_NE0);
+    ITEM_LOOP(W, i, nE) {
+        const bool has = i < nE;
+        const int c = has ? D.lE0[i] : 0;
+        const int n = lane_nbr(G, c, W.q, has);
+        const uint8_t nm = n >= 0 ? D.cv[n] : 0, nf = n >= 0 ? D.flags[n] : WALL;
+        const bool keep = has && W.any(nm == CV_F) == 0u;
+        if (keep && W.q == 0) cv_or(D.cv, c, CV_E);
+        wave_append(keep && W.q == 0, c, D.lE, D.counters + C_NE, D.cap, D.err);
+        const bool won = keep && nf == LIQ && !(cv_or(D.cv, n, CV_NEWL) & CV_NEWL);
+        wave_append(won, n, D.lNL, D.counters + C_NNL, D.cap, D.err);
+        if (won) D.m[n] = cell_rho<ST>(G, D, Ph, D.fB, n);
+    }
+    ITEM_LOOP(W, j, nF) {
+        const bool has = j < nF;
+        const int c = has ? D.lF[j] : 0;
+        const int n = lane_nbr(G, c, W.q, has);
+        const bool won = n >= 0 && D.flags[n] == GAS && !(cv_or(D.cv, n, CV_NEWG) & CV_NEWG);
+        wave_append(won, n, D.lNG, D.counters + C_NNG, D.cap, D.err);
+        if (won) D.m[n] = 0.0;
+    }
+}
+
+// a neighbour's type before and after the change phase, from the type it shows and its mark
+__device__ __forceinline__ bool was_fluid(uint8_t f, uint8_t m) {  // liquid or interface before
+    return (m & (CV_F | CV_E0 | CV_NEWL)) ? true : (m & CV_NEWG) ? false : f == LIQ || f == IFC;
+}
+__device__ __forceinline__ bool is_interface(uint8_t f, uint8_t m) {  // interface after
+    return (m & (CV_NEWG | CV_NEWL)) ? true : (m & (CV_F | CV_E)) ? false : f == IFC;
+}
+
+// excess mass of cell c (the value of the half wave's lane 0) to its neighbours
+__device__ __forceinline__ void share_excess(const Geom &G, const Dev &D, const Items &W, int c, bool has, double ex) {
+    const int n = lane_nbr(G, c, W.q, has);
+    const bool to = n >= 0 && is_interface(D.flags[n], D.cv[n]);
+    const int k = __popc(W.any(to));
+    ex = W.from(ex, 0);
+    if (!has) return;
+    if (k == 0) {
+        if (W.q == 0) unsafeAtomicAdd(D.ledger, ex);
+        return;
+    }
+    const double part = ex / k;
+    if (to) unsafeAtomicAdd(D.m + n, part);
+}
+
+template <int ST>
+__device__ __forceinline__ void conv_change(const Geom &G, const Phys &Ph, const Dev &D, const Items &W) {
+    const int nG = list_len(D, C_NNG), nL = list_len(D, C_NNL), nF = list_len(D, C_NF), nE = list_len(D, C_NE);
+    ITEM_LOOP(W, i, nG) {
+        const bool has = i < nG;
+        const int c = has ? D.lNG[i] : 0;
+        const int n = lane_nbr(G, c, W.q, has);
+        const bool src = n >= 0 && was_fluid(D.flags[n], D.cv[n]);
+        float r = 0.f, a = 0.f, b = 0.f, e = 0.f;
+        if (src) cell_rho_u<ST>(G, Ph, D.fB, n, r, a, b, e);
+        const unsigned m = W.any(src);
+        // the mean over the neighbours, summed in direction order
+        float rs = 0.f, s0 = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
         for (int q = 1; q < Q; ++q) {
-            int n = nbr_idx(G, x, y, z, q, 1);
-            if (n < 0) continue;
-            uint8_t f = D.flags[n];
-            if (f == IFC) {
-                D.phi_nxt[n] = D.m[n] / cell_rho<ST>(G, D, Ph, D.fB, n);
-            } else if (filled && f == GAS) {
-                atomicOr(D.err, ERR_LG);
-            } else if (!filled && f == LIQ) {
-                atomicOr(D.err, ERR_LG);
-            } else if (!filled && f == GAS) {
-                int a = bubble_root(D, D.bub[c]), b = bubble_root(D, D.bub[n]);
-                if (a != b) {
-                    int s = atomicAdd(D.counters + C_NMERGE, 1);
-                    if (s < D.cap) D.merges[s] = make_int2(a, b);
-                    else atomicOr(D.err, ERR_CAP);
-                }
+            const float rq = W.from(r, q), aq = W.from(a, q), bq = W.from(b, q), eq = W.from(e, q);
+            if ((m >> q) & 1u) {
+                rs += rq;
+                s0 += aq;
+                s1 += bq;
+                s2 += eq;
+            }
+        }
+        if (has && W.q == 0) {
+            const float inv = 1.0f / (float)__popc(m);
+            store_equilibrium<ST>(G, Ph, D.fB, c, (double)(rs * inv), s0 * inv, s1 * inv, s2 * inv);
+            D.flags[c] = IFC;
+        }
+    }
+    ITEM_LOOP(W, j, nL) {
+        const bool has = j < nL;
+        const int c = has ? D.lNL[j] : 0;
+        const int n = lane_nbr(G, c, W.q, has);
+        const unsigned m = W.any(n >= 0 && (D.cv[n] & CV_E));
+        if (has && m && W.q == __ffs(m) - 1) D.bub[c] = D.bub[n];
+        if (has && W.q == 0) D.flags[c] = IFC;
+    }
+    ITEM_LOOP(W, k, nF) {
+        const bool has = k < nF;
+        const int c = has ? D.lF[k] : 0;
+        double ex = 0.0;
+        if (has && W.q == 0) {
+            ex = D.m[c] - cell_rho<ST>(G, D, Ph, D.fB, c);
+            D.m[c] = 0.0;
+            D.flags[c] = LIQ;
+        }
+        share_excess(G, D, W, c, has, ex);
+    }
+    ITEM_LOOP(W, l, nE) {
+        const bool has = l < nE;
+        const int c = has ? D.lE[l] : 0;
+        double ex = 0.0;
+        if (has && W.q == 0) {
+            ex = D.m[c];
+            D.m[c] = 0.0;
+            D.flags[c] = GAS;
+        }
+        share_excess(G, D, W, c, has, ex);
+    }
+}
+
+template <int ST>
+__device__ __forceinline__ void conv_fill(const Geom &G, const Phys &Ph, const Dev &D, const Items &W, int thread,
+                                          int nthreads) {
+    const int nF = list_len(D, C_NF), nE = list_len(D, C_NE);
+    const int nE0 = list_len(D, C_NE0), nG = list_len(D, C_NNG), nL = list_len(D, C_NNL);
+    ITEM_LOOP(W, i, nF + nE) {
+        const bool has = i < nF + nE, filled = i < nF;
+        const int c = !has ? 0 : filled ? D.lF[i] : D.lE[i - nF];
+        if (has && W.q == 0) D.phi_nxt[c] = filled ? 1.0 : 0.0;
+        const int n = lane_nbr(G, c, W.q, has);
+        if (n < 0) continue;
+        const uint8_t f = D.flags[n];
+        if (f == IFC) {
+            D.phi_nxt[n] = D.m[n] / cell_rho<ST>(G, D, Ph, D.fB, n);
+        } else if (filled ? f == GAS : f == LIQ) {
+            atomicOr(D.err, ERR_LG);
+        } else if (!filled && f == GAS) {
+            const int a = bubble_root(D, D.bub[c]), b = bubble_root(D, D.bub[n]);
+            if (a != b) {
+                const int s = atomicAdd(D.counters + C_NMERGE, 1);
+                if (s < D.cap) D.merges[s] = make_int2(a, b);
+                else atomicOr(D.err, ERR_CAP);
             }
         }
     }
-    GRID_STRIDE(i, nF) D.cv[D.lF[i]] = 0;
+    for (int i = thread; i < nF; i += nthreads) D.cv[D.lF[i]] = 0;
     // emptied cells are new gas: marked for the splitting test
-    GRID_STRIDE(i, nE0) D.cv[D.lE0[i]] = (D.cv[D.lE0[i]] & CV_E) ? CV_GAD : 0;
-    GRID_STRIDE(i, nG) D.cv[D.lNG[i]] = CV_GRM;  // left the gas: for the splitting test
-    GRID_STRIDE(i, nL) D.cv[D.lNL[i]] = 0;
+    for (int i = thread; i < nE0; i += nthreads) D.cv[D.lE0[i]] = (D.cv[D.lE0[i]] & CV_E) ? CV_GAD : 0;
+    for (int i = thread; i < nG; i += nthreads) D.cv[D.lNG[i]] = CV_GRM;  // left the gas: for the splitting test
+    for (int i = thread; i < nL; i += nthreads) D.cv[D.lNL[i]] = 0;
 }
 
-// serial union of merged bubbles: the lower root id survives, gas masses add
-__global__ void k_bubble_merge(Dev D) {
-    if (blockIdx.x || threadIdx.x) return;
-    int n = list_len(D, C_NMERGE);
+// serial union of merged bubbles: the lower root id survives, gas masses add.  The cells
+// of merged bubbles are relabelled to their root by the bubble pass of the step.
+__device__ __forceinline__ void merge_bubbles(const Dev &D) {
+    int n = __hip_atomic_load(D.counters + C_NMERGE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n > D.cap) n = D.cap;
     for (int i = 0; i < n; ++i) {
         int a = bubble_root(D, D.merges[i].x), b = bubble_root(D, D.merges[i].y);
         if (a == b) continue;
@@ -296,33 +322,55 @@ __global__ void k_bubble_merge(Dev D) {
     }
 }
 
-// after a merge every gas and interface cell carries its root id, so that the merged
-// ids hold no cells and a split can take them again
-__global__ void k_bubble_relabel(Geom G, Dev D) {
-    if (D.counters[C_MERGED] == 0) return;
-    for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < G.N;
-         c += (long long)gridDim.x * blockDim.x) {
-        const uint8_t f = D.flags[c];
-        if (f == GAS || f == IFC) D.bub[c] = (uint16_t)bubble_root(D, D.bub[c]);
-    }
+// The phases as one launch each (large boxes: any number of listed cells) ...
+template <int ST>
+__global__ __launch_bounds__(256) void k_conv_closure(Geom G, Phys Ph, Dev D) {
+    conv_closure<ST>(G, Ph, D, Items(blockIdx.x, gridDim.x));
+}
+template <int ST>
+__global__ __launch_bounds__(256) void k_conv_change(Geom G, Phys Ph, Dev D) {
+    conv_change<ST>(G, Ph, D, Items(blockIdx.x, gridDim.x));
+}
+template <int ST>
+__global__ __launch_bounds__(256) void k_conv_fill(Geom G, Phys Ph, Dev D) {
+    conv_fill<ST>(G, Ph, D, Items(blockIdx.x, gridDim.x), blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+    if (last_block(D.counters + C_DONEC, gridDim.x) && threadIdx.x == 0) merge_bubbles(D);
+}
+// ... or all of them in one launch (small boxes): a launch costs 4.5 us, a barrier of the
+// block a fraction of one and a grid barrier about two.  As many blocks take part as the
+// lists fill, two cells per half wave; the others leave.
+template <int ST>
+__global__ __launch_bounds__(256) void k_conversions(Geom G, Phys Ph, Dev D) {
+    const int n = list_len(D, C_NF) + list_len(D, C_NE0);
+    const int nblk = min((int)gridDim.x, (n + 15) / 16);
+    if ((int)blockIdx.x >= nblk) return;
+    GridBarrier B{D.counters + C_BAR, nblk, 0, D.err};
+    const Items W(blockIdx.x, nblk);
+    conv_closure<ST>(G, Ph, D, W);
+    B.wait();
+    conv_change<ST>(G, Ph, D, W);
+    B.wait();
+    conv_fill<ST>(G, Ph, D, W, blockIdx.x * blockDim.x + threadIdx.x, nblk * blockDim.x);
+    if (last_block(D.counters + C_DONEC, nblk) && threadIdx.x == 0) merge_bubbles(D);
 }
 
 // ---- bubble volumes: dense pass over the cell types ------------------------------
-// gate: null, or a flag that must read 2 (a bubble split) for the kernel to run
-__global__ void k_bubble_zero(Dev D, const int *gate) {
-    if (gate && *gate != 2) return;
-    GRID_STRIDE(i, D.nb * BACC_STRIDE) D.bacc[i] = 0.0;
-}
+struct BubbleLds {
+    double acc[64 * BACC_STRIDE];
+    int root[64];
+};
 
 // V_b = #gas cells + sum over interface cells of (1 - phi), with centroid moments;
-// per-block LDS accumulation (FP64), one global atomic per block and component
-__global__ __launch_bounds__(256) void k_bubble_accum(Geom G, Dev D, const double *phi, const int *gate) {
-    if (gate && *gate != 2) return;
-    __shared__ double acc[64 * BACC_STRIDE];
-    __shared__ int root[64];
+// per-block LDS accumulation (FP64), one global atomic per block and component.  The cells
+// of a bubble merged away in this step take their root's id on the way (relabel), so that
+// merged ids hold no cells and a split can take them again.  A thread takes 16
+// consecutive cells (one 16-byte load of types); 16 gas cells of one bubble in one row,
+// which is nearly every chunk with gas, add in closed form (counts and coordinate sums
+// are integers, exact in FP64).
+__device__ __forceinline__ void bubble_accum(const Geom &G, const Dev &D, const double *phi, BubbleLds &L, bool relabel) {
     const int nb = D.nb;
-    for (int i = threadIdx.x; i < nb * BACC_STRIDE; i += blockDim.x) acc[i] = 0.0;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) root[i] = bubble_root(D, i);
+    for (int i = threadIdx.x; i < nb * BACC_STRIDE; i += blockDim.x) L.acc[i] = 0.0;
+    for (int i = threadIdx.x; i < nb; i += blockDim.x) L.root[i] = bubble_root(D, i);
     __syncthreads();
     const long long N = G.N;
     const long long nchunk = (N + 15) / 16;
@@ -333,7 +381,7 @@ __global__ __launch_bounds__(256) void k_bubble_accum(Geom G, Dev D, const doubl
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, a4 = 0.0, a5 = 0.0;
     auto flush = [&]() {
         if (bc >= 0) {
-            double *a = acc + bc * BACC_STRIDE;
+            double *a = L.acc + bc * BACC_STRIDE;
             atomicAdd(a + 0, a0);
             atomicAdd(a + 1, a1);
             atomicAdd(a + 2, a2);
@@ -345,34 +393,53 @@ __global__ __launch_bounds__(256) void k_bubble_accum(Geom G, Dev D, const doubl
     };
     for (long long ch = blockIdx.x * (long long)blockDim.x + threadIdx.x; ch < nchunk;
          ch += (long long)gridDim.x * blockDim.x) {
-        long long c0 = ch * 16;
-        uint4 f4 = *(const uint4 *)(D.flags + c0);
-        uint32_t wds[4] = {f4.x, f4.y, f4.z, f4.w};
-        bool any = false;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            uint32_t v = wds[k];
-            // a byte is GAS (0) or IFC (2): test each byte
-#pragma unroll
-            for (int bb = 0; bb < 4; ++bb) {
-                uint32_t f = (v >> (8 * bb)) & 0xffu;
-                any |= (f == GAS || f == IFC) && (c0 + 4 * k + bb < N);
+        const long long c0 = ch * 16;
+        const uint4 f4 = *(const uint4 *)(D.flags + c0);
+        // gas (0) and interface (2) are the even types
+        if (((f4.x & f4.y & f4.z & f4.w) & 0x01010101u) == 0x01010101u) continue;
+        int x = (int)(c0 % G.nx);
+        const int yz = (int)(c0 / G.nx);
+        int y = yz % G.ny, z = yz / G.ny;
+        if ((f4.x | f4.y | f4.z | f4.w) == 0u && c0 + 16 <= N && x + 16 <= G.nx && !relabel) {
+            const uint4 u = *(const uint4 *)(D.bub + c0), v = *(const uint4 *)(D.bub + c0 + 8);
+            const unsigned id2 = (u.x & 0xffffu) * 0x10001u;
+            if (((u.x ^ id2) | (u.y ^ id2) | (u.z ^ id2) | (u.w ^ id2) | (v.x ^ id2) | (v.y ^ id2) | (v.z ^ id2) |
+                 (v.w ^ id2)) == 0u) {
+                const int id = (int)(id2 & 0xffffu);
+                const int b = id < nb ? L.root[id] : 0;
+                if (b != bc) {
+                    flush();
+                    bc = b;
+                }
+                a0 += 16.0;
+                a1 += 16.0 * x + 120.0;
+                a2 += 16.0 * y;
+                a3 += 16.0 * z;
+                a4 += 16.0;
+                continue;
             }
         }
-        if (!any) continue;
-        for (int k = 0; k < 16; ++k) {
+        const uint32_t wds[4] = {f4.x, f4.y, f4.z, f4.w};
+        for (int k = 0; k < 16; ++k, ++x) {
+            if (x == G.nx) {
+                x = 0;
+                if (++y == G.ny) {
+                    y = 0;
+                    ++z;
+                }
+            }
             const int c = (int)(c0 + k);
             if (c >= N) break;
-            uint32_t f = (wds[k >> 2] >> (8 * (k & 3))) & 0xffu;
+            const uint32_t f = (wds[k >> 2] >> (8 * (k & 3))) & 0xffu;
             if (f != GAS && f != IFC) continue;
-            int id = D.bub[c];
-            int b = id < nb ? root[id] : 0;
+            const int id = D.bub[c];
+            const int b = id < nb ? L.root[id] : 0;
+            if (relabel && id != b) D.bub[c] = (uint16_t)b;
             if (b != bc) {
                 flush();
                 bc = b;
             }
-            double w = (f == GAS) ? 1.0 : 1.0 - phi[c];
-            const int x = c % G.nx, yz = c / G.nx, y = yz % G.ny, z = yz / G.ny;
+            const double w = (f == GAS) ? 1.0 : 1.0 - phi[c];
             a0 += w;
             a1 += w * x;
             a2 += w * y;
@@ -384,19 +451,23 @@ __global__ __launch_bounds__(256) void k_bubble_accum(Geom G, Dev D, const doubl
     flush();
     __syncthreads();
     for (int i = threadIdx.x; i < nb * BACC_STRIDE; i += blockDim.x)
-        if (acc[i] != 0.0) unsafeAtomicAdd(D.bacc + i, acc[i]);
+        if (L.acc[i] != 0.0) unsafeAtomicAdd(D.bacc + i, L.acc[i]);
 }
 
-// rho_g = M / V for every root bubble; per-id FP32 mirror for the boundary condition
-// with init set, the gas densities of the initial state are read from the
-// table's density slot and the constant gas masses M = rho_g V(0) are fixed
-// open: bubble 0 is a pressure outlet, held at the density in its table slot (the
-// initial rho_g0) with its mass following its volume
-__global__ void k_bubble_finalize(Dev D, int init, const int *gate, int open) {
-    if (blockIdx.x || (gate && *gate != 2)) return;
+// rho_g = M / V for every root bubble; per-id FP32 mirror for the boundary condition.
+// With init set, the gas densities of the initial state are read from the table's density
+// slot and the constant gas masses M = rho_g V(0) are fixed.  open: bubble 0 is a pressure
+// outlet, held at the density in its table slot (the initial rho_g0) with its mass
+// following its volume.  One block; the sums are cleared for the next pass.
+__device__ __forceinline__ void bubble_finalize(const Dev &D, int init, int open) {
     for (int b = threadIdx.x; b < D.nb; b += blockDim.x) {
         double *t = D.btab + b * B_STRIDE;
-        const double *a = D.bacc + b * BACC_STRIDE;
+        double a[BACC_STRIDE];
+#pragma unroll
+        for (int k = 0; k < BACC_STRIDE; ++k) {
+            a[k] = __hip_atomic_load(D.bacc + b * BACC_STRIDE + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            D.bacc[b * BACC_STRIDE + k] = 0.0;
+        }
         if (init) {
             t[B_M] = t[B_RHO] * a[0];
             t[B_V0] = a[0];
@@ -426,7 +497,6 @@ __global__ void k_bubble_finalize(Dev D, int init, const int *gate, int open) {
     for (int b = threadIdx.x; b < D.nb; b += blockDim.x)
         D.rhog[b] = (float)D.btab[bubble_root(D, b) * B_STRIDE + B_RHO];
 }
-
 
 // ---- surface tension: interface curvature (end of Sec. 2.2) ----------------------
 // The fill level as the curvature sees it: liquid and particle nodes 1 (perfect

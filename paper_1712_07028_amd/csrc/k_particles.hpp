@@ -804,6 +804,8 @@ __global__ void k_cov_apply(Geom G, Phys Ph, Dev D, double *phi) {
             if (f == LIQ) led = cell_rho<ST>(G, D, Ph, D.fB, c);
             else if (f == IFC) led = D.m[c];
             else if (f == GAS) D.cv[c] = CV_GRM;  // left the gas: for the splitting test
+            // the relabelling after a merge sees gas and interface cells only
+            if ((f == GAS || f == IFC) && D.counters[C_MERGED]) D.bub[c] = (uint16_t)bubble_root(D, D.bub[c]);
             D.flags[c] = SOL;
             D.pid[c] = P;
             phi[c] = 0.0;

@@ -46,39 +46,6 @@ __device__ __forceinline__ int blk_cell(const Geom &G, int x, int y, int z, int 
     return a + G.nx * (b + G.ny * d);
 }
 
-// Cell c left the gas phase: its block's gas and removed cells of its root, tested by
-// split_block_ok.
-__device__ bool split_local_ok(const Geom &G, const Dev &D, int c) {
-    int x, y, z;
-    cell_xyz(G, c, x, y, z);
-    const int r = bubble_root(D, D.bub[c]);
-    unsigned gas = 0u, rem = 0u;
-    for (int b = 0; b < 27; ++b) {
-        if (b == 13) continue;
-        const int n = blk_cell(G, x, y, z, b % 3 - 1, (b / 3) % 3 - 1, b / 9 - 1);
-        if (n < 0) continue;
-        if (D.flags[n] == GAS) {
-            if (bubble_root(D, D.bub[n]) == r) gas |= 1u << b;
-        } else if ((D.cv[n] & CV_GRM) && bubble_root(D, D.bub[n]) == r) {
-            rem |= 1u << b;
-        }
-    }
-    return split_block_ok(gas, rem);
-}
-
-// Cell c entered the gas phase: it joins the older gas of its root (gas before the
-// step and still gas) through a D3Q19 neighbour.
-__device__ bool split_added_ok(const Geom &G, const Dev &D, int c) {
-    int x, y, z;
-    cell_xyz(G, c, x, y, z);
-    const int r = bubble_root(D, D.bub[c]);
-    for (int q = 1; q < Q; ++q) {
-        const int n = nbr_idx(G, x, y, z, q, 1);
-        if (n >= 0 && D.flags[n] == GAS && !(D.cv[n] & CV_GAD) && bubble_root(D, D.bub[n]) == r) return true;
-    }
-    return false;
-}
-
 // the step's cells that left the gas (new interface cells from gas, covered gas
 // cells: CV_GRM) and that entered it (emptied cells, cells uncovered as gas: CV_GAD),
 // taken from the step's lists in that order
@@ -91,31 +58,59 @@ __device__ __forceinline__ int split_cell(const Dev &D, int i, int nG, int nC, i
     return D.lUnc[2 * (i - nE)];
 }
 
-// a failed test or a merge in this step asks for labelling
-__global__ void k_split_test(Geom G, Dev D) {
+// A failed test or a merge in this step asks for labelling.  A cell is worked by 32 lanes,
+// lane b taking cell b of its 3x3x3 block (one thread per cell paid the latency of 26
+// neighbours in turn: 40 us on the 384 x 256 surface).  Cell left the gas phase: its
+// block's gas and removed cells of its root, tested by split_block_ok.  Cell entered it: it
+// joins the older gas of its root (gas before the step and still gas) through a D3Q19
+// neighbour.  root: the block's table of bubble roots.
+__device__ __forceinline__ void split_test(const Geom &G, const Dev &D, const int *root, const Items &W) {
     const int nG = list_len(D, C_NNG), nC = event_len(D, C_NCOVER);
     const int nE = list_len(D, C_NE), nU = event_len(D, C_NUNCOVER);
     // a periodic axis shorter than the block folds it onto itself: always label
     const bool fold = (G.per[0] && G.nx < 3) || (G.per[1] && G.ny < 3) || (G.per[2] && G.nz < 3);
     if (blockIdx.x == 0 && threadIdx.x == 0 && D.counters[C_NMERGE] > 0) atomicOr(D.counters + C_SPLIT, 1);
-    GRID_STRIDE(i, nG + nC + nE + nU) {
-        const int c = split_cell(D, i, nG, nC, nE);
-        const uint8_t m = D.cv[c];
+    const int n = nG + nC + nE + nU;
+    auto root_of = [&](int c) {
+        const int id = D.bub[c];
+        return id < D.nb ? root[id] : 0;
+    };
+    ITEM_LOOP(W, i, n) {
+        const bool has = i < n;
+        const int c = has ? split_cell(D, i, nG, nC, nE) : 0;
+        const uint8_t m = has ? D.cv[c] : 0;
+        const int q = W.q;
+        int nb = -1;
+        if ((m & (CV_GRM | CV_GAD)) && q < 27 && q != 13) {
+            int x, y, z;
+            cell_xyz(G, c, x, y, z);
+            nb = blk_cell(G, x, y, z, q % 3 - 1, (q / 3) % 3 - 1, q / 9 - 1);
+        }
+        bool gas = false, old = false, rem = false;
+        if (nb >= 0) {
+            const uint8_t f = D.flags[nb], v = D.cv[nb];
+            if ((f == GAS || (v & CV_GRM)) && root_of(nb) == root_of(c)) {
+                gas = f == GAS;
+                old = gas && !(v & CV_GAD);
+                rem = !gas;
+            }
+        }
+        const unsigned mg = W.any(gas), mo = W.any(old), mr = W.any(rem);
         bool ok = true;
-        if (m & CV_GRM) ok = !fold && split_local_ok(G, D, c);
-        else if (m & CV_GAD) ok = split_added_ok(G, D, c);
-        if (!ok) atomicOr(D.counters + C_SPLIT, 1);
+        if (m & CV_GRM) ok = !fold && split_block_ok(mg, mr);
+        else if (m & CV_GAD) ok = (mo & blk_step(1u << 13)) != 0u;
+        if (has && !ok && q == 0) atomicOr(D.counters + C_SPLIT, 1);
     }
 }
 
-
-// labelling of the current state regardless of the test (initial state, new tables
-// or particles)
-__global__ void k_split_force(Dev D) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        D.counters[C_SPLIT] = 1;
-        D.counters[C_NCOMP] = 0;
-    }
+// The bubble pass of a step in one launch: volumes, the splitting test, and in the block
+// that finishes last the gas densities.  (Clearing, summing and finishing the table took
+// three launches, the test a fourth.)
+__global__ __launch_bounds__(256) void k_bubbles(Geom G, Dev D, const double *phi, int init, int test, int open) {
+    __shared__ BubbleLds L;
+    bubble_accum(G, D, phi, L, D.counters[C_MERGED] != 0);
+    if (test) split_test(G, D, L.root, Items(blockIdx.x, gridDim.x));
+    if (last_block(D.counters + C_DONEB, gridDim.x)) bubble_finalize(D, init, open);
 }
 
 // ---- labelling: union-find over the gas cells -------------------------------------
@@ -151,23 +146,26 @@ __device__ void lab_unite(int *lab, int a, int b) {
     }
 }
 
-#define CELL_STRIDE(c, n)                                                                      \
-    for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < (n);              \
-         c += (long long)gridDim.x * blockDim.x)
+// a range of cells for thread `thread` of `nthreads`
+#define CELL_RANGE(c, n) for (long long c = T.thread; c < (n); c += T.nthreads)
+struct Threads {
+    long long thread, nthreads;
+};
 
-// clears the marks the test read (cv is zero outside the conversion phase), then
-// starts the labelling: every gas cell its own part
-__global__ void k_ccl_init(Geom G, Dev D, SplitBuf B) {
+// clears the marks the test read (cv is zero outside the conversion phase)
+__device__ __forceinline__ void split_clear(const Dev &D, const Threads &T) {
     const int nG = list_len(D, C_NNG), nC = event_len(D, C_NCOVER);
     const int nE = list_len(D, C_NE), nU = event_len(D, C_NUNCOVER);
-    GRID_STRIDE(i, nG + nC + nE + nU) D.cv[split_cell(D, i, nG, nC, nE)] = 0;
-    if (D.counters[C_SPLIT] == 0) return;
-    CELL_STRIDE(c, G.N) if (D.flags[c] == GAS) B.lab[c] = (int)c;
+    CELL_RANGE(i, nG + nC + nE + nU) D.cv[split_cell(D, (int)i, nG, nC, nE)] = 0;
 }
 
-__global__ void k_ccl_union(Geom G, Dev D, SplitBuf B) {
-    if (D.counters[C_SPLIT] == 0) return;
-    CELL_STRIDE(c, G.N) {
+// starts the labelling: every gas cell its own part
+__device__ __forceinline__ void ccl_init(const Geom &G, const Dev &D, const SplitBuf &B, const Threads &T) {
+    CELL_RANGE(c, G.N) if (D.flags[c] == GAS) B.lab[c] = (int)c;
+}
+
+__device__ __forceinline__ void ccl_union(const Geom &G, const Dev &D, const SplitBuf &B, const Threads &T) {
+    CELL_RANGE(c, G.N) {
         if (D.flags[c] != GAS) continue;
         int x, y, z;
         cell_xyz(G, (int)c, x, y, z);
@@ -183,9 +181,8 @@ __global__ void k_ccl_union(Geom G, Dev D, SplitBuf B) {
 
 // every gas cell links straight to its part's lowest cell (a concurrent find only
 // ever sees a link to an ancestor); the parts' lowest cells are listed
-__global__ void k_ccl_flatten(Geom G, Dev D, SplitBuf B) {
-    if (D.counters[C_SPLIT] == 0) return;
-    CELL_STRIDE(c, G.N) {
+__device__ __forceinline__ void ccl_flatten(const Geom &G, const Dev &D, const SplitBuf &B, const Threads &T) {
+    CELL_RANGE(c, G.N) {
         if (D.flags[c] != GAS) continue;
         const int root = lab_find(B.lab, (int)c);
         if (root != (int)c) {
@@ -198,43 +195,45 @@ __global__ void k_ccl_flatten(Geom G, Dev D, SplitBuf B) {
     }
 }
 
+struct PlanLds {
+    int sorted[SPLIT_MAXC];
+    unsigned char seen[64], taken[64];
+};
+
 // parts in order of their lowest cell index: the first part of each root keeps it,
-// the others take the lowest ids that are not alive
-__global__ __launch_bounds__(1024) void k_split_plan(Dev D, SplitBuf B, int open) {
-    if (D.counters[C_SPLIT] == 0) return;
-    __shared__ int sorted[SPLIT_MAXC];
-    __shared__ unsigned char seen[64], taken[64];
-    if (D.counters[C_NCOMP] > SPLIT_MAXC) {  // not every part listed: no split, error set
+// the others take the lowest ids that are not alive.  One block.
+__device__ __forceinline__ void split_plan(const Dev &D, const SplitBuf &B, PlanLds &P, int open) {
+    const int n = __hip_atomic_load(D.counters + C_NCOMP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n > SPLIT_MAXC) {  // not every part listed: no split, error set
         if (threadIdx.x == 0) D.counters[C_SPLIT] = 1;
         return;
     }
-    const int n = D.counters[C_NCOMP];
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
         const int v = B.comp[k];
         int rank = 0;
         for (int j = 0; j < n; ++j) rank += B.comp[j] < v;
-        sorted[rank] = v;
+        P.sorted[rank] = v;
     }
-    for (int i = threadIdx.x; i < 64; i += blockDim.x) seen[i] = taken[i] = 0;
+    for (int i = threadIdx.x; i < 64; i += blockDim.x) P.seen[i] = P.taken[i] = 0;
     __syncthreads();
     if (threadIdx.x) return;
-    int used = D.counters[C_BUSED], any = 0;
+    int used = *D.bused, any = 0;
     for (int k = 0; k < n; ++k) {
-        const int c = sorted[k];
+        const int c = P.sorted[k];
         const int r = bubble_root(D, D.bub[c]);
         int id = -1;
         if (r == 0 && open) {
             // every part of an open atmosphere stays at the outlet
-        } else if (!seen[r]) {
-            seen[r] = 1;
+        } else if (!P.seen[r]) {
+            P.seen[r] = 1;
         } else {
             // the lowest id that is not alive: never used, or merged away (merges
             // relabel the cells to their roots)
             int b = 1;
-            while (b < D.maxB && (D.balive[b] || taken[b])) ++b;
+            while (b < D.maxB && (D.balive[b] || P.taken[b])) ++b;
             if (b < D.maxB) {
                 id = b;
-                taken[b] = 1;
+                P.taken[b] = 1;
                 used = max(used, b + 1);
                 any = 1;
             } else {
@@ -246,7 +245,7 @@ __global__ __launch_bounds__(1024) void k_split_plan(Dev D, SplitBuf B, int open
         B.vol[k] = 0.0;
         B.lab[c] = -(k + 2);
     }
-    D.counters[C_BUSED] = used;
+    *D.bused = used;
     D.counters[C_SPLIT] = any ? 2 : 1;
 }
 
@@ -256,10 +255,10 @@ __device__ __forceinline__ int lab_slot(const int *lab, int c) {
 }
 
 // interface cells first: they find their part through the ids of their gas
-// neighbours, which the next kernel changes
-__global__ void k_split_ifc(Geom G, Dev D, SplitBuf B, const double *phi) {
-    if (D.counters[C_SPLIT] != 2) return;
-    CELL_STRIDE(c, G.N) {
+// neighbours, which the next phase changes
+__device__ __forceinline__ void split_ifc(const Geom &G, const Dev &D, const SplitBuf &B, const double *phi,
+                                          const Threads &T) {
+    CELL_RANGE(c, G.N) {
         if (D.flags[c] != IFC) continue;
         int x, y, z;
         cell_xyz(G, (int)c, x, y, z);
@@ -282,13 +281,11 @@ __global__ void k_split_ifc(Geom G, Dev D, SplitBuf B, const double *phi) {
 }
 
 // gas cells: 16 consecutive cells per thread, their count summed per part
-__global__ void k_split_gas(Geom G, Dev D, SplitBuf B) {
-    if (D.counters[C_SPLIT] != 2) return;
+__device__ __forceinline__ void split_gas(const Geom &G, const Dev &D, const SplitBuf &B, const Threads &T) {
     const long long nchunk = (G.N + 15) / 16;
     int ks = -1;
     double acc = 0.0;
-    for (long long ch = blockIdx.x * (long long)blockDim.x + threadIdx.x; ch < nchunk;
-         ch += (long long)gridDim.x * blockDim.x) {
+    CELL_RANGE(ch, nchunk) {
         for (long long c = ch * 16; c < ch * 16 + 16 && c < G.N; ++c) {
             if (D.flags[c] != GAS) continue;
             const int k = lab_slot(B.lab, (int)c);
@@ -306,32 +303,101 @@ __global__ void k_split_gas(Geom G, Dev D, SplitBuf B) {
     if (ks >= 0) unsafeAtomicAdd(B.vol + ks, acc);
 }
 
+struct MassLds {
+    double Mr[64], taken[64];
+};
+
 // gas masses of the new bubbles: M_part = M_root V_part / V_root, the root keeps
-// the rest (the root volumes are those of the state before the split); the block
-// also clears the volume sums for the recount that follows
-__global__ void k_split_mass(Dev D, SplitBuf B) {
-    if (D.counters[C_SPLIT] != 2 || blockIdx.x) return;
-    for (int i = threadIdx.x; i < D.nb * BACC_STRIDE; i += blockDim.x) D.bacc[i] = 0.0;
-    if (threadIdx.x) return;
-    __shared__ double Mr[64], taken[64];
+// the rest (the root volumes are those of the state before the split).  One thread.
+__device__ __forceinline__ void split_mass(const Dev &D, const SplitBuf &B, MassLds &S) {
     for (int r = 0; r < D.maxB; ++r) {
-        Mr[r] = D.btab[r * B_STRIDE + B_M];
-        taken[r] = 0.0;
+        S.Mr[r] = D.btab[r * B_STRIDE + B_M];
+        S.taken[r] = 0.0;
     }
-    const int n = min(D.counters[C_NCOMP], SPLIT_MAXC);
+    const int n = min(__hip_atomic_load(D.counters + C_NCOMP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), SPLIT_MAXC);
     for (int k = 0; k < n; ++k) {
         const int id = B.cid[k];
         if (id < 0) continue;
         const int r = B.parent[k];
         double *t = D.btab + id * B_STRIDE;
-        t[B_M] = Mr[r] * B.vol[k] / D.btab[r * B_STRIDE + B_V];
-        t[B_V0] = B.vol[k];
+        const double v = __hip_atomic_load(B.vol + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        t[B_M] = S.Mr[r] * v / D.btab[r * B_STRIDE + B_V];
+        t[B_V0] = v;
         D.broot[id] = id;
         D.balive[id] = 1;
-        taken[r] += t[B_M];
+        S.taken[r] += t[B_M];
     }
     for (int r = 0; r < D.maxB; ++r)
-        if (taken[r] != 0.0) D.btab[r * B_STRIDE + B_M] = Mr[r] - taken[r];
+        if (S.taken[r] != 0.0) D.btab[r * B_STRIDE + B_M] = S.Mr[r] - S.taken[r];
+}
+
+// The labelling and the split in one launch (small boxes, where six more launches cost more
+// than the step has to spare): the blocks return after clearing the marks when there is
+// nothing to do.  force: label regardless of the test (initial state, new tables or
+// particles).
+__global__ __launch_bounds__(256) void k_split(Geom G, Dev D, SplitBuf B, const double *phi, int force, int open) {
+    __shared__ union {
+        PlanLds P;
+        MassLds S;
+        BubbleLds V;
+    } L;
+    const Threads T{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x};
+    const bool run = force || D.counters[C_SPLIT] != 0;
+    split_clear(D, T);
+    if (!run) return;
+    GridBarrier GB{D.counters + C_BARS, (int)gridDim.x, 0, D.err};
+    ccl_init(G, D, B, T);
+    GB.wait();
+    ccl_union(G, D, B, T);
+    GB.wait();
+    ccl_flatten(G, D, B, T);
+    GB.wait();
+    if (blockIdx.x == 0) split_plan(D, B, L.P, open);
+    GB.wait();
+    if (__hip_atomic_load(D.counters + C_SPLIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2) return;
+    split_ifc(G, D, B, phi, T);
+    GB.wait();
+    split_gas(G, D, B, T);
+    GB.wait();
+    if (blockIdx.x == 0 && threadIdx.x == 0) split_mass(D, B, L.S);
+    GB.wait();
+    bubble_accum(G, D, phi, L.V, false);
+    if (last_block(D.counters + C_DONES, gridDim.x)) bubble_finalize(D, 0, open);
+}
+
+// The same as a launch per phase, for boxes where the labelling wants the whole device (a
+// phase of a few values goes to the block that finishes the one before it); each returns
+// at once when there is nothing to do.
+__global__ void k_split_start(Geom G, Dev D, SplitBuf B, int force) {
+    const Threads T{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x};
+    split_clear(D, T);
+    if (force || D.counters[C_SPLIT] != 0) ccl_init(G, D, B, T);
+}
+__global__ void k_ccl_union(Geom G, Dev D, SplitBuf B, int force) {
+    if (!force && D.counters[C_SPLIT] == 0) return;
+    ccl_union(G, D, B, Threads{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x});
+}
+__global__ __launch_bounds__(256) void k_ccl_flatten(Geom G, Dev D, SplitBuf B, int force, int open) {
+    __shared__ PlanLds P;
+    if (!force && D.counters[C_SPLIT] == 0) return;
+    ccl_flatten(G, D, B, Threads{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x});
+    if (last_block(D.counters + C_DONES, gridDim.x)) split_plan(D, B, P, open);
+}
+__global__ void k_split_ifc(Geom G, Dev D, SplitBuf B, const double *phi) {
+    if (D.counters[C_SPLIT] != 2) return;
+    split_ifc(G, D, B, phi, Threads{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x});
+}
+__global__ __launch_bounds__(256) void k_split_gas(Geom G, Dev D, SplitBuf B) {
+    __shared__ MassLds S;
+    if (D.counters[C_SPLIT] != 2) return;
+    split_gas(G, D, B, Threads{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x});
+    if (last_block(D.counters + C_DONES, gridDim.x) && threadIdx.x == 0) split_mass(D, B, S);
+}
+__global__ __launch_bounds__(256) void k_split_volumes(Geom G, Dev D, const double *phi, int open) {
+    __shared__ BubbleLds L;
+    if (D.counters[C_SPLIT] != 2) return;
+    bubble_accum(G, D, phi, L, false);
+    if (last_block(D.counters + C_DONES, gridDim.x)) bubble_finalize(D, 0, open);
 }
 
 }  // namespace fsl

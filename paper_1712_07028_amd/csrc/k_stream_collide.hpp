@@ -525,6 +525,7 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
         if (!collide_store<ST>(Ph, fi, M, B, S, (unsigned)c)) atomicOr(D.err, ERR_NAN);
     }
 
+    if (isF || isE) D.cv[c] = isF ? CV_F : CV_E0;  // marked for the conversion phases
     wave_append(isF, c, D.lF, D.counters + C_NF, D.cap, D.err);
     wave_append(isE, c, D.lE0, D.counters + C_NE0, D.cap, D.err);
     if (D.np > 0) acc_reduce_wave(G, D, acc, x, y, z);
@@ -1037,6 +1038,10 @@ template <int ST, bool MW, bool PER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))) void k_stream_collide(
     Geom G, Phys Ph, Dev D, int tilesX, int tilesY, int nChunks, int nzc, int *gen, int *ngen) {
     __shared__ MarchLds L;
+    if (blockIdx.x == 0 && D.counters_nxt) {  // nothing reads these before the next step
+        if (threadIdx.x < C_COUNT) D.counters_nxt[threadIdx.x] = 0;
+        if (threadIdx.x < 18 && D.wallF_nxt) D.wallF_nxt[threadIdx.x] = 0.0;
+    }
     int col, chunk;
     march_of_block(blockIdx.x, tilesX * tilesY, nChunks, col, chunk);
     const int x0 = (col % tilesX) * TX, y0 = (col / tilesX) * TY;

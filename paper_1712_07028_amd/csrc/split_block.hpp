@@ -9,19 +9,24 @@
 namespace fsl {
 
 // block cells as a 27-bit set, bit (dx + 1) + 3 (dy + 1) + 9 (dz + 1); the centre is 13
-// cells of the block one D3Q19 step away from a cell of m
+constexpr unsigned blk_layer(int axis, int v) {  // the cells with coordinate v (0..2) along an axis
+    unsigned m = 0u;
+    for (int b = 0; b < 27; ++b)
+        if ((axis == 0 ? b % 3 : axis == 1 ? (b / 3) % 3 : b / 9) == v) m |= 1u << b;
+    return m;
+}
+// cells of the block one step along an axis away from a cell of m
+template <int A>
+__host__ __device__ __forceinline__ unsigned blk_axis(unsigned m) {
+    constexpr int sh = A == 0 ? 1 : A == 1 ? 3 : 9;
+    constexpr unsigned lo = blk_layer(A, 0), hi = blk_layer(A, 2);
+    return ((m & ~hi) << sh) | ((m & ~lo) >> sh);
+}
+// cells of the block one D3Q19 step away from a cell of m: one step along an axis, or one
+// along each of two
 __host__ __device__ __forceinline__ unsigned blk_step(unsigned m) {
-    unsigned out = 0u;
-    for (int b = 0; b < 27; ++b) {
-        if (!((m >> b) & 1u)) continue;
-        const int a0 = b % 3, a1 = (b / 3) % 3, a2 = b / 9;
-        for (int q = 1; q < Q; ++q) {
-            const int e0 = a0 + cx(q), e1 = a1 + cy(q), e2 = a2 + cz(q);
-            if (e0 < 0 || e0 > 2 || e1 < 0 || e1 > 2 || e2 < 0 || e2 > 2) continue;
-            out |= 1u << (e0 + 3 * e1 + 9 * e2);
-        }
-    }
-    return out;
+    const unsigned x = blk_axis<0>(m), y = blk_axis<1>(m), z = blk_axis<2>(m);
+    return x | y | z | blk_axis<1>(x) | blk_axis<2>(x) | blk_axis<2>(y);
 }
 
 // The centre cell left the gas; gas: the block's cells that are still gas of its
