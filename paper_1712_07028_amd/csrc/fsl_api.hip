@@ -190,6 +190,10 @@ struct fsl_ctx {
     int profiling;
     int have_prev;  // a previous step's hydrodynamic force exists (particle update)
     int stamp;      // stamp of the next stream-collide launch (>= 1)
+    // gas or interface cells may exist: conversions, bubble pass, splitting and curvature
+    // run.  They come from gas alone, so a box without any stays without (2: none in the
+    // cell types just set; one more step with them brings the bubble table up to date)
+    int gas;
     int counters_clear;  // the counters of the next step are zero
     int rhow_ok;    // the density words of stamp - 1 hold the densities of the populations in A
     // two steps captured as a HIP graph from a steady state (stored densities valid, the
@@ -310,6 +314,7 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
     const int nChunks = (c->G.nz + nzc - 1) / nzc;
     hipLaunchKernelGGL((k_stream_collide<ST, MW, PER>), dim3(c->tilesX * c->tilesY * nChunks), dim3(256), 0, c->st,
                        c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen);
+    if (!c->gas && !MW) return;  // the list is empty
     hipLaunchKernelGGL((k_general<ST, MW>), dim3(std::min(c->nTiles, 4096)), dim3(256), 0, c->st, c->G, c->Ph, Dv,
                        c->tilesX, c->tilesY, (const int *)glist, (const int *)ngen);
 }
@@ -327,7 +332,7 @@ void launch_stream_collide(fsl_ctx *c, const Dev &Dv) {
     }
 }
 
-template <int ST> int enqueue_steps(fsl_ctx *c, int n, int split = 1);
+template <int ST> int enqueue_steps(fsl_ctx *c, int n);
 template <int ST> int enqueue_integration(fsl_ctx *c);
 template <int ST> int enqueue_pair_forces(fsl_ctx *c);
 template <int ST> int enqueue_coverage_step(fsl_ctx *c);
@@ -379,7 +384,7 @@ int enqueue_conversions(fsl_ctx *c) {
     Dev &D = c->D;
     dim3 g(LIST_BLOCKS), b(256);
     if (fused_phases(c)) {
-        hipLaunchKernelGGL(k_conversions<ST>, dim3(SYNC_BLOCKS), b, 0, c->st, c->G, c->Ph, D);
+        hipLaunchKernelGGL(k_conversions<ST>, dim3(SYNC_BIG), dim3(1024), 0, c->st, c->G, c->Ph, D);
     } else {
         hipLaunchKernelGGL(k_conv_closure<ST>, g, b, 0, c->st, c->G, c->Ph, D);
         hipLaunchKernelGGL(k_conv_change<ST>, g, b, 0, c->st, c->G, c->Ph, D);
@@ -389,14 +394,35 @@ int enqueue_conversions(fsl_ctx *c) {
     return FSL_OK;
 }
 
-// cover / uncover events with the lattice lat and fill levels phi as "current"
+// blocks of the uncover pass: 32 lanes per node, and a sphere leaves about half a node per
+// step (pi R^2 times its velocity)
+int uncover_blocks(const fsl_ctx *c, int block) { return std::min(256, std::max(2, c->D.np / 2 * 32 / block)); }
+
+// threads per sphere (a power of two's exponent) for the passes over spheres' nodes: as
+// many as leave the launch within what the device holds at once (half a million threads)
+int team_shift(int np) { return np <= 512 ? 10 : np <= 2048 ? 8 : np <= 4096 ? 7 : 6; }
+dim3 team_grid(int np, int sh) { return dim3(std::max(1, sh > 8 ? np : (np + (256 >> sh) - 1) / (256 >> sh))); }
+dim3 team_block(int sh) { return dim3(std::max(256, 1 << sh)); }
+
+// the spheres' nodes after a step: claims of spheres that may overlap, covered and
+// uncovered nodes, claims taken back
 template <int ST>
-int enqueue_cover_events(fsl_ctx *c, const Dev &Dv, double *phi) {
-    dim3 g(LIST_BLOCKS), b(256);
-    hipLaunchKernelGGL(k_cov_apply<ST>, g, b, 0, c->st, c->G, c->Ph, Dv, phi);
-    hipLaunchKernelGGL(k_unc_decide<ST>, g, b, 0, c->st, c->G, c->Ph, Dv);
-    hipLaunchKernelGGL(k_unc_apply<ST>, g, b, 0, c->st, c->G, c->Ph, Dv, phi);
-    hipLaunchKernelGGL(k_unc_closure, g, b, 0, c->st, c->G, Dv, phi);
+int enqueue_coverage_step(fsl_ctx *c) {
+    Dev &D = c->D;
+    const int np = D.np;
+    ProfScope ps(c, 5);
+    if (np > INT_BLOCK_MAX) {
+        hipLaunchKernelGGL(k_cov_flag_init, dim3(grid_for(np)), dim3(256), 0, c->st, c->G, D);
+        hipLaunchKernelGGL(k_cov_flag_pairs, dim3(grid_for(c->L.pcap, 256, 1024)), dim3(256), 0, c->st, c->G, D,
+                           c->L.pcap);
+        hipLaunchKernelGGL(k_part_mirror, dim3(grid_for(np)), dim3(256), 0, c->st, D);
+    }
+    const int sh = team_shift(np);
+    const dim3 g = team_grid(np, sh), b = team_block(sh);
+    hipLaunchKernelGGL(k_cov_claim, g, b, 0, c->st, c->G, D, 0, sh);
+    hipLaunchKernelGGL(k_cov_scan<ST>, g, b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, sh);
+    const int ub = uncover_blocks(c, b.x);
+    hipLaunchKernelGGL(k_unc<ST>, dim3(ub + g.x), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, ub, sh);
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -416,22 +442,30 @@ int enqueue_pair_forces(fsl_ctx *c) {
     const int np = D.np;
     ProfScope ps(c, 3);
     // candidate pairs (positions at t): particle-particle links and lubrication
-    hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(c->ncell)), dim3(256), 0, c->st, D, c->ncell);
-    hipLaunchKernelGGL(k_grid_count, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
-    {
+    if (np <= PAIRS_DIRECT) {
+        hipLaunchKernelGGL(k_pairs_direct, dim3((np + PDIR_P - 1) / PDIR_P, (np + 255) / 256), dim3(256), 0, c->st, D,
+                           c->PG, c->L.pcap);
+    } else {
+        hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(c->ncell)), dim3(256), 0, c->st, D, c->ncell);
+        hipLaunchKernelGGL(k_grid_count, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
         const int chunk = std::max(256, (c->ncell + 1023) / 1024 + 255) / 256 * 256;
         const int nb = (c->ncell + chunk - 1) / chunk;
         int *bsum = (int *)(c->xs + c->L.gBsum);
         hipLaunchKernelGGL(k_gscan_sum, dim3(nb), dim3(256), 0, c->st, D, c->ncell, chunk, bsum);
         hipLaunchKernelGGL(k_gscan_top, dim3(1), dim3(1024), 0, c->st, D, c->ncell, nb, bsum);
         hipLaunchKernelGGL(k_gscan_apply, dim3(nb), dim3(256), 0, c->st, D, c->ncell, chunk, (const int *)bsum);
+        hipLaunchKernelGGL(k_grid_fill, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
+        hipLaunchKernelGGL(k_pairs, dim3(grid_for((long long)np * 27, 256, 2048)), dim3(256), 0, c->st, D, c->PG, c->L.pcap);
     }
-    hipLaunchKernelGGL(k_grid_fill, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
-    hipLaunchKernelGGL(k_pairs, dim3(grid_for((long long)np * 27, 256, 2048)), dim3(256), 0, c->st, D, c->PG, c->L.pcap);
-    hipLaunchKernelGGL(k_solid_pairs, dim3(grid_for(c->L.pcap, 4, 8192)), dim3(256), 0, c->st, c->G, D, c->L.pcap);
-    if (!c->G.per[0] || !c->G.per[1] || !c->G.per[2])
-        hipLaunchKernelGGL(k_face_links, dim3((np + 3) / 4), dim3(256), 0, c->st, c->G, c->Ph, D);
-    hipLaunchKernelGGL(k_part_forces, dim3((np + 255) / 256), dim3(256), 0, c->st, D, c->cfg.integrate);
+    const bool faces = !c->G.per[0] || !c->G.per[1] || !c->G.per[2];
+    const int chunk = np <= INT_BLOCK_MAX ? 1 : 8;
+    // two waves per group of listed pairs (a few per sphere as a rule), a wave per group of
+    // spheres
+    const int pb = grid_for(4LL * np, 2 * chunk, 8192);
+    hipLaunchKernelGGL(k_solid_links, dim3(pb + (faces ? (np + 4 * chunk - 1) / (4 * chunk) : 0)), dim3(256), 0, c->st,
+                       c->G, c->Ph, D, c->L.pcap, pb, chunk);
+    hipLaunchKernelGGL(k_part_forces, dim3(std::min(2048, np <= 2048 ? (np + 3) / 4 : (np + 15) / 16)), dim3(256), 0,
+                       c->st, D, c->cfg.integrate && np > INT_BLOCK_MAX);
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -446,9 +480,13 @@ int enqueue_integration(fsl_ctx *c) {
     int wmask = 0;  // axes whose faces are no-slip walls
     for (int a = 0; a < 3; ++a)
         if (c->cfg.boundary[a] == FSL_NOSLIP) wmask |= 1 << a;
-    if (np <= INT_BLOCK_MAX) {  // small tables: every substep in one block
-        hipLaunchKernelGGL(k_integrate_block, dim3(1), dim3(1024), 0, c->st, c->G, D, ns, mu, c->cfg.contact_k,
-                           c->L.pcap, c->cfg.g[0], c->cfg.g[1], c->cfg.g[2], c->have_prev, wmask);
+    if (np <= INT_BLOCK_MAX) {
+        if (np <= 1024)
+            hipLaunchKernelGGL(k_integrate_block<1>, dim3(1), dim3(1024), 0, c->st, c->G, D, ns, mu, c->cfg.contact_k,
+                               c->L.pcap, c->cfg.g[0], c->cfg.g[1], c->cfg.g[2], c->have_prev, wmask);
+        else
+            hipLaunchKernelGGL(k_integrate_block<2>, dim3(1), dim3(1024), 0, c->st, c->G, D, ns, mu, c->cfg.contact_k,
+                               c->L.pcap, c->cfg.g[0], c->cfg.g[1], c->cfg.g[2], c->have_prev, wmask);
     } else {
         for (int s = 0; s < ns; ++s) {
             hipLaunchKernelGGL(k_lub, dim3(grid_for(c->L.pcap, 256, 1024)), dim3(256), 0, c->st, c->G, D, mu,
@@ -462,51 +500,30 @@ int enqueue_integration(fsl_ctx *c) {
     return FSL_OK;
 }
 
-template <int ST>
-int enqueue_coverage_step(fsl_ctx *c) {
-    Dev &D = c->D;
-    const int np = D.np;
-    ProfScope ps(c, 5);
-    dim3 pw((np + 3) / 4);
-    hipLaunchKernelGGL(k_cov_flag_init, dim3(grid_for(np)), dim3(256), 0, c->st, c->G, D);
-    hipLaunchKernelGGL(k_cov_flag_pairs, dim3(grid_for(c->L.pcap, 256, 1024)), dim3(256), 0, c->st, c->G, D,
-                       c->L.pcap);
-    hipLaunchKernelGGL(k_cov_claim, pw, dim3(256), 0, c->st, c->G, D, 0);
-    hipLaunchKernelGGL(k_cov_scan, pw, dim3(256), 0, c->st, c->G, D);
-    int rc = enqueue_cover_events<ST>(c, D, D.phi_nxt);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_cov_reset, pw, dim3(256), 0, c->st, c->G, D);
-    hipLaunchKernelGGL(k_part_mirror, dim3(grid_for(np)), dim3(256), 0, c->st, D);
-    LAUNCHCHK(c);
-    return FSL_OK;
-}
-
-// curvature at the interface cells of the current state (phi_cur, flags)
-void enqueue_curvature(fsl_ctx *c) {
+// curvature at the interface cells of the current state (phi_cur, flags); tc: the word that
+// counts the listed tiles, zero on entry
+void enqueue_curvature(fsl_ctx *c, int *tc) {
     const Layout &L = c->L;
     char *w = c->ws;
     unsigned *tf = (unsigned *)(w + L.ktf);
-    int *tl = (int *)(w + L.klist), *tc = (int *)(w + L.kcount);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->st, tc, 1LL, 0);
+    int *tl = (int *)(w + L.klist);
     hipLaunchKernelGGL(k_curv_mark, dim3(grid_for((c->G.N + 15) / 16, 256, 8192)), dim3(256), 0, c->st, c->G,
                        c->D, tf, tl, tc, L.ktx, L.kty);
     hipLaunchKernelGGL(k_curv_tiles, dim3(std::min(L.nKT, 1024)), dim3(256), 0, c->st, c->G, c->D,
                        (const double *)c->D.phi_cur, tf, (const int *)tl, (const int *)tc, L.ktx, L.kty);
 }
 
-// split = 0 leaves out the bubble-splitting test (a state without gas cells: the
-// differentiation window)
 template <int ST>
-int enqueue_steps(fsl_ctx *c, int n, int split) {
+int enqueue_steps(fsl_ctx *c, int n) {
     for (int s = 0; s < n; ++s) {
         Dev &D = c->D;
         if (!c->counters_clear) hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, D);
         if (c->FS.n > 0 && D.wallF)  // face forces from the state at t
-            hipLaunchKernelGGL(k_wall_forces<ST>, dim3(grid_for(c->FS.start[c->FS.n], 256, 1024)), dim3(256), 0, c->st,
-                               c->G, c->Ph, D, c->FS);
-        if (D.kappa) {  // curvature of the interface at t for the Laplace jump
+            hipLaunchKernelGGL(k_wall_forces<ST>, dim3(grid_for(c->FS.start[c->FS.n] / c->FS.n, 256, 512), c->FS.n),
+                               dim3(256), 0, c->st, c->G, c->Ph, D, c->FS);
+        if (D.kappa && c->gas) {  // curvature of the interface at t for the Laplace jump
             ProfScope ps(c, 6);
-            enqueue_curvature(c);
+            enqueue_curvature(c, D.counters + C_NKT);
         }
         if (!c->rhow_ok && D.rhow) {  // densities of the current populations for rho_w
             hipLaunchKernelGGL(k_rhow_fill<ST>, dim3(grid_for(c->G.N, 256, 8192)), dim3(256), 0, c->st, c->G,
@@ -529,18 +546,19 @@ int enqueue_steps(fsl_ctx *c, int n, int split) {
         } else {
             c->rhow_ok = 1;
         }
-        int rc = enqueue_conversions<ST>(c);
+        int rc = c->gas ? enqueue_conversions<ST>(c) : FSL_OK;
         if (rc) return rc;
         if (D.np > 0) {
             rc = enqueue_particles<ST>(c);
             if (rc) return rc;
         }
-        rc = enqueue_bubbles<ST>(c, D.phi_nxt, 0, split);
-        if (rc) return rc;
-        if (split) {
+        if (c->gas) {
+            rc = enqueue_bubbles<ST>(c, D.phi_nxt, 0, 1);
+            if (rc) return rc;
             rc = enqueue_split<ST>(c, D.phi_nxt, 0);
             if (rc) return rc;
         }
+        if (c->gas == 2) c->gas = 0;
         std::swap(D.fA, D.fB);
         std::swap(D.phi_cur, D.phi_nxt);
         std::swap(D.counters, D.counters_nxt);  // cleared by this step's first kernel
@@ -559,14 +577,15 @@ int enqueue_coverage_full(fsl_ctx *c) {
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, Dv);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
-    if (Dv.np > 0) hipLaunchKernelGGL(k_cov_claim, dim3((Dv.np + 3) / 4), dim3(256), 0, c->st, c->G, Dv, 1);
+    const int sh = team_shift(Dv.np);
+    if (Dv.np > 0) hipLaunchKernelGGL(k_cov_claim, team_grid(Dv.np, sh), team_block(sh), 0, c->st, c->G, Dv, 1, sh);
     hipLaunchKernelGGL(k_cov_scan_dense, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, c->G, Dv);
-    int rc = enqueue_cover_events<ST>(c, Dv, Dv.phi_cur);
-    if (rc) return rc;
+    hipLaunchKernelGGL(k_cov_apply<ST>, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, c->Ph, Dv, Dv.phi_cur);
+    hipLaunchKernelGGL(k_unc<ST>, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, c->Ph, Dv, Dv.phi_cur, LIST_BLOCKS, 6);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
     LAUNCHCHK(c);
-    rc = enqueue_bubbles<ST>(c, Dv.phi_cur, 0, 0);
+    int rc = enqueue_bubbles<ST>(c, Dv.phi_cur, 0, 0);
     if (rc) return rc;
     return enqueue_split<ST>(c, Dv.phi_cur, 1);
 }
@@ -642,7 +661,7 @@ int window_forward(fsl_ctx *c, int T, int k, double *J) {
     const size_t st = (size_t)Q * c->G.S * 4, stride = adj_up(st) / 4;
     HIPCHK(c, hipMemcpyAsync(A.cp, D.fA, st, hipMemcpyDeviceToDevice, c->st));
     for (int t = 0; t < T; ++t) {
-        int rc = enqueue_steps<ST_F32>(c, 1, 0);  // no gas in the window
+        int rc = enqueue_steps<ST_F32>(c, 1);
         if (rc) return rc;
         if (D.np > 0) hipLaunchKernelGGL(k_win_J, dim3(1), dim3(256), 0, c->st, D, A.acc);
         if ((t + 1) % k == 0 && t + 1 < T)
@@ -807,6 +826,7 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
     D.pairs = (int2 *)(x + L.pairs);
     D.counters = (int *)(w + L.counters);
     D.counters_nxt = D.counters + C_SET;
+    c->gas = !(cfg->zs < 0.0) || cfg->n_gas_spheres > 0;
     D.bused = D.counters + C_BUSED;
     c->counters_clear = 0;
     D.err = (unsigned *)(w + L.ctl);
@@ -1027,7 +1047,7 @@ int fsl_step(fsl_ctx *c, int n) {
     return by_storage(c, [&](auto st) -> int {
         constexpr int ST = decltype(st)::value;
         while (n > 0) {
-            const bool steady = n >= 8 && c->gstate == 0 && c->st != nullptr && !c->profiling && c->rhow_ok &&
+            const bool steady = n >= 8 && c->gstate == 0 && c->st != nullptr && !c->profiling && c->rhow_ok && c->gas != 2 &&
                                 (c->D.np == 0 || !c->cfg.integrate || c->have_prev) && c->stamp < (1 << 29);
             if (steady && !c->gexec) {
                 const int rc = capture_pair<ST>(c);
@@ -1218,7 +1238,9 @@ int fsl_fields_get(fsl_ctx *c, int field, void *host) {
         if (!D.kappa) return fail(c, FSL_E_ARG, "fields_get: no surface tension configured");
         double *stage = (double *)(c->xs + c->L.stage);
         const long long chunk = (long long)(c->L.stageBytes / 8);
-        enqueue_curvature(c);  // of the current state: the one the next step uses
+        int *tc = (int *)(c->ws + c->L.kcount);
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, c->st, tc, 1LL, 0);
+        enqueue_curvature(c, tc);  // of the current state: the one the next step uses
         LAUNCHCHK(c);
         std::vector<uint8_t> fl(N);
         HIPCHK(c, hipMemcpyAsync(fl.data(), D.flags, N, hipMemcpyDeviceToHost, c->st));
@@ -1272,7 +1294,12 @@ int fsl_fields_set(fsl_ctx *c, int field, const void *host) {
     double *stage = (double *)(c->xs + c->L.stage);
     const long long chunk = (long long)(c->L.stageBytes / 8);
     switch (field) {
-    case FSL_FIELD_FLAGS: HIPCHK(c, hipMemcpyAsync(D.flags, host, N, hipMemcpyHostToDevice, c->st)); break;
+    case FSL_FIELD_FLAGS: {
+        const uint8_t *f = (const uint8_t *)host;
+        c->gas = std::any_of(f, f + N, [](uint8_t v) { return v == GAS || v == IFC; }) ? 1 : 2;
+        HIPCHK(c, hipMemcpyAsync(D.flags, host, N, hipMemcpyHostToDevice, c->st));
+        break;
+    }
     case FSL_FIELD_MASS: HIPCHK(c, hipMemcpyAsync(D.m, host, N * 8, hipMemcpyHostToDevice, c->st)); break;
     case FSL_FIELD_PHI: HIPCHK(c, hipMemcpyAsync(D.phi_cur, host, N * 8, hipMemcpyHostToDevice, c->st)); break;
     case FSL_FIELD_PID: HIPCHK(c, hipMemcpyAsync(D.pid, host, N * 4, hipMemcpyHostToDevice, c->st)); break;

@@ -62,6 +62,8 @@ constexpr uint8_t CV_F = 1, CV_E0 = 2, CV_E = 4, CV_NEWG = 8, CV_NEWL = 16;
 constexpr uint8_t CV_GRM = 32;
 // a cell that entered the gas phase in this step (emptied or uncovered as gas)
 constexpr uint8_t CV_GAD = 64;
+// a node that its sphere leaves in this step, until its new state is decided
+constexpr uint8_t CV_UNC = 128;
 
 // counters in the control block
 enum Counter {
@@ -70,10 +72,13 @@ enum Counter {
     C_NCOMP,  // gas components listed by the splitting pass
     C_MERGED, // some bubbles merged in this step: cells are relabelled to their roots
     C_NGEN,   // tiles listed for the general path of the stream-collide step
+    C_NKT,    // tiles listed for the curvature
     C_BAR,    // arrivals at the grid barriers of the fused conversion phases
     C_BARS,   // ... of the fused labelling
     C_DONEC,  // blocks of the last conversion phase that are done
     C_DONEB,  // blocks of the bubble pass that are done
+    C_NUGAS,  // nodes uncovered as gas
+    C_DONEU,  // blocks of the uncover pass that are done
     C_DONES,  // blocks of a splitting phase that are done
     C_COUNT
 };
@@ -230,13 +235,15 @@ __host__ __device__ inline bool sphere_supported(const double x[3], double R, co
 
 // a coordinate along a periodic axis taken into [0, n)
 __host__ __device__ inline double wrap_coord(double v, int n) {
+    if (v >= 0.0 && v < n) return v;  // no division on the common path
     v -= n * floor(v / n);
     return v < n ? v : 0.0;  // v just below 0 can round up to n
 }
 
 // a displacement along an axis, the nearest image along a periodic one: [-n/2, n/2)
 __host__ __device__ inline double min_img(double d, int n, int per) {
-    return per ? d - n * floor(d / n + 0.5) : d;
+    if (!per || fabs(d) < 0.49 * n) return d;  // no division on the common path
+    return d - n * floor(d / n + 0.5);
 }
 
 // lever arm x - x_P along one axis from the FP32 mirror: the integer part x - anchor
@@ -304,14 +311,14 @@ __device__ __forceinline__ void block_phase() {
 }
 
 // A barrier between two phases over the first nblk blocks of a launch.  The callers launch
-// at most SYNC_BLOCKS blocks of 256 threads, a sixteenth of what the device holds, so the
+// at most SYNC_BLOCKS blocks of 256 threads (or SYNC_BIG of 1,024), a sixteenth of what the device holds, so the
 // blocks come to run together whatever else is running (kernels in other streams end, and
 // sixteen launches of this kind at once would still fit); one block needs no device
 // barrier.  bar counts arrivals since the step's counters were cleared, target the
 // arrivals the next barrier waits for.  Every wave's stores have left the wave before its
 // block arrives; one thread releases them to the device and acquires the others'.  The
 // wait is bounded: a launch that lost a block reports an error instead of hanging.
-constexpr int SYNC_BLOCKS = 128;
+constexpr int SYNC_BLOCKS = 128, SYNC_BIG = 32;  // blocks of 256 threads, of 1,024
 struct GridBarrier {
     int *bar;
     int nblk, target;
@@ -341,25 +348,48 @@ struct GridBarrier {
 };
 
 // true in every thread of the block that finishes last of nblk (its reads then see what
-// the others wrote); done counts the blocks and is left at zero
+// the others wrote); done counts the blocks and is left at zero.  STORES: the others hand
+// over plain stores; without, atomics only, which need no release (a release writes a
+// whole L2 back: 40 us of the 84 of the 2,048 blocks of the bubble pass)
+template <bool STORES = true>
 __device__ __forceinline__ bool last_block(int *done, int nblk) {
     __shared__ int last;
     __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
+        if (STORES) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nblk - 1;
-        __threadfence();
-        if (last) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (last) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
     return last != 0;
 }
 
+// FP64 sum over the wave with DPP on the two 32-bit halves: pairs, quads, half-row and row
+// mirrors leave every lane of a row of 16 with the row sum; row_bcast:15 on rows 1 and 3
+// then adds the row before, row_bcast:31 on rows 2 and 3 lane 31, so that lane 63 holds
+// the whole wave.  Every lane of the wave must be active; all get the sum.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add_d(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xF, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xF, false);
+    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    v = dpp_add_d<0xB1, 0xF>(v);
+    v = dpp_add_d<0x4E, 0xF>(v);
+    v = dpp_add_d<0x141, 0xF>(v);
+    v = dpp_add_d<0x140, 0xF>(v);
+    v = dpp_add_d<0x142, 0xA>(v);
+    v = dpp_add_d<0x143, 0xC>(v);
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 63);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 }  // namespace fsl

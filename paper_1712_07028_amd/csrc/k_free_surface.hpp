@@ -337,12 +337,12 @@ __global__ __launch_bounds__(256) void k_conv_fill(Geom G, Phys Ph, Dev D) {
     if (last_block(D.counters + C_DONEC, gridDim.x) && threadIdx.x == 0) merge_bubbles(D);
 }
 // ... or all of them in one launch (small boxes): a launch costs 4.5 us, a barrier of the
-// block a fraction of one and a grid barrier about two.  As many blocks take part as the
+// block a fraction of one and a grid barrier about three.  As many blocks take part as the
 // lists fill, two cells per half wave; the others leave.
 template <int ST>
-__global__ __launch_bounds__(256) void k_conversions(Geom G, Phys Ph, Dev D) {
+__global__ __launch_bounds__(1024) void k_conversions(Geom G, Phys Ph, Dev D) {
     const int n = list_len(D, C_NF) + list_len(D, C_NE0);
-    const int nblk = min((int)gridDim.x, (n + 15) / 16);
+    const int nblk = min((int)gridDim.x, (n + 63) / 64);
     if ((int)blockIdx.x >= nblk) return;
     GridBarrier B{D.counters + C_BAR, nblk, 0, D.err};
     const Items W(blockIdx.x, nblk);
@@ -419,7 +419,16 @@ __device__ __forceinline__ void bubble_accum(const Geom &G, const Dev &D, const 
                 continue;
             }
         }
+        // all loads of the chunk first (the fields reach beyond the last cell to a multiple
+        // of 256), then the cells in turn
         const uint32_t wds[4] = {f4.x, f4.y, f4.z, f4.w};
+        const uint4 u = *(const uint4 *)(D.bub + c0), v = *(const uint4 *)(D.bub + c0 + 8);
+        const uint32_t ids[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+        double ph[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            ph[k] = ((wds[k >> 2] >> (8 * (k & 3))) & 0xffu) == IFC && c0 + k < N ? phi[c0 + k] : 0.0;
+#pragma unroll
         for (int k = 0; k < 16; ++k, ++x) {
             if (x == G.nx) {
                 x = 0;
@@ -428,24 +437,39 @@ __device__ __forceinline__ void bubble_accum(const Geom &G, const Dev &D, const 
                     ++z;
                 }
             }
-            const int c = (int)(c0 + k);
+            const long long c = c0 + k;
             if (c >= N) break;
             const uint32_t f = (wds[k >> 2] >> (8 * (k & 3))) & 0xffu;
             if (f != GAS && f != IFC) continue;
-            const int id = D.bub[c];
+            const int id = (int)((ids[k >> 1] >> (16 * (k & 1))) & 0xffffu);
             const int b = id < nb ? L.root[id] : 0;
             if (relabel && id != b) D.bub[c] = (uint16_t)b;
             if (b != bc) {
                 flush();
                 bc = b;
             }
-            const double w = (f == GAS) ? 1.0 : 1.0 - phi[c];
+            const double w = (f == GAS) ? 1.0 : 1.0 - ph[k];
             a0 += w;
             a1 += w * x;
             a2 += w * y;
             a3 += w * z;
             if (f == GAS) a4 += 1.0;
             else a5 += 1.0;
+        }
+    }
+    // a wave whose lanes ended on one bubble sums first (64 lanes on one LDS address would
+    // queue)
+    const unsigned long long holds = __ballot(bc >= 0);
+    if (holds) {
+        const int b0 = __builtin_amdgcn_readlane(bc, __ffsll((long long)holds) - 1);
+        if (__ballot(bc >= 0 && bc != b0) == 0ull) {
+            a0 = wave_sum(a0);
+            a1 = wave_sum(a1);
+            a2 = wave_sum(a2);
+            a3 = wave_sum(a3);
+            a4 = wave_sum(a4);
+            a5 = wave_sum(a5);
+            bc = lane_id() == 0 ? b0 : -1;
         }
     }
     flush();
@@ -558,13 +582,24 @@ __global__ __launch_bounds__(256) void k_curv_mark(Geom G, Dev D, unsigned *tfla
         const long long c0 = ch * 16;
         const uint4 f4 = *(const uint4 *)(D.flags + c0);
         const uint32_t wds[4] = {f4.x, f4.y, f4.z, f4.w};
+        uint32_t any = 0;  // interface is the type with bit 1 set and bit 0 clear
+#pragma unroll
+        for (int k = 0; k < 4; ++k) any |= (wds[k] >> 1) & ~wds[k] & 0x01010101u;
+        if (!any) continue;
+        int x = (int)(c0 % G.nx);
+        const int yz = (int)(c0 / G.nx);
+        int y = yz % G.ny, z = yz / G.ny;
         int last = -1;
-        for (int e = 0; e < 16; ++e) {
-            const long long c = c0 + e;
-            if (c >= N) break;
+        for (int e = 0; e < 16 && c0 + e < N; ++e, ++x) {
+            if (x == G.nx) {
+                x = 0;
+                if (++y == G.ny) {
+                    y = 0;
+                    ++z;
+                }
+            }
             if (((wds[e >> 2] >> (8 * (e & 3))) & 0xffu) != IFC) continue;
-            const int i = (int)(c % G.nx), j = (int)((c / G.nx) % G.ny), k = (int)(c / ((long long)G.nx * G.ny));
-            const int t = (k * kty + j / KTY) * ktx + i / KTX;
+            const int t = (z * kty + y / KTY) * ktx + x / KTX;
             if (t == last) continue;
             last = t;
             if (atomicExch(tflag + t, 1u) == 0u) tlist[atomicAdd(count, 1)] = t;
@@ -599,10 +634,26 @@ __global__ __launch_bounds__(256) void k_curv_tiles(Geom G, Dev D, const double 
     for (int it = blockIdx.x; it < nt; it += gridDim.x) {
         const int t = tlist[it];
         const int x0 = (t % ktx) * KTX, y0 = ((t / ktx) % kty) * KTY, z = t / (ktx * kty);
-        for (int e = threadIdx.x; e < KFX * KFY * KFZ; e += blockDim.x) {
+        // the tile's cell types in one batch of loads, the interface cells' fill levels in a
+        // second (a loop over the elements paid both latencies nine times)
+        constexpr int NF = KFX * KFY * KFZ, K = (NF + 255) / 256;
+        int ce[K];
+        uint8_t fe[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int e = min((int)threadIdx.x + 256 * k, NF - 1);
             const int ex = e % KFX, ey = (e / KFX) % KFY, ez = e / (KFX * KFY);
-            F[ez][ey][ex] = st_fill(G, D, phi, kc_wrap(x0 - 2 + ex, G.nx, G.per[0]),
-                                    kc_wrap(y0 - 2 + ey, G.ny, G.per[1]), kc_wrap(z - 2 + ez, G.nz, G.per[2]));
+            ce[k] = kc_wrap(x0 - 2 + ex, G.nx, G.per[0]) +
+                    G.nx * (kc_wrap(y0 - 2 + ey, G.ny, G.per[1]) + G.ny * kc_wrap(z - 2 + ez, G.nz, G.per[2]));
+            fe[k] = D.flags[ce[k]];
+        }
+        double ve[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) ve[k] = fe[k] == GAS ? 0.0 : fe[k] == IFC ? phi[ce[k]] : 1.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int e = (int)threadIdx.x + 256 * k;
+            if (e < NF) (&F[0][0][0])[e] = ve[k];
         }
         __syncthreads();
         for (int e = threadIdx.x; e < KNX * KNY * KNZ; e += blockDim.x) {

@@ -13,44 +13,50 @@ namespace fsl {
 constexpr int CLAIM_NONE = 0x7fffffff;
 
 // per particle: F, T of the step (reported), mass paid by moving bounce-back to the
-// ledger (block reduction then one atomic per block), accumulators cleared
+// ledger (block reduction then one atomic per block), accumulators cleared.  A particle's
+// copies lie in 64 consecutive values: a wave reads and clears them in one access each (a
+// thread per particle touched 64 lines an access), four particles at a time, and sums
+// component (lane & 7) over the copies in order.
 __global__ __launch_bounds__(256) void k_part_forces(Dev D, int integrate) {
-    __shared__ double red[256];
-    int P = blockIdx.x * blockDim.x + threadIdx.x;
+    static_assert(ACC_COPIES * ACC_STRIDE == 64, "one value per lane");
+    __shared__ double red[4];
+    constexpr int U = 4;
+    const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
     double dm = 0.0;
-    if (P < D.np) {
-        double *a = D.pacc + acc_at(P, 0);
-        double *o = D.pFT + (long long)P * 6;
-        double *op = D.pFTp + (long long)P * 6;
-        double s[7];
+    for (int P0 = (blockIdx.x * 4 + wv) * U; P0 < D.np; P0 += gridDim.x * 4 * U) {
+        double v[U], o[U];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) s[k] = a[k];
-        for (int j = 1; j < ACC_COPIES; ++j)
-#pragma unroll
-            for (int k = 0; k < 7; ++k) s[k] += a[j * ACC_STRIDE + k];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            op[k] = o[k];
-            o[k] = s[k];
+        for (int j = 0; j < U; ++j) {
+            const int P = min(P0 + j, D.np - 1);
+            v[j] = D.pacc[acc_at(P, 0) + lane];
+            o[j] = D.pFT[(long long)P * 6 + min(lane, 5)];
         }
-        dm = s[6];
-        for (int k = 0; k < ACC_COPIES * ACC_STRIDE; ++k) a[k] = 0.0;
-        if (integrate) {
-            double *t = D.ptab + (long long)P * P_STRIDE;
-            t[P_XOLD] = t[P_X];
-            t[P_XOLD + 1] = t[P_X + 1];
-            t[P_XOLD + 2] = t[P_X + 2];
-            double *fl = D.pFl + (long long)P * 3;
-            fl[0] = fl[1] = fl[2] = 0.0;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int P = P0 + j;
+            double s = __shfl(v[j], lane & 7);
+#pragma unroll
+            for (int k = 1; k < ACC_COPIES; ++k) s += __shfl(v[j], (lane & 7) + k * ACC_STRIDE);
+            if (P >= D.np) continue;
+            D.pacc[acc_at(P, 0) + lane] = 0.0;
+            if (lane < 6) {
+                D.pFTp[(long long)P * 6 + lane] = o[j];
+                D.pFT[(long long)P * 6 + lane] = s;
+            }
+            if (lane == 6) dm += s;
+            if (integrate && lane < 3) {  // the launch-per-substep update follows
+                double *t = D.ptab + (long long)P * P_STRIDE;
+                t[P_XOLD + lane] = t[P_X + lane];
+                D.pFl[(long long)P * 3 + lane] = 0.0;
+            }
         }
     }
-    red[threadIdx.x] = dm;
+    if (lane == 6) red[wv] = dm;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        const double s = (red[0] + red[1]) + (red[2] + red[3]);
+        if (s != 0.0) unsafeAtomicAdd(D.ledger, -s);
     }
-    if (threadIdx.x == 0 && red[0] != 0.0) unsafeAtomicAdd(D.ledger, -red[0]);
 }
 
 // node box [lo, hi] of a sphere: clipped to the box along walled axes, unwrapped along
@@ -103,16 +109,19 @@ __device__ __forceinline__ bool inside(double i, double j, double k, const doubl
 
 // FP32 mirror used by the stream-collide kernel: integer anchor floor(x_P), the
 // fraction x_P - anchor, velocity and angular velocity
+__device__ __forceinline__ void mirror_store(const Dev &D, int P, const double *x, const double *u, const double *w) {
+    float4 *m = D.pmir + 4LL * P;
+    const double a0 = floor(x[0]), a1 = floor(x[1]), a2 = floor(x[2]);
+    // PMir order: anchor, fraction, u, omega
+    m[0] = make_float4((float)a0, (float)a1, (float)a2, (float)(x[0] - a0));
+    m[1] = make_float4((float)(x[1] - a1), (float)(x[2] - a2), (float)u[0], (float)u[1]);
+    m[2] = make_float4((float)u[2], (float)w[0], (float)w[1], (float)w[2]);
+    m[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
 __global__ void k_part_mirror(Dev D) {
     GRID_STRIDE(P, D.np) {
         const double *t = D.ptab + (long long)P * P_STRIDE;
-        float4 *m = D.pmir + 4LL * P;
-        double a0 = floor(t[P_X]), a1 = floor(t[P_X + 1]), a2 = floor(t[P_X + 2]);
-        // PMir order: anchor, fraction, u, omega
-        m[0] = make_float4((float)a0, (float)a1, (float)a2, (float)(t[P_X] - a0));
-        m[1] = make_float4((float)(t[P_X + 1] - a1), (float)(t[P_X + 2] - a2), (float)t[P_U], (float)t[P_U + 1]);
-        m[2] = make_float4((float)t[P_U + 2], (float)t[P_W], (float)t[P_W + 1], (float)t[P_W + 2]);
-        m[3] = make_float4(0.f, 0.f, 0.f, 0.f);
+        mirror_store(D, P, t + P_X, t + P_U, t + P_W);
     }
 }
 
@@ -232,11 +241,42 @@ __device__ __forceinline__ void wave_push2(bool pred, int a, int b, int *list, i
 // (about one per wave), so they are gathered per block in LDS and appended with one
 // atomic per block: one atomic per pair on the same counter serialises.
 constexpr int PAIR_BUF = 1024;
+struct PairLds {
+    int2 buf[PAIR_BUF];
+    int cnt, base;
+};
+
+// the pair (P, Qp) to the block's buffer when the surfaces are closer than the reach
+__device__ __forceinline__ void pair_test(const Dev &D, const PGrid &PG, PairLds &L, int P, const double *x, int Qp,
+                                          const double *y, int pcap) {
+    const double d0 = min_img(y[0] - x[0], PG.n[0], PG.per[0]), d1 = min_img(y[1] - x[1], PG.n[1], PG.per[1]),
+                 d2 = min_img(y[2] - x[2], PG.n[2], PG.per[2]);
+    const double gap = sqrt(d0 * d0 + d1 * d1 + d2 * d2) - x[P_R] - y[P_R];
+    if (gap >= PG.reach) return;
+    const int k = atomicAdd(&L.cnt, 1);
+    if (k < PAIR_BUF) {
+        L.buf[k] = make_int2(P, Qp);
+    } else {  // the block's buffer is full: straight to the list
+        const int g = atomicAdd(D.counters + C_NPAIRS, 1);
+        if (g < pcap) D.pairs[g] = make_int2(P, Qp);
+        else atomicOr(D.err, ERR_CAP);
+    }
+}
+// the block's pairs to the list; every thread of the block
+__device__ __forceinline__ void pairs_flush(const Dev &D, PairLds &L, int pcap) {
+    __syncthreads();
+    const int n = min(L.cnt, PAIR_BUF);
+    if (threadIdx.x == 0) L.base = n ? atomicAdd(D.counters + C_NPAIRS, n) : 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+        if (L.base + k < pcap) D.pairs[L.base + k] = L.buf[k];
+        else atomicOr(D.err, ERR_CAP);
+    }
+}
 
 __global__ __launch_bounds__(256) void k_pairs(Dev D, PGrid PG, int pcap) {
-    __shared__ int2 buf[PAIR_BUF];
-    __shared__ int cnt, base;
-    if (threadIdx.x == 0) cnt = 0;
+    __shared__ PairLds L;
+    if (threadIdx.x == 0) L.cnt = 0;
     __syncthreads();
     const int total = D.np * 27;
     // whole blocks take the same rounds, so every thread reaches the barriers below
@@ -264,111 +304,131 @@ __global__ __launch_bounds__(256) void k_pairs(Dev D, PGrid PG, int pcap) {
         const int cell = cc[0] + PG.g[0] * (cc[1] + PG.g[1] * cc[2]);
         for (int s = D.gridStart[cell]; s < D.gridStart[cell + 1]; ++s) {
             const int Qp = D.gridIdx[s];
-            if (Qp <= P) continue;
-            const double *y = D.ptab + (long long)Qp * P_STRIDE;
-            const double d0 = min_img(y[0] - x[0], PG.n[0], PG.per[0]), d1 = min_img(y[1] - x[1], PG.n[1], PG.per[1]),
-                         d2 = min_img(y[2] - x[2], PG.n[2], PG.per[2]);
-            const double gap = sqrt(d0 * d0 + d1 * d1 + d2 * d2) - x[P_R] - y[P_R];
-            if (gap >= PG.reach) continue;
-            const int k = atomicAdd(&cnt, 1);
-            if (k < PAIR_BUF) {
-                buf[k] = make_int2(P, Qp);
-            } else {  // the block's buffer is full: straight to the list
-                const int g = atomicAdd(D.counters + C_NPAIRS, 1);
-                if (g < pcap) D.pairs[g] = make_int2(P, Qp);
-                else atomicOr(D.err, ERR_CAP);
-            }
+            if (Qp > P) pair_test(D, PG, L, P, x, Qp, D.ptab + (long long)Qp * P_STRIDE, pcap);
         }
     }
-    __syncthreads();
-    const int n = min(cnt, PAIR_BUF);
-    if (threadIdx.x == 0) base = n ? atomicAdd(D.counters + C_NPAIRS, n) : 0;
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
-        if (base + k < pcap) D.pairs[base + k] = buf[k];
-        else atomicOr(D.err, ERR_CAP);
+    pairs_flush(D, L, pcap);
+}
+
+// Small tables (up to PAIRS_DIRECT spheres): every pair tested, in one launch instead of the
+// seven that build and walk the grid (4.6 us each whatever the size).  A block takes
+// PDIR_P spheres (x) against 256 later ones (y), one per thread, so that the launch is one
+// round of loads deep.  A first test in FP32 on the axes' distances (nearest images of
+// centres in [0, n); half a cell of slack, far beyond the rounding of coordinates below
+// 2^16) leaves the distance itself to the near ones.
+constexpr int PAIRS_DIRECT = 2048, PDIR_P = 16;
+__global__ __launch_bounds__(256) void k_pairs_direct(Dev D, PGrid PG, int pcap) {
+    __shared__ PairLds L;
+    __shared__ float c[PDIR_P][4];
+    const int P0 = blockIdx.x * PDIR_P, n = min(PDIR_P, D.np - P0);
+    const int Q0 = blockIdx.y * 256;
+    if (Q0 + 255 <= P0) return;  // every sphere of the chunk comes before
+    if (threadIdx.x == 0) L.cnt = 0;
+    if ((int)threadIdx.x < 4 * n) {
+        const int p = threadIdx.x >> 2, k = threadIdx.x & 3;
+        c[p][k] = (float)D.ptab[(long long)(P0 + p) * P_STRIDE + (k < 3 ? P_X + k : P_R)];
     }
+    const int Qp = Q0 + (int)threadIdx.x;
+    const double *y = D.ptab + (long long)min(Qp, D.np - 1) * P_STRIDE;
+    const float y0 = (float)y[P_X], y1 = (float)y[P_X + 1], y2 = (float)y[P_X + 2],
+                yr = (float)(y[P_R] + PG.reach) + 0.5f;
+    __syncthreads();
+    auto apart = [&](float d, int k) {
+        d = fabsf(d);
+        return PG.per[k] ? fminf(d, (float)PG.n[k] - d) : d;
+    };
+    for (int p = 0; p < n; ++p) {
+        const float d0 = apart(y0 - c[p][0], 0), d1 = apart(y1 - c[p][1], 1), d2 = apart(y2 - c[p][2], 2);
+        const float r = c[p][3] + yr;
+        if (P0 + p < Qp && Qp < D.np && d0 * d0 + d1 * d1 + d2 * d2 < r * r)
+            pair_test(D, PG, L, P0 + p, D.ptab + (long long)(P0 + p) * P_STRIDE, Qp, y, pcap);
+    }
+    pairs_flush(D, L, pcap);
 }
 
 // Momentum exchange between two particles (Sec. 2.3): a node inside particle P'
 // with a link into particle P contributes with equilibrium populations at rho = 1
 // and the rigid velocity of P' at the node, Delta j = 2 c_q e^+_q(1, u_P'(x)), to
 // P's force and torque.  Such nodes exist only for pairs closer than sqrt(2), all
-// of which are in the candidate list; one wave per pair scans the nodes of each
-// particle that lie within one cell of the other's bounding box.
-__global__ __launch_bounds__(256) void k_solid_pairs(Geom G, Dev D, int pcap) {
-    const int n = min(D.counters[C_NPAIRS], pcap);
+// of which are in the candidate list; one wave per pair and direction (of P' towards P)
+// scans the nodes of P' that lie within one cell of P's bounding box.  A node's links are
+// decided by the inside tests first, which coverage takes as well, so that only nodes
+// with such a link read cell types and owners.
+// nodes of one sphere next to nodes of the other need the centres closer than the radii
+// plus the longest link (sqrt 2); margin 1.5
+__device__ __forceinline__ bool pair_links(const Geom &G, const Dev &D, int2 pr) {
+    const double *ta = D.ptab + (long long)pr.x * P_STRIDE, *tb = D.ptab + (long long)pr.y * P_STRIDE;
+    const double d0 = min_img(ta[P_X] - tb[P_X], G.nx, G.per[0]), d1 = min_img(ta[P_X + 1] - tb[P_X + 1], G.ny, G.per[1]),
+                 d2 = min_img(ta[P_X + 2] - tb[P_X + 2], G.nz, G.per[2]);
+    const double reach = ta[P_R] + tb[P_R] + 1.5;
+    return !(d0 * d0 + d1 * d1 + d2 * d2 > reach * reach);
+}
+__device__ __forceinline__ void solid_pair(const Geom &G, const Dev &D, int Pp, int Po, int copy) {
     const int lane = threadIdx.x & 63;
-    for (int k = blockIdx.x * 4 + (threadIdx.x >> 6); k < n; k += gridDim.x * 4) {
-    const int pa = D.pairs[k].x, pb = D.pairs[k].y;
-    {
-        // nodes of one sphere next to nodes of the other need the centres closer than
-        // the radii plus the longest link (sqrt 2); margin 1.5
-        const double *ta = D.ptab + (long long)pa * P_STRIDE, *tb = D.ptab + (long long)pb * P_STRIDE;
-        const double d0 = min_img(ta[P_X] - tb[P_X], G.nx, G.per[0]), d1 = min_img(ta[P_X + 1] - tb[P_X + 1], G.ny, G.per[1]),
-                     d2 = min_img(ta[P_X + 2] - tb[P_X + 2], G.nz, G.per[2]);
-        const double reach = ta[P_R] + tb[P_R] + 1.5;
-        if (d0 * d0 + d1 * d1 + d2 * d2 > reach * reach) continue;
-    }
-    for (int side = 0; side < 2; ++side) {
-        const int Pp = side ? pb : pa, Po = side ? pa : pb;
-        const double *tp = D.ptab + (long long)Pp * P_STRIDE, *tq = D.ptab + (long long)Po * P_STRIDE;
-        // the other sphere's centre at its image nearest to this one (node coordinates
-        // below stay in this sphere's frame; node_at wraps them)
-        double to[3];
-        image_near(G, tq + P_X, tp + P_X, to);
-        const double Ro = tq[P_R];
-        const double ro = (Ro + 1.5) * (Ro + 1.5);
-        int lo[3], hi[3], lo2[3], hi2[3];
-        sphere_box(G, tp + P_X, tp[P_R], lo, hi);
-        sphere_box(G, to, Ro + 1.0, lo2, hi2);
-        for (int a = 0; a < 3; ++a) { lo[a] = max(lo[a], lo2[a]); hi[a] = min(hi[a], hi2[a]); }
-        double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-        if (lo[0] <= hi[0] && lo[1] <= hi[1] && lo[2] <= hi[2]) {
-            const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
-            const int tot = ex * ey * ez;
-            for (int s2 = lane; s2 < tot; s2 += 64) {
-                const int i = lo[0] + s2 % ex, j = lo[1] + (s2 / ex) % ey, kk = lo[2] + s2 / (ex * ey);
-                {
-                    // only nodes within a link of the other sphere can have such links
-                    const double e0 = i - to[0], e1 = j - to[1], e2 = kk - to[2];
-                    if (e0 * e0 + e1 * e1 + e2 * e2 > ro) continue;
-                }
-                // a node of Pp lies inside Pp and a node of Po inside Po (coverage takes
-                // the same inside test), so cells that fail it need no loads
-                if (!inside(i, j, kk, tp + P_X, tp[P_R])) continue;
-                const int c = node_at(G, i, j, kk);
-                if (D.flags[c] != SOL || D.pid[c] != Pp) continue;
-                const double rx = i - tp[P_X], ry = j - tp[P_X + 1], rz = kk - tp[P_X + 2];
-                const double ur0 = tp[P_U] + (tp[P_W + 1] * rz - tp[P_W + 2] * ry);
-                const double ur1 = tp[P_U + 1] + (tp[P_W + 2] * rx - tp[P_W] * rz);
-                const double ur2 = tp[P_U + 2] + (tp[P_W] * ry - tp[P_W + 1] * rx);
-                const double uu = ur0 * ur0 + ur1 * ur1 + ur2 * ur2;
-                const double ox = i - to[0], oy = j - to[1], oz = kk - to[2];
-                for (int q = 1; q < Q; ++q) {
-                    if (!inside(i + cx(q), j + cy(q), kk + cz(q), to, Ro)) continue;
-                    int iw, jw, kw;
-                    cell_xyz(G, c, iw, jw, kw);
-                    const int nb = nbr_idx(G, iw, jw, kw, q, 1);
-                    if (nb < 0 || D.flags[nb] != SOL || D.pid[nb] != Po) continue;
-                    const double cu = cx(q) * ur0 + cy(q) * ur1 + cz(q) * ur2;
-                    const double e2 = 2.0 * wqd(q) * (1.0 + 4.5 * cu * cu - 1.5 * uu);
-                    const double j0 = cx(q) * e2, j1 = cy(q) * e2, j2 = cz(q) * e2;
-                    acc[0] += j0;
-                    acc[1] += j1;
-                    acc[2] += j2;
-                    acc[3] += oy * j2 - oz * j1;
-                    acc[4] += oz * j0 - ox * j2;
-                    acc[5] += ox * j1 - oy * j0;
-                }
-            }
+    const double *tp = D.ptab + (long long)Pp * P_STRIDE, *tq = D.ptab + (long long)Po * P_STRIDE;
+    // the other sphere's centre at its image nearest to this one (node coordinates
+    // below stay in this sphere's frame; node_at wraps them)
+    double to[3];
+    image_near(G, tq + P_X, tp + P_X, to);
+    const double Ro = tq[P_R], Rp = tp[P_R];
+    const double xp[3] = {tp[P_X], tp[P_X + 1], tp[P_X + 2]};
+    const double ro = (Ro + 1.5) * (Ro + 1.5);
+    int lo[3], hi[3], lo2[3], hi2[3];
+    sphere_box(G, xp, Rp, lo, hi);
+    sphere_box(G, to, Ro + 1.0, lo2, hi2);
+    for (int a = 0; a < 3; ++a) { lo[a] = max(lo[a], lo2[a]); hi[a] = min(hi[a], hi2[a]); }
+    if (lo[0] > hi[0] || lo[1] > hi[1] || lo[2] > hi[2]) return;
+    double acc[6] = {0, 0, 0, 0, 0, 0};
+    bool some = false;
+    const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
+    const int tot = ex * ey * ez;
+    for (int s = lane; s < tot; s += 64) {
+        const int i = lo[0] + s % ex, j = lo[1] + (s / ex) % ey, k = lo[2] + s / (ex * ey);
+        const double ox = i - to[0], oy = j - to[1], oz = k - to[2];
+        // only nodes within a link of the other sphere can have such links
+        if (ox * ox + oy * oy + oz * oz > ro || !inside(i, j, k, xp, Rp)) continue;
+        unsigned links = 0u;
+#pragma unroll
+        for (int q = 1; q < Q; ++q) links |= (unsigned)inside(i + cx(q), j + cy(q), k + cz(q), to, Ro) << q;
+        if (!links) continue;
+        // the node and the far ends of its links in one batch of loads
+        const int c = node_at(G, i, j, k);
+        int iw, jw, kw;
+        cell_xyz(G, c, iw, jw, kw);
+        unsigned real = 0u;
+#pragma unroll
+        for (int q = 1; q < Q; ++q) {
+            const int nb = (links >> q) & 1u ? nbr_idx(G, iw, jw, kw, q, 1) : -1;
+            const uint8_t f = D.flags[nb < 0 ? c : nb];
+            const int o = D.pid[nb < 0 ? c : nb];
+            real |= (unsigned)((nb >= 0) & (f == SOL) & (o == Po)) << q;
         }
-        double *dst = D.pacc + acc_at(Po, k & (ACC_COPIES - 1));
-        for (int a = 0; a < 6; ++a) {
-            const double v = wave_sum(acc[a]);
-            if (lane == 0 && v != 0.0) unsafeAtomicAdd(dst + a, v);
+        if ((D.flags[c] != SOL) | (D.pid[c] != Pp)) continue;
+        const double rx = i - xp[0], ry = j - xp[1], rz = k - xp[2];
+        const double ur0 = tp[P_U] + (tp[P_W + 1] * rz - tp[P_W + 2] * ry);
+        const double ur1 = tp[P_U + 1] + (tp[P_W + 2] * rx - tp[P_W] * rz);
+        const double ur2 = tp[P_U + 2] + (tp[P_W] * ry - tp[P_W + 1] * rx);
+        const double uu = ur0 * ur0 + ur1 * ur1 + ur2 * ur2;
+#pragma unroll
+        for (int q = 1; q < Q; ++q) {
+            if (!((real >> q) & 1u)) continue;
+            const double cu = cx(q) * ur0 + cy(q) * ur1 + cz(q) * ur2;
+            const double e2 = 2.0 * wqd(q) * (1.0 + 4.5 * cu * cu - 1.5 * uu);
+            const double j0 = cx(q) * e2, j1 = cy(q) * e2, j2 = cz(q) * e2;
+            acc[0] += j0;
+            acc[1] += j1;
+            acc[2] += j2;
+            acc[3] += oy * j2 - oz * j1;
+            acc[4] += oz * j0 - ox * j2;
+            acc[5] += ox * j1 - oy * j0;
+            some = true;
         }
     }
+    if (!__ballot(some)) return;
+    double *dst = D.pacc + acc_at(Po, copy & (ACC_COPIES - 1));
+    for (int a = 0; a < 6; ++a) {
+        const double v = wave_sum(acc[a]);
+        if (lane == 0 && v != 0.0) unsafeAtomicAdd(dst + a, v);
     }
 }
 
@@ -382,10 +442,8 @@ __global__ __launch_bounds__(256) void k_solid_pairs(Geom G, Dev D, int pcap) {
 // the face by the lattice pressure 1/3.  One wave per particle walks the face-layer
 // nodes of its node box; the torque arm runs from the centre to the far end of the
 // link.
-__global__ __launch_bounds__(256) void k_face_links(Geom G, Phys Ph, Dev D) {
-    const int P = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (P >= D.np) return;
-    const int lane = threadIdx.x & 63;
+// the node box of particle P reaches a face layer of a walled axis
+__device__ __forceinline__ bool touches_face(const Geom &G, const Dev &D, int P) {
     const double *t = D.ptab + (long long)P * P_STRIDE;
     const int n[3] = {G.nx, G.ny, G.nz};
     int lo[3], hi[3];
@@ -393,8 +451,18 @@ __global__ __launch_bounds__(256) void k_face_links(Geom G, Phys Ph, Dev D) {
     bool touch = false;
     for (int a = 0; a < 3; ++a)
         if (!G.per[a] && lo[a] <= hi[a] && (lo[a] == 0 || hi[a] == n[a] - 1)) touch = true;
-    if (!touch) return;  // the whole wave: no face layer in reach
+    return touch;
+}
+__device__ __forceinline__ void face_links(const Geom &G, const Phys &Ph, const Dev &D, int P) {
+    const int lane = threadIdx.x & 63;
+    const double *t = D.ptab + (long long)P * P_STRIDE;
+    const int n[3] = {G.nx, G.ny, G.nz};
+    int lo[3], hi[3];
+    sphere_box(G, t + P_X, t[P_R], lo, hi);
     double acc[6] = {0, 0, 0, 0, 0, 0};
+    float wu[18];
+#pragma unroll
+    for (int k = 0; k < 18; ++k) wu[k] = D.wallu[k];
     // the face layers of the walled axes that the node box reaches; a node on the
     // layers of two axes is taken with the lower axis
     for (int a = 0; a < 3; ++a) {
@@ -414,7 +482,7 @@ __global__ __launch_bounds__(256) void k_face_links(Geom G, Phys Ph, Dev D) {
                     if (!G.per[k] && (p[k] == 0 || p[k] == n[k] - 1)) lower = true;
                 if (lower || !inside(p[0], p[1], p[2], t + P_X, t[P_R])) continue;
                 const int c = node_at(G, p[0], p[1], p[2]);
-                if (D.flags[c] != SOL || D.pid[c] != P) continue;
+                if ((D.flags[c] != SOL) | (D.pid[c] != P)) continue;
                 for (int q = 1; q < Q; ++q) {
                     const int f[3] = {p[0] - cx(q), p[1] - cy(q), p[2] - cz(q)};  // far end
                     int fa = -1;
@@ -428,10 +496,14 @@ __global__ __launch_bounds__(256) void k_face_links(Geom G, Phys Ph, Dev D) {
                     const int sd = fa >= 0 && f[fa] >= 0 ? 1 : 0;
                     double u0 = 0.0, u1 = 0.0, u2 = 0.0;
                     if (fa >= 0) {
-                        const float *uw = D.wallu + (fa * 2 + sd) * 3;
-                        u0 = uw[0];
-                        u1 = uw[1];
-                        u2 = uw[2];
+                        const int f6 = fa * 2 + sd;
+#pragma unroll
+                        for (int k = 0; k < 6; ++k)
+                            if (k == f6) {
+                                u0 = wu[3 * k];
+                                u1 = wu[3 * k + 1];
+                                u2 = wu[3 * k + 2];
+                            }
                     }
                     const double cu = cx(q) * u0 + cy(q) * u1 + cz(q) * u2;
                     const double e2 = 2.0 * wqd(q) * (1.0 + 4.5 * cu * cu - 1.5 * (u0 * u0 + u1 * u1 + u2 * u2));
@@ -460,6 +532,41 @@ __global__ __launch_bounds__(256) void k_face_links(Geom G, Phys Ph, Dev D) {
     }
 }
 
+// Both kinds of links that the lattice update does not see, in one launch: the first
+// pair_blocks blocks take the pairs, the others the particles for the box faces.  A wave
+// takes `chunk` of them at a time (at most 64), a lane testing each, and works those that
+// have such links in turn: one on small tables, where the waves are few and a chain of
+// several is latency; eight on large ones, where few of the 1e5 spheres touch anything.
+__global__ __launch_bounds__(256) void k_solid_links(Geom G, Phys Ph, Dev D, int pcap, int pair_blocks, int chunk) {
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if ((int)blockIdx.x < pair_blocks) {
+        const int n = min(D.counters[C_NPAIRS], pcap);
+        // two waves per group of pairs, one for each direction of their links
+        for (int k0 = (blockIdx.x * 2 + (wv >> 1)) * chunk; k0 < n; k0 += pair_blocks * 2 * chunk) {
+            const int k = k0 + lane;
+            const bool has = lane < chunk && k < n;
+            const int2 pr = has ? D.pairs[k] : make_int2(0, 0);
+            unsigned long long m = __ballot(has && pair_links(G, D, pr));
+            while (m) {
+                const int l = __ffsll((long long)m) - 1;
+                m &= m - 1ull;
+                const int a = __builtin_amdgcn_readlane(pr.x, l), b = __builtin_amdgcn_readlane(pr.y, l);
+                if (wv & 1) solid_pair(G, D, b, a, k0 + l);
+                else solid_pair(G, D, a, b, k0 + l);
+            }
+        }
+        return;
+    }
+    const int P0 = ((blockIdx.x - pair_blocks) * 4 + wv) * chunk;
+    const int P = P0 + lane;
+    unsigned long long m = __ballot(lane < chunk && P < D.np && touches_face(G, D, min(P, D.np - 1)));
+    while (m) {
+        const int l = __ffsll((long long)m) - 1;
+        m &= m - 1ull;
+        face_links(G, Ph, D, P0 + l);
+    }
+}
+
 // Pair force of one candidate pair (x, u of each sphere; f: force on sphere 1, sphere 2
 // takes -f).  Contact (the paper gives no contact model; reading): overlapping spheres
 // repel by a linear spring of stiffness kc along the line of centres, -kc (R1 + R2 -
@@ -472,10 +579,11 @@ __device__ __forceinline__ bool pair_force(const Geom &G, const double *x1, cons
     const double dc = 2.0 / 3.0;
     const double d0 = min_img(x2[0] - x1[0], G.nx, G.per[0]), d1 = min_img(x2[1] - x1[1], G.ny, G.per[1]),
                  d2 = min_img(x2[2] - x1[2], G.nz, G.per[2]);
-    const double dist = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-    const double sR = R1 + R2;
-    double gap = dist - sR;
+    const double sR = R1 + R2, dd = d0 * d0 + d1 * d1 + d2 * d2;
     f[0] = f[1] = f[2] = 0.0;
+    if (dd > (sR + dc) * (sR + dc) * (1.0 + 1e-12)) return false;  // beyond Delta_c: no root taken
+    const double dist = sqrt(dd);
+    double gap = dist - sR;
     if (kc > 0.0 && dist < sR && dist > 0.0) {
         const double s = -kc * (sR - dist) / dist;
         f[0] = s * d0;
@@ -537,34 +645,50 @@ __global__ void k_lub(Geom G, Dev D, double mu, double kc, int pcap) {
     }
 }
 
-// one semi-implicit Euler substep of particle t (x, u, omega may live elsewhere than
-// the table): velocity from F_hyd + m g + F_pair, then position; angular velocity from
-// T_hyd; the no-slip faces act through face_force at the position and velocity the
-// substep starts from; normal velocity reversed when closer than R to a wall face and
-// moving towards it; along a periodic axis the centre kept in [0, n).  F_hyd, T_hyd are the mean of
+// What a sphere keeps through the substeps of one lattice step: F_hyd, T_hyd are the mean of
 // this and the previous step's momentum exchange (two-step average that removes the
 // period-two oscillation of explicit coupling), or this step's alone after a reset.
-__device__ __forceinline__ void substep_one(const Geom &G, const Dev &D, int P, double *x, double *u, double *w,
-                                            double *fl, double dt, const double gg[3], int have_prev, double mu,
-                                            double kc, int wmask) {
+// F: F_hyd + m g, du: the change of velocity in a substep without pair and face forces, dw:
+// that of the angular velocity.
+struct SubstepConst {
+    double R, mP, F[3], du[3], dw[3];
+};
+__device__ __forceinline__ SubstepConst substep_const(const Dev &D, int P, int have_prev, double dt, const double gg[3]) {
     const double *t = D.ptab + (long long)P * P_STRIDE;
     const double *FTn = D.pFT + (long long)P * 6, *FTp = D.pFTp + (long long)P * 6;
-    const double R = t[P_R];
-    if (wmask) face_force(G, wmask, x, u, R, mu, kc, fl);
-    const double mP = t[P_RHO] * (4.0 / 3.0) * M_PI * R * R * R;
-    const double IP = 0.4 * mP * R * R;
-    const int n[3] = {G.nx, G.ny, G.nz};
+    SubstepConst c;
+    c.R = t[P_R];
+    c.mP = t[P_RHO] * (4.0 / 3.0) * M_PI * c.R * c.R * c.R;
+    const double IP = 0.4 * c.mP * c.R * c.R;
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
         const double Fh = have_prev ? 0.5 * (FTn[d] + FTp[d]) : FTn[d];
         const double Th = have_prev ? 0.5 * (FTn[3 + d] + FTp[3 + d]) : FTn[3 + d];
-        const double F = Fh + mP * gg[d] + fl[d];
-        u[d] += dt * F / mP;
+        c.F[d] = Fh + c.mP * gg[d];
+        c.du[d] = dt * c.F[d] / c.mP;
+        c.dw[d] = dt * Th / IP;
+    }
+    return c;
+}
+
+// one semi-implicit Euler substep of a sphere: velocity from F_hyd + m g + F_pair (fl,
+// consumed), then position; angular velocity from T_hyd; the no-slip faces act through
+// face_force at the position and velocity the substep starts from; normal velocity
+// reversed when closer than R to a wall face and moving towards it; along a periodic axis
+// the centre kept in [0, n)
+__device__ __forceinline__ void substep_one(const Geom &G, const SubstepConst &c, double *x, double *u, double *w,
+                                            double *fl, double dt, double mu, double kc, int wmask) {
+    if (wmask) face_force(G, wmask, x, u, c.R, mu, kc, fl);
+    const int n[3] = {G.nx, G.ny, G.nz};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        u[d] += fl[d] == 0.0 ? c.du[d] : dt * (c.F[d] + fl[d]) / c.mP;
         x[d] += dt * u[d];
         if (G.per[d]) x[d] = wrap_coord(x[d], n[d]);
-        w[d] += dt * Th / IP;
+        w[d] += c.dw[d];
         if (!G.per[d]) {
-            if (x[d] < R - 0.5 && u[d] < 0) u[d] = -u[d];
-            if (x[d] > n[d] - 0.5 - R && u[d] > 0) u[d] = -u[d];
+            if (x[d] < c.R - 0.5 && u[d] < 0) u[d] = -u[d];
+            if (x[d] > n[d] - 0.5 - c.R && u[d] > 0) u[d] = -u[d];
         }
         fl[d] = 0.0;
     }
@@ -575,60 +699,105 @@ __global__ void k_substep(Dev D, Geom G, double dt, double g0, double g1, double
     GRID_STRIDE(P, D.np) {
         double *t = D.ptab + (long long)P * P_STRIDE;
         const double gg[3] = {g0, g1, g2};
-        substep_one(G, D, P, t + P_X, t + P_U, t + P_W, D.pFl + (long long)P * 3, dt, gg, have_prev, mu, kc,
-                    wmask);
+        substep_one(G, substep_const(D, P, have_prev, dt, gg), t + P_X, t + P_U, t + P_W, D.pFl + (long long)P * 3, dt,
+                    mu, kc, wmask);
         const int n[3] = {G.nx, G.ny, G.nz};
         if (!sphere_supported(t + P_X, t[P_R], n, G.per)) atomicOr(D.err, ERR_PART);
     }
 }
 
-// All ns substeps in one block for small tables (np <= INT_BLOCK_MAX): centres,
-// velocities and pair forces in LDS, so that a substep's pair phase sees the
-// previous substep's update after a barrier; the same arithmetic as k_lub and
-// k_substep, which take one launch each per substep.
-constexpr int INT_BLOCK_MAX = 512;
+// half a cell or more in one step (see k_cov_flag_init)
+__device__ __forceinline__ bool moved_far(const Geom &G, const double *x, const double *xo) {
+    return fmax(fabs(min_img(x[0] - xo[0], G.nx, G.per[0])),
+                fmax(fabs(min_img(x[1] - xo[1], G.ny, G.per[1])), fabs(min_img(x[2] - xo[2], G.nz, G.per[2])))) >= 0.5;
+}
+// nodes of the two spheres may lie inside both (see k_cov_flag_init)
+__device__ __forceinline__ bool may_overlap(const Geom &G, const double *a, double Ra, const double *b, double Rb) {
+    const double d0 = min_img(a[0] - b[0], G.nx, G.per[0]), d1 = min_img(a[1] - b[1], G.ny, G.per[1]),
+                 d2 = min_img(a[2] - b[2], G.nz, G.per[2]);
+    const double r = Ra + Rb + 1.0;
+    return d0 * d0 + d1 * d1 + d2 * d2 < r * r;
+}
+
+// The particle update of a step in one block, for tables of up to INT_BLOCK_MAX spheres:
+// the ns substeps, the coverage flags and the mirror.  A thread keeps its NPT spheres' constants, centres and velocities in registers
+// and shares centres and velocities through LDS, where the pair forces are summed; the
+// first 1,024 pairs stay in registers too, so that a substep reads no global memory (with
+// a launch per half substep, 20 launches: 110 us for 1,400 spheres).  The same arithmetic as
+// k_lub and k_substep.
+constexpr int INT_BLOCK_MAX = 2048;
+template <int NPT>
 __global__ __launch_bounds__(1024) void k_integrate_block(Geom G, Dev D, int ns, double mu, double kc, int pcap,
                                                           double g0, double g1, double g2, int have_prev,
                                                           int wmask) {
-    __shared__ double sx[INT_BLOCK_MAX][3], su[INT_BLOCK_MAX][3], sf[INT_BLOCK_MAX][3];
+    __shared__ double sx[NPT * 1024][3], su[NPT * 1024][3], sf[NPT * 1024][3];
     const int np = D.np, npair = min(D.counters[C_NPAIRS], pcap);
-    for (int P = threadIdx.x; P < np; P += blockDim.x) {
-        const double *t = D.ptab + (long long)P * P_STRIDE;
-        for (int d = 0; d < 3; ++d) {
-            sx[P][d] = t[P_X + d];
-            su[P][d] = t[P_U + d];
-            sf[P][d] = D.pFl[3 * P + d];
-        }
-    }
-    __syncthreads();
+    const int tid = threadIdx.x;
     const double dt = 1.0 / ns, gg[3] = {g0, g1, g2};
+    SubstepConst c[NPT];
+    double w[NPT][3], xo[NPT][3];
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const int P = tid + 1024 * j;
+        if (P >= np) continue;
+        const double *t = D.ptab + (long long)P * P_STRIDE;
+        c[j] = substep_const(D, P, have_prev, dt, gg);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            xo[j][d] = sx[P][d] = t[P_X + d];
+            su[P][d] = t[P_U + d];
+            w[j][d] = t[P_W + d];
+            sf[P][d] = 0.0;
+        }
+    }
+    const bool hp = tid < npair;
+    const int2 pr = hp ? D.pairs[tid] : make_int2(0, 0);
+    const double Ra = hp ? D.ptab[(long long)pr.x * P_STRIDE + P_R] : 0.0, Rb = hp ? D.ptab[(long long)pr.y * P_STRIDE + P_R] : 0.0;
+    __syncthreads();
+    auto pair_add = [&](int a, int b, double R1, double R2) {
+        double f[3];
+        if (!pair_force(G, sx[a], su[a], R1, sx[b], su[b], R2, mu, kc, f)) return;
+        for (int d = 0; d < 3; ++d) {
+            atomicAdd(&sf[a][d], f[d]);
+            atomicAdd(&sf[b][d], -f[d]);
+        }
+    };
     for (int s = 0; s < ns; ++s) {
-        for (int k = threadIdx.x; k < npair; k += blockDim.x) {
-            const int a = D.pairs[k].x, b = D.pairs[k].y;
-            double f[3];
-            if (!pair_force(G, sx[a], su[a], D.ptab[(long long)a * P_STRIDE + P_R], sx[b], su[b],
-                            D.ptab[(long long)b * P_STRIDE + P_R], mu, kc, f))
-                continue;
-            for (int d = 0; d < 3; ++d) {
-                atomicAdd(&sf[a][d], f[d]);
-                atomicAdd(&sf[b][d], -f[d]);
-            }
+        if (hp) pair_add(pr.x, pr.y, Ra, Rb);
+        for (int k = tid + 1024; k < npair; k += 1024) {
+            const int2 q = D.pairs[k];
+            pair_add(q.x, q.y, D.ptab[(long long)q.x * P_STRIDE + P_R], D.ptab[(long long)q.y * P_STRIDE + P_R]);
         }
         __syncthreads();
-        for (int P = threadIdx.x; P < np; P += blockDim.x)
-            substep_one(G, D, P, sx[P], su[P], D.ptab + (long long)P * P_STRIDE + P_W, sf[P], dt, gg, have_prev, mu,
-                        kc, wmask);
+#pragma unroll
+        for (int j = 0; j < NPT; ++j) {
+            const int P = tid + 1024 * j;
+            if (P < np) substep_one(G, c[j], sx[P], su[P], w[j], sf[P], dt, mu, kc, wmask);
+        }
         __syncthreads();
     }
-    for (int P = threadIdx.x; P < np; P += blockDim.x) {
+    const int n[3] = {G.nx, G.ny, G.nz};
+#pragma unroll
+    for (int j = 0; j < NPT; ++j) {
+        const int P = tid + 1024 * j;
+        if (P >= np) continue;
         double *t = D.ptab + (long long)P * P_STRIDE;
         for (int d = 0; d < 3; ++d) {
+            t[P_XOLD + d] = xo[j][d];
             t[P_X + d] = sx[P][d];
             t[P_U + d] = su[P][d];
-            D.pFl[3 * P + d] = 0.0;
+            t[P_W + d] = w[j][d];
         }
-        const int n[3] = {G.nx, G.ny, G.nz};
-        if (!sphere_supported(t + P_X, t[P_R], n, G.per)) atomicOr(D.err, ERR_PART);
+        t[P_OVL] = 0.0;
+        if (moved_far(G, sx[P], xo[j])) atomicOr(D.counters + C_COVALL, 1);
+        if (!sphere_supported(sx[P], c[j].R, n, G.per)) atomicOr(D.err, ERR_PART);
+        mirror_store(D, P, sx[P], su[P], w[j]);
+    }
+    block_phase();
+    for (int k = tid; k < npair; k += 1024) {
+        const int2 q = k == tid ? pr : D.pairs[k];
+        double *ta = D.ptab + (long long)q.x * P_STRIDE, *tb = D.ptab + (long long)q.y * P_STRIDE;
+        if (may_overlap(G, sx[q.x], ta[P_R], sx[q.y], tb[P_R])) ta[P_OVL] = tb[P_OVL] = 1.0;
     }
 }
 
@@ -642,14 +811,11 @@ __global__ __launch_bounds__(1024) void k_integrate_block(Geom G, Dev D, int ns,
 __global__ void k_cov_flag_init(Geom G, Dev D) {
     GRID_STRIDE(P, D.np) {
         double *t = D.ptab + (long long)P * P_STRIDE;
-        const double m = fmax(fabs(min_img(t[P_X] - t[P_XOLD], G.nx, G.per[0])),
-                              fmax(fabs(min_img(t[P_X + 1] - t[P_XOLD + 1], G.ny, G.per[1])),
-                                   fabs(min_img(t[P_X + 2] - t[P_XOLD + 2], G.nz, G.per[2]))));
         t[P_OVL] = 0.0;
         // a sphere that moved half a cell or more in one step may meet partners that
         // the pair list (taken at the old positions) does not hold: then every
         // sphere takes the claim path this step
-        if (m >= 0.5) atomicOr(D.counters + C_COVALL, 1);
+        if (moved_far(G, t + P_X, t + P_XOLD)) atomicOr(D.counters + C_COVALL, 1);
     }
 }
 __device__ __forceinline__ bool cov_claims(const Dev &D, const double *t) {
@@ -660,30 +826,38 @@ __global__ void k_cov_flag_pairs(Geom G, Dev D, int pcap) {
     GRID_STRIDE(k, n) {
         const int a = D.pairs[k].x, b = D.pairs[k].y;
         double *ta = D.ptab + (long long)a * P_STRIDE, *tb = D.ptab + (long long)b * P_STRIDE;
-        const double d0 = min_img(ta[P_X] - tb[P_X], G.nx, G.per[0]), d1 = min_img(ta[P_X + 1] - tb[P_X + 1], G.ny, G.per[1]),
-                     d2 = min_img(ta[P_X + 2] - tb[P_X + 2], G.nz, G.per[2]);
-        const double r = ta[P_R] + tb[P_R] + 1.0;
-        if (d0 * d0 + d1 * d1 + d2 * d2 < r * r) {
-            ta[P_OVL] = 1.0;
-            tb[P_OVL] = 1.0;
-        }
+        if (may_overlap(G, ta + P_X, ta[P_R], tb + P_X, tb[P_R])) ta[P_OVL] = tb[P_OVL] = 1.0;
     }
 }
 
-// one wave per particle walks its bounding box; all = 0 limits the claims to the
-// spheres flagged above
-__global__ __launch_bounds__(256) void k_cov_claim(Geom G, Dev D, int all) {
-    int P = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (P >= D.np) return;
-    const double *t = D.ptab + (long long)P * P_STRIDE;
+// The threads that walk one sphere's nodes: 2^sh of them (a wave or more; blocks of
+// max(256, 2^sh)).  With a wave a sphere of R = 8 takes 77 rounds of dependent loads, so
+// small tables, which leave the device idle, give a sphere up to 1,024 threads (333
+// spheres: claims 49 -> 8 us, scan 84 -> 14 us); large ones fill it with a wave each.
+struct Team {
+    int P, lane, n;
+    __device__ __forceinline__ Team(int block, int sh) {
+        const int t = block * (int)blockDim.x + (int)threadIdx.x;
+        P = t >> sh;
+        n = 1 << sh;
+        lane = t & (n - 1);
+    }
+};
+
+// the node box of every sphere (all = 0: of those flagged above) is walked and its nodes
+// claimed
+__global__ void k_cov_claim(Geom G, Dev D, int all, int sh) {
+    const Team T(blockIdx.x, sh);
+    if (T.P >= D.np) return;
+    const double *t = D.ptab + (long long)T.P * P_STRIDE;
     if (!all && !cov_claims(D, t)) return;
     int lo[3], hi[3];
     sphere_box(G, t + P_X, t[P_R], lo, hi);
     int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
     int tot = ex * ey * ez;
-    for (int s = threadIdx.x & 63; s < tot; s += 64) {
+    for (int s = T.lane; s < tot; s += T.n) {
         int i = lo[0] + s % ex, j = lo[1] + (s / ex) % ey, k = lo[2] + s / (ex * ey);
-        if (inside(i, j, k, t + P_X, t[P_R])) atomicMin(D.claim + node_at(G, i, j, k), P);
+        if (inside(i, j, k, t + P_X, t[P_R])) atomicMin(D.claim + node_at(G, i, j, k), T.P);
     }
 }
 
@@ -698,20 +872,31 @@ __device__ __forceinline__ void push_event(const Dev &D, int *list, int which, i
     else atomicOr(D.err, ERR_CAP);
 }
 
-__device__ __forceinline__ void classify_node(const Dev &D, int c, int P) {
-    int cl = D.claim[c];
-    uint8_t f = D.flags[c];
-    bool owned = (f == SOL) && D.pid[c] == P;
-    if (owned && cl == CLAIM_NONE) push_event(D, D.lUnc, C_NUNCOVER, c, P);
-    if (cl == P && !owned) {
-        if (f == SOL) D.pid[c] = P;  // owner changes to the lower index
-        else push_event(D, D.lCov, C_NCOVER, c, P);
-    }
+// cell c becomes a node of sphere P; returns the mass it hands to the ledger.  Only the
+// sphere that takes a node (the lowest index inside, see k_cov_flag_init) calls this, and a
+// scan that meets the cell before or after decides the same: a fluid cell has no owner.
+template <int ST>
+__device__ __forceinline__ double cover_cell(const Geom &G, const Phys &Ph, const Dev &D, int c, int P, double *phi) {
+    const uint8_t f = D.flags[c];
+    double led = 0.0;
+    if (f == LIQ) led = cell_rho<ST>(G, D, Ph, D.fB, c);
+    else if (f == IFC) led = D.m[c];
+    else if (f == GAS) D.cv[c] = CV_GRM;  // left the gas: for the splitting test
+    // the relabelling after a merge sees gas and interface cells only
+    if ((f == GAS || f == IFC) && D.counters[C_MERGED]) D.bub[c] = (uint16_t)bubble_root(D, D.bub[c]);
+    D.flags[c] = SOL;
+    D.pid[c] = P;
+    phi[c] = 0.0;
+    return led;
 }
 
-// walks the union of the old and new bounding boxes
-__global__ __launch_bounds__(256) void k_cov_scan(Geom G, Dev D) {
-    int P = blockIdx.x * 4 + (threadIdx.x >> 6);
+// Walks the union of the old and new bounding boxes: nodes that the sphere covers become
+// its nodes at once, nodes that it leaves are marked (CV_UNC) and listed for k_unc.  The
+// ledger takes the covered mass summed per wave.
+template <int ST>
+__global__ void k_cov_scan(Geom G, Phys Ph, Dev D, double *phi, int sh) {
+    const Team T(blockIdx.x, sh);
+    const int P = T.P;
     if (P >= D.np) return;
     const double *t = D.ptab + (long long)P * P_STRIDE;
     // the old centre at its image nearest the new one: both boxes in one frame
@@ -725,6 +910,13 @@ __global__ __launch_bounds__(256) void k_cov_scan(Geom G, Dev D) {
         lo[a] = !inNew ? lo2[a] : !inOld ? lo[a] : min(lo[a], lo2[a]);
         hi[a] = !inNew ? hi2[a] : !inOld ? hi[a] : max(hi[a], hi2[a]);
     }
+    double led = 0.0;
+    auto events = [&](bool cov, bool unc, int c) {
+        wave_push2(cov, c, P, D.lCov, D.counters + C_NCOVER, D.capEv, D.err);
+        wave_push2(unc, c, P, D.lUnc, D.counters + C_NUNCOVER, D.capEv, D.err);
+        if (cov) led += cover_cell<ST>(G, Ph, D, c, P, phi);
+        if (unc) D.cv[c] = CV_UNC;
+    };
     if (cov_claims(D, t)) {
         // by cell index: along a periodic axis n consecutive nodes hold every cell once
         const int n[3] = {G.nx, G.ny, G.nz};
@@ -732,47 +924,50 @@ __global__ __launch_bounds__(256) void k_cov_scan(Geom G, Dev D) {
             if (G.per[a]) hi[a] = min(hi[a], lo[a] + n[a] - 1);
         const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
         const int tot = ex * ey * ez;
-        for (int s = threadIdx.x & 63; s < tot; s += 64) {
-            int i = lo[0] + s % ex, j = lo[1] + (s / ex) % ey, k = lo[2] + s / (ex * ey);
-            classify_node(D, node_at(G, i, j, k), P);
-        }
-        return;
-    }
-    const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1;
-    // a sphere alone (it moved less than half a cell): only nodes whose inside test
-    // changed between the old and new positions can change owner.  Walked as (x, y) columns: the in-plane part of
-    // both squared distances is formed once per column, in the order of inside(), and
-    // a column outside both circles is skipped (adding dz^2 cannot bring it inside);
-    // cov_column_ranges gives the candidates of the others, and every candidate
-    // still takes the exact test.
-    const double *xn = t + P_X;
-    const double R2 = __dmul_rn(t[P_R], t[P_R]);
-    for (int s = threadIdx.x & 63; s < ex * ey; s += 64) {
-        const int i = lo[0] + s % ex, j = lo[1] + s / ex;
-        const double a0 = i - xn[0], a1 = j - xn[1], b0 = i - xo[0], b1 = j - xo[1];
-        const double sn = __dadd_rn(__dmul_rn(a0, a0), __dmul_rn(a1, a1));
-        const double so = __dadd_rn(__dmul_rn(b0, b0), __dmul_rn(b1, b1));
-        if (sn > R2 && so > R2) continue;
-        int r[4];  // candidate ranges of k
-        cov_column_ranges(sn, so, R2, xn[2], xo[2], lo[2], hi[2], r);
-        const int r1lo = r[0], r2lo = r[2];
-        const int n1 = max(r[1] - r1lo + 1, 0), n2 = max(r[3] - r2lo + 1, 0);
-        for (int m = 0; m < n1 + n2; ++m) {
-            const int k = m < n1 ? r1lo + m : r2lo + (m - n1);
-            const double a2 = k - xn[2], b2 = k - xo[2];
-            const bool in_new = __dadd_rn(sn, __dmul_rn(a2, a2)) <= R2;
-            const bool in_old = __dadd_rn(so, __dmul_rn(b2, b2)) <= R2;
-            bool cov = false, unc = false;
+        for (int s = T.lane; s < tot; s += T.n) {
+            const int i = lo[0] + s % ex, j = lo[1] + (s / ex) % ey, k = lo[2] + s / (ex * ey);
             const int c = node_at(G, i, j, k);
-            if (in_new != in_old) {
+            const int cl = D.claim[c];
+            const uint8_t f = D.flags[c];
+            const bool owned = f == SOL && D.pid[c] == P;
+            const bool mine = cl == P && !owned;
+            if (mine && f == SOL) D.pid[c] = P;  // owner changes to the lower index
+            events(mine && f != SOL, owned && cl == CLAIM_NONE, c);
+        }
+    } else {
+        const int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1;
+        // a sphere alone (it moved less than half a cell): only nodes whose inside test
+        // changed between the old and new positions can change owner.  Walked as (x, y) columns: the in-plane part of
+        // both squared distances is formed once per column, in the order of inside(), and
+        // a column outside both circles is skipped (adding dz^2 cannot bring it inside);
+        // cov_column_ranges gives the candidates of the others, and every candidate
+        // still takes the exact test.
+        const double *xn = t + P_X;
+        const double R2 = __dmul_rn(t[P_R], t[P_R]);
+        for (int s = T.lane; s < ex * ey; s += T.n) {
+            const int i = lo[0] + s % ex, j = lo[1] + s / ex;
+            const double a0 = i - xn[0], a1 = j - xn[1], b0 = i - xo[0], b1 = j - xo[1];
+            const double sn = __dadd_rn(__dmul_rn(a0, a0), __dmul_rn(a1, a1));
+            const double so = __dadd_rn(__dmul_rn(b0, b0), __dmul_rn(b1, b1));
+            if (sn > R2 && so > R2) continue;
+            int r[4];  // candidate ranges of k
+            cov_column_ranges(sn, so, R2, xn[2], xo[2], lo[2], hi[2], r);
+            const int r1lo = r[0], r2lo = r[2];
+            const int n1 = max(r[1] - r1lo + 1, 0), n2 = max(r[3] - r2lo + 1, 0);
+            for (int m = 0; m < n1 + n2; ++m) {
+                const int k = m < n1 ? r1lo + m : r2lo + (m - n1);
+                const double a2 = k - xn[2], b2 = k - xo[2];
+                const bool in_new = __dadd_rn(sn, __dmul_rn(a2, a2)) <= R2;
+                const bool in_old = __dadd_rn(so, __dmul_rn(b2, b2)) <= R2;
+                if (in_new == in_old) continue;
+                const int c = node_at(G, i, j, k);
                 const uint8_t f = D.flags[c];
-                cov = in_new && f != SOL;
-                unc = !in_new && f == SOL && D.pid[c] == P;
+                events(in_new && f != SOL, !in_new && f == SOL && D.pid[c] == P, c);
             }
-            wave_push2(cov, c, P, D.lCov, D.counters + C_NCOVER, D.capEv, D.err);
-            wave_push2(unc, c, P, D.lUnc, D.counters + C_NUNCOVER, D.capEv, D.err);
         }
     }
+    led = wave_sum(led);
+    if (lane_id() == 0 && led != 0.0) unsafeAtomicAdd(D.ledger, led);
 }
 
 // full-box variant used when the table is replaced (no previous positions)
@@ -782,84 +977,76 @@ __global__ void k_cov_scan_dense(Geom G, Dev D) {
         int cl = D.claim[c];
         uint8_t f = D.flags[c];
         if (f == SOL) {
-            if (cl == CLAIM_NONE) push_event(D, D.lUnc, C_NUNCOVER, (int)c, D.pid[c]);
-            else D.pid[c] = cl;
+            if (cl == CLAIM_NONE) {
+                push_event(D, D.lUnc, C_NUNCOVER, (int)c, D.pid[c]);
+                D.cv[c] = CV_UNC;
+            } else {
+                D.pid[c] = cl;
+            }
         } else if (cl != CLAIM_NONE) {
             push_event(D, D.lCov, C_NCOVER, (int)c, cl);
         }
     }
 }
 
-// the ledger takes the covered mass summed per wave (one atomic per wave): every
-// wave of the block takes the same rounds, so the sums see whole waves
+// the covered nodes of a whole new table; the ledger takes the mass summed per wave (one
+// atomic per wave): every wave of the block takes the same rounds, so the sums see whole
+// waves
 template <int ST>
 __global__ void k_cov_apply(Geom G, Phys Ph, Dev D, double *phi) {
     const int n = event_len(D, C_NCOVER);
     for (int base = blockIdx.x * blockDim.x; base < n; base += gridDim.x * blockDim.x) {
         const int e = base + threadIdx.x;
         double led = 0.0;
-        if (e < n) {
-            const int c = D.lCov[2 * e], P = D.lCov[2 * e + 1];
-            const uint8_t f = D.flags[c];
-            if (f == LIQ) led = cell_rho<ST>(G, D, Ph, D.fB, c);
-            else if (f == IFC) led = D.m[c];
-            else if (f == GAS) D.cv[c] = CV_GRM;  // left the gas: for the splitting test
-            // the relabelling after a merge sees gas and interface cells only
-            if ((f == GAS || f == IFC) && D.counters[C_MERGED]) D.bub[c] = (uint16_t)bubble_root(D, D.bub[c]);
-            D.flags[c] = SOL;
-            D.pid[c] = P;
-            phi[c] = 0.0;
-        }
+        if (e < n) led = cover_cell<ST>(G, Ph, D, D.lCov[2 * e], D.lCov[2 * e + 1], phi);
         led = wave_sum(led);
         if (lane_id() == 0 && led != 0.0) unsafeAtomicAdd(D.ledger, led);
     }
 }
 
-// decision with the flags after covering (uncovered nodes are still solid)
+// Uncovered nodes (32 lanes each, lane q the neighbour along q): the decision with the cell
+// types after covering, every uncovered node still solid (its mark says so, whatever type
+// it shows by then), and the cell's new state.  The block that finishes last makes
+// interface cells of those that came to lie next to gas uncovered in this step (the
+// closure; only if there is any) and clears the marks.
 template <int ST>
-__global__ void k_unc_decide(Geom G, Phys Ph, Dev D) {
-    int n = event_len(D, C_NUNCOVER);
-    GRID_STRIDE(e, n) {
-        int c = D.lUnc[2 * e], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        int nli = 0, gfirst = -1;
+__device__ __forceinline__ void uncover(const Geom &G, const Phys &Ph, const Dev &D, double *phi, const Items &W) {
+    const int n = event_len(D, C_NUNCOVER);
+    ITEM_LOOP(W, e, n) {
+        const bool has = e < n;
+        const int c = has ? D.lUnc[2 * e] : 0;
+        const int nb = lane_nbr(G, c, W.q, has);
+        const uint8_t f = nb < 0 ? WALL : (D.cv[nb] & CV_UNC) ? SOL : D.flags[nb];
+        const bool li = f == LIQ || f == IFC;
+        const double r = li ? cell_rho<ST>(G, D, Ph, D.fB, nb) : 0.0;
+        const unsigned ml = W.any(li), mg = W.any(f == GAS);
+        const int bub = W.from(f == GAS ? (int)D.bub[nb] : 0, mg ? __ffs(mg) - 1 : 0);
+        // mean density of the neighbours, summed in direction order
         double rs = 0.0;
+#pragma unroll
         for (int q = 1; q < Q; ++q) {
-            int nb = nbr_idx(G, x, y, z, q, 1);
-            if (nb < 0) continue;
-            uint8_t f = D.flags[nb];
-            if (f == LIQ || f == IFC) {
-                rs += cell_rho<ST>(G, D, Ph, D.fB, nb);
-                ++nli;
-            } else if (f == GAS && gfirst < 0) {
-                gfirst = nb;
-            }
+            const double rq = W.from(r, q);
+            if ((ml >> q) & 1u) rs += rq;
         }
-        int type = nli > 0 ? (gfirst >= 0 ? IFC : LIQ) : (gfirst >= 0 ? GAS : LIQ);
-        int bub = gfirst >= 0 ? D.bub[gfirst] : 0;
-        D.uncDec[e] = type | (bub << 8);
-        D.uncRho[e] = nli > 0 ? rs / nli : 1.0;
-    }
-}
-
-template <int ST>
-__global__ void k_unc_apply(Geom G, Phys Ph, Dev D, double *phi) {
-    int n = event_len(D, C_NUNCOVER);
-    GRID_STRIDE(e, n) {
-        int c = D.lUnc[2 * e], P = D.lUnc[2 * e + 1], x, y, z;
-        cell_xyz(G, c, x, y, z);
-        int type = D.uncDec[e] & 0xff, bub = D.uncDec[e] >> 8;
-        double rb = D.uncRho[e];
+        if (!has || W.q != 0) continue;
+        const int nli = __popc(ml);
+        const int type = nli > 0 ? (mg ? IFC : LIQ) : (mg ? GAS : LIQ);
+        const double rb = nli > 0 ? rs / nli : 1.0;
+        D.uncDec[e] = type;
+        D.uncRho[e] = rb;
         D.pid[c] = -1;
         D.flags[c] = (uint8_t)type;
         if (type == GAS) {
             D.bub[c] = (uint16_t)bub;
             phi[c] = 0.0;
-            D.cv[c] = CV_GAD;  // new gas: for the splitting test
+            atomicAdd(D.counters + C_NUGAS, 1);
             continue;
         }
+        const int P = D.lUnc[2 * e + 1];
         float u0 = 0.f, u1 = 0.f, u2 = 0.f;
         if ((unsigned)P < (unsigned)D.np) {
+            int x, y, z;
+            cell_xyz(G, c, x, y, z);
             const double *t = D.ptab + (long long)P * P_STRIDE;
             double rx = min_img(x - t[P_X], G.nx, G.per[0]), ry = min_img(y - t[P_X + 1], G.ny, G.per[1]),
                    rz = min_img(z - t[P_X + 2], G.nz, G.per[2]);
@@ -880,35 +1067,46 @@ __global__ void k_unc_apply(Geom G, Phys Ph, Dev D, double *phi) {
     }
 }
 
-__global__ void k_unc_closure(Geom G, Dev D, double *phi) {
-    int n = event_len(D, C_NUNCOVER);
-    GRID_STRIDE(e, n) {
-        int c = D.lUnc[2 * e], x, y, z;
-        if ((D.uncDec[e] & 0xff) != LIQ) continue;
-        cell_xyz(G, c, x, y, z);
-        for (int q = 1; q < Q; ++q) {
-            int nb = nbr_idx(G, x, y, z, q, 1);
-            if (nb >= 0 && D.flags[nb] == GAS) {
-                D.flags[c] = IFC;
-                D.m[c] = D.uncRho[e];
-                phi[c] = 1.0;
-                D.bub[c] = D.bub[nb];
-                break;
-            }
-        }
+// an uncovered liquid cell next to gas becomes interface.  One block.
+__device__ __forceinline__ void uncover_closure(const Geom &G, const Dev &D, double *phi) {
+    const int n = event_len(D, C_NUNCOVER);
+    const Items W(0, 1);
+    ITEM_LOOP(W, e, n) {
+        const bool has = e < n && D.uncDec[e < n ? e : 0] == LIQ;
+        const int c = has ? D.lUnc[2 * e] : 0;
+        const int nb = lane_nbr(G, c, W.q, has);
+        const unsigned mg = W.any(nb >= 0 && D.flags[nb < 0 ? 0 : nb] == GAS);
+        if (!has || !mg || W.q != __ffs(mg) - 1) continue;
+        D.flags[c] = IFC;
+        D.m[c] = D.uncRho[e];
+        phi[c] = 1.0;
+        D.bub[c] = D.bub[nb];
     }
 }
 
-__global__ __launch_bounds__(256) void k_cov_reset(Geom G, Dev D) {
-    int P = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (P >= D.np) return;
-    const double *t = D.ptab + (long long)P * P_STRIDE;
+// the first unc_blocks blocks take the uncovered nodes, the others (threads by sphere as
+// in k_cov_claim) take back the claims, which the scan before was the last to read
+template <int ST>
+__global__ __launch_bounds__(1024) void k_unc(Geom G, Phys Ph, Dev D, double *phi, int unc_blocks, int sh) {
+    if ((int)blockIdx.x < unc_blocks) {
+        uncover<ST>(G, Ph, D, phi, Items(blockIdx.x, unc_blocks));
+        if (!last_block(D.counters + C_DONEU, unc_blocks)) return;
+        const int ng = __hip_atomic_load(D.counters + C_NUGAS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (ng > 0) uncover_closure(G, D, phi);
+        const int n = event_len(D, C_NUNCOVER);
+        // new gas stays marked for the splitting test
+        for (int e = threadIdx.x; e < n; e += blockDim.x) D.cv[D.lUnc[2 * e]] = D.uncDec[e] == GAS ? CV_GAD : 0;
+        return;
+    }
+    const Team T(blockIdx.x - unc_blocks, sh);
+    if (T.P >= D.np) return;
+    const double *t = D.ptab + (long long)T.P * P_STRIDE;
     if (!cov_claims(D, t)) return;
     int lo[3], hi[3];
     sphere_box(G, t + P_X, t[P_R], lo, hi);
     int ex = hi[0] - lo[0] + 1, ey = hi[1] - lo[1] + 1, ez = hi[2] - lo[2] + 1;
     int tot = ex * ey * ez;
-    for (int s = threadIdx.x & 63; s < tot; s += 64) {
+    for (int s = T.lane; s < tot; s += T.n) {
         int i = lo[0] + s % ex, j = lo[1] + (s / ex) % ey, k = lo[2] + s / (ex * ey);
         D.claim[node_at(G, i, j, k)] = CLAIM_NONE;
     }

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256) void k_bubbles(Geom G, Dev D, const double *ph
     __shared__ BubbleLds L;
     bubble_accum(G, D, phi, L, D.counters[C_MERGED] != 0);
     if (test) split_test(G, D, L.root, Items(blockIdx.x, gridDim.x));
-    if (last_block(D.counters + C_DONEB, gridDim.x)) bubble_finalize(D, init, open);
+    if (last_block<false>(D.counters + C_DONEB, gridDim.x)) bubble_finalize(D, init, open);
 }
 
 // ---- labelling: union-find over the gas cells -------------------------------------

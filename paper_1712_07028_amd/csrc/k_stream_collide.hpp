@@ -15,6 +15,8 @@
 // neighbouring tiles stays inside one L2.
 #pragma once
 
+#include <type_traits>
+
 #include "fsl_device.hpp"
 
 namespace fsl {
@@ -268,50 +270,72 @@ __device__ __forceinline__ bool collide_store(const Phys &Ph, const float (&fi)[
 
 // Specular reflection at free-slip faces: the link q of cell (x, y, z) whose source
 // lies beyond the faces of the axes marked o* arrives from the cell beside it along
-// the wall, with the crossed components of its direction reversed.  Gas there gives
-// the free-surface condition (Eq. fsk) with that cell's bubble; a particle node
-// gives plain bounce-back (fbb, the cell's own opposite population).
-__device__ __forceinline__ int mirror_q(int q, bool ox, bool oy, bool oz) {
-    const int ex = ox ? -cx(q) : cx(q), ey = oy ? -cy(q) : cy(q), ez = oz ? -cz(q) : cz(q);
-    int r = q;
-#pragma unroll
-    for (int p = 1; p < Q; ++p)
-        if (cx(p) == ex && cy(p) == ey && cz(p) == ez) r = p;
-    return r;
-}
-
-template <int ST>
-__device__ __noinline__ float slip_link(const Geom &G, const Phys &Ph, const Dev &D,
-                                        const uint8_t (&tile)[3][TY + 2][TX + 2], int lx, int ly, int x, int y,
-                                        int z, int c, int q, bool ox, bool oy, bool oz, float ut0, float ut1,
-                                        float ut2, float fbb) {
-    using SS = Store<ST>;
-    const int dx = ox ? 0 : cx(q), dy = oy ? 0 : cy(q), dz = oz ? 0 : cz(q);
-    const uint8_t sf = tile[1 - dz][ly + 1 - dy][lx + 1 - dx];
-    const int sp = wrapc(x - dx, G.nx) + G.nx * wrapc(y - dy, G.ny) + G.nx * G.ny * wrapc(z - dz, G.nz);
-    if (sf == LIQ || sf == IFC)
-        return SS::ld((const typename SS::T *)D.fA + mirror_q(q, ox, oy, oz) * G.S + (unsigned)sp, Ph.inv);
-    if (sf == GAS) {
-        const int bid = D.bub[sp];
-        const float rg = D.rhog[bid < D.maxB ? bid : 0] + (D.kappa ? Ph.s6 * D.kappa[c] : 0.f);
-        const float cu = cx(q) * ut0 + cy(q) * ut1 + cz(q) * ut2;
-        const float uu = ut0 * ut0 + ut1 * ut1 + ut2 * ut2;
-        return -fbb + 2.0f * wq(q) * ((rg - 1.0f) + rg * (4.5f * cu * cu - 1.5f * uu));
+// the wall, with the crossed components of its direction reversed: mirror_q(q, o) with
+// o = ox + 2 oy + 4 oz, from a table of eight 5-bit entries per direction.
+constexpr unsigned long long mirror_table(int q) {
+    unsigned long long t = 0;
+    for (int o = 0; o < 8; ++o) {
+        const int ex = o & 1 ? -cx(q) : cx(q), ey = o & 2 ? -cy(q) : cy(q), ez = o & 4 ? -cz(q) : cz(q);
+        for (int p = 0; p < Q; ++p)
+            if (cx(p) == ex && cy(p) == ey && cz(p) == ez) t |= (unsigned long long)p << (5 * o);
     }
-    return fbb;
+    return t;
+}
+template <int Q_> __device__ __forceinline__ int mirror_q(int o) {
+    constexpr unsigned long long t = mirror_table(Q_);
+    return (int)((t >> (5 * o)) & 31ull);
+}
+// a * b rounded on its own (never fused into a following addition)
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+// a population h bounced at a moving face plus its term a * b (Eq. bbrule).  The rounding is
+// the one each storage form has always had: the binary16 form rounds the product first
+// (one unit in FP32, but a changed rounding to 16 bits shows in the forces).
+template <int ST> __device__ __forceinline__ float face_add(float h, float a, float b) {
+    return ST == ST_F16 ? h + mul_rounded(a, b) : fmaf(a, b, h);
 }
 
-// One boundary cell of the fused step (a cell with an interface, gas or particle
-// next to it, or an interface cell).  INTERIOR: the tile and its halo lie inside
+// c_q . v for a direction known at compile time, without the products by zero
+__device__ __forceinline__ float dir_dot(int q, float v0, float v1, float v2) {
+    float s = 0.f;
+    bool any = false;
+    auto add = [&](int c, float v) {
+        if (c == 0) return;
+        s = !any ? (c > 0 ? v : -v) : c > 0 ? s + v : s - v;
+        any = true;
+    };
+    add(cx(q), v0);
+    add(cy(q), v1);
+    add(cz(q), v2);
+    return s;
+}
+// compile-time loop over the moving directions
+template <int Q_ = 1, typename F> __device__ __forceinline__ void for_dirs(F &&f) {
+    if constexpr (Q_ < Q) {
+        f(std::integral_constant<int, Q_>{});
+        for_dirs<Q_ + 1>(f);
+    }
+}
+
+// One boundary cell of the fused step: an interface cell, or a liquid cell with gas (MW: or
+// a wall) next to it.  INTERIOR: the tile and its halo lie inside
 // the box, so a source is the cell index minus a uniform offset (no wrap, no wall).
 // Lanes without a cell (inb false) stay in the wave with nothing to do, because the
 // wave-level sums below read every lane.  MW: some box face moves (its wall links
-// then take the moving-wall form of Eq. bbrule).
+// then take the moving-wall form of Eq. bbrule) or slips; wu: the faces' velocities.
+//
+// The cells are few (a surface, a bubble, wall layers), so the time is the latency of the
+// chain of loads: everything a link may need (the cell's own populations, the pulled
+// ones, bubble and particle ids of the sources) is loaded in one batch with selected
+// addresses, then the tables by those ids.  With the loads inside the branches of each link
+// the chain was up to 20 deep (32^3 pool: 24.5 us a launch; free-slip 40 x 40 x 100 column: 73 us).
 template <int ST, bool INTERIOR, bool MW>
 __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev &D,
                                         const uint8_t (&tile)[3][TY + 2][TX + 2],
-                                        const double (&ph)[3][TY + 2][TX + 2], int lx, int ly, int x, int y,
-                                        int z, bool inb) {
+                                        const double (&ph)[3][TY + 2][TX + 2], const float *wu, int lx, int ly, int x,
+                                        int y, int z, bool inb) {
     using SS = Store<ST>;
     using T = typename SS::T;
     const int nx = G.nx, ny = G.ny, nz = G.nz, nxy = nx * ny;
@@ -335,6 +359,7 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
     bool isF = false, isE = false;
 
     if (fl == LIQ || fl == IFC) {
+        // the links by source: gas (gm), particle node (sm), beyond a wall (wm)
         uint32_t gm = 0, sm = 0, wm = 0;
 #pragma unroll
         for (int q = 1; q < Q; ++q) {
@@ -343,41 +368,56 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
             sm |= (uint32_t)(sf == SOL) << q;
             if (!INTERIOR) wm |= (uint32_t)(sf == WALL) << q;
         }
-        const uint32_t miss = gm | sm | wm;
-        bool needOwn = (fl == IFC) || gm || (MW && wm);
-        float fi[Q];
-        // density and velocity of this cell at t from its own populations, which are
-        // then reloaded where a rule needs one (a compiler barrier keeps the two
-        // groups of loads apart, so that both arrays are never live together).  A
-        // cell whose only missing links lead to particles needs the density alone
-        // (Eq. bbrule): the previous launch stored it when it took this path too.
-        float rho_t = 1.0f, ut0 = 0.f, ut1 = 0.f, ut2 = 0.f;
-        if (!needOwn && sm) {
-            bool have = false;
-            if (D.rhow != nullptr && D.st_prev >= 0) {
-                const unsigned e = D.rhow[c];
-                have = rhow_valid(e, D.st_prev);
-                rho_t = __uint_as_float(e);
+        const uint32_t gas_in = gm;  // gas sources inside the box: no liquid cell may have one
+        // the cell's own populations (density and velocity at t, bounced links)
+        float fa[Q], fi[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) fa[q] = SS::ld(A + q * S + (unsigned)c, inv);
+        const float kap = D.kappa ? D.kappa[c] : 0.f;
+        // pulls: from the source, or across free-slip faces from the mirrored population
+        // of the cell beside (its type decides: rm, then links of liquid and interface
+        // cells; gas joins gm, a particle node is plain bounce-back); links without a
+        // pulled population read their own word
+        uint32_t rm = 0;    // reflected links
+        uint32_t slip = 0;  // links that cross free-slip faces only
+        int bq[Q];          // bubble of a gas link's cell
+        if (MW && !INTERIOR && wm && (Ph.slip[0] | Ph.slip[1] | Ph.slip[2])) {
+            for_dirs([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                if (!((wm >> q) & 1u)) return;
+                const int sx = x - cx(q), sy = y - cy(q), sz = z - cz(q);
+                const bool ox = !G.per[0] && (sx < 0 || sx >= nx);
+                const bool oy = !G.per[1] && (sy < 0 || sy >= ny);
+                const bool oz = !G.per[2] && (sz < 0 || sz >= nz);
+                if ((ox && !Ph.slip[0]) || (oy && !Ph.slip[1]) || (oz && !Ph.slip[2])) return;
+                slip |= 1u << q;
+                const uint8_t sf = tile[oz ? 1 : 1 - cz(q)][ly + 1 - (oy ? 0 : cy(q))][lx + 1 - (ox ? 0 : cx(q))];
+                if (sf == LIQ || sf == IFC) rm |= 1u << q;
+                else if (sf == GAS) gm |= 1u << q;
+            });
+        }
+        fi[0] = fa[0];
+        for_dirs([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const bool pull = !(((gm | sm | wm) >> q) & 1u);
+            int s = src(q);
+            int pl = q;
+            if (MW && !INTERIOR) {
+                if ((slip >> q) & 1u) {
+                    const int sx = x - cx(q), sy = y - cy(q), sz = z - cz(q);
+                    const bool ox = !G.per[0] && (sx < 0 || sx >= nx);
+                    const bool oy = !G.per[1] && (sy < 0 || sy >= ny);
+                    const bool oz = !G.per[2] && (sz < 0 || sz >= nz);
+                    s = (ox ? x : wrapc(sx, nx)) + nx * (oy ? y : wrapc(sy, ny)) + nxy * (oz ? z : wrapc(sz, nz));
+                    pl = mirror_q<q>((int)ox + 2 * (int)oy + 4 * (int)oz);
+                }
+                const bool ld = pull || ((rm >> q) & 1u);
+                fi[q] = SS::ld(A + (long long)(ld ? pl : q) * S + (unsigned)(ld ? s : c), inv);
+            } else {
+                fi[q] = SS::ld(A + q * S + (unsigned)(pull ? s : c), inv);
             }
-            needOwn = !have;
-        }
-        if (needOwn) {
-            float fa[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) fa[q] = SS::ld(A + q * S + (unsigned)c, inv);
-            const Moments Mt = cell_moments(fa);
-            rho_t = 1.0f + (float)Mt.drho;
-            const float ir = __builtin_amdgcn_rcpf(rho_t);
-            ut0 = Mt.j0 * ir - 0.5f * Ph.g[0];
-            ut1 = Mt.j1 * ir - 0.5f * Ph.g[1];
-            ut2 = Mt.j2 * ir - 0.5f * Ph.g[2];
-        }
-        __asm__ volatile("" ::: "memory");
-        auto fo = [&](int q) { return SS::ld(A + q * S + (unsigned)c, inv); };
-        fi[0] = fo(0);
-#pragma unroll
-        for (int q = 1; q < Q; ++q)
-            if (!((miss >> q) & 1u)) fi[q] = SS::ld(A + q * S + (unsigned)src(q), inv);
+            bq[q] = (int)D.bub[((gm >> q) & 1u) ? s : c];
+        });
         // particle ids of the solid sources: one batch of loads, reduced to the first
         // id P0 and the mask of links whose particle is P0
         int P0 = -1;
@@ -385,14 +425,35 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
         if (sm) {
             int pq[Q];
 #pragma unroll
-            for (int q = 1; q < Q; ++q) pq[q] = ((sm >> q) & 1u) ? D.pid[src(q)] : -1;
+            for (int q = 1; q < Q; ++q) pq[q] = D.pid[((sm >> q) & 1u) ? src(q) : c];
 #pragma unroll
             for (int q = Q - 1; q >= 1; --q)
                 if ((sm >> q) & 1u) P0 = pq[q];
 #pragma unroll
             for (int q = 1; q < Q; ++q) same |= (uint32_t)(((sm >> q) & 1u) && pq[q] == P0) << q;
         }
-        if (miss) {
+        // the gas density of the first gas link's bubble; links of other bubbles (rare)
+        // look theirs up
+        int b0 = 0;
+        uint32_t sameb = 0;
+        float rg0 = 1.0f;
+        if (gm) {
+#pragma unroll
+            for (int q = Q - 1; q >= 1; --q)
+                if ((gm >> q) & 1u) b0 = bq[q];
+#pragma unroll
+            for (int q = 1; q < Q; ++q) sameb |= (uint32_t)(bq[q] == b0) << q;
+            rg0 = D.rhog[b0 < D.maxB ? b0 : 0];
+        }
+        const Moments Mt = cell_moments(fa);
+        const float rho_t = 1.0f + (float)Mt.drho;
+        const float ir = __builtin_amdgcn_rcpf(rho_t);
+        const float ut0 = fmaf(Mt.j0, ir, -(0.5f * Ph.g[0]));
+        const float ut1 = fmaf(Mt.j1, ir, -(0.5f * Ph.g[1]));
+        const float ut2 = fmaf(Mt.j2, ir, -(0.5f * Ph.g[2]));
+        const float uu15 = 1.5f * fmaf(ut2, ut2, fmaf(ut1, ut1, ut0 * ut0));
+        const float jump = D.kappa ? mul_rounded(Ph.s6, kap) : 0.f;
+        {
             // rigid-body velocity of the lane's particle at the node: c_q . u_w at
             // the link midpoint x - c_q/2 equals c_q . (u_P + omega x (x - x_P))
             // because c_q . (omega x c_q) = 0, so one velocity serves all links
@@ -404,44 +465,47 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
                 const float rx = mirror_arm(x, m.ax, m.fx, G.nx, G.per[0]);
                 const float ry = mirror_arm(y, m.ay, m.fy, G.ny, G.per[1]);
                 const float rz = mirror_arm(z, m.az, m.fz, G.nz, G.per[2]);
-                un0 = m.ux + (m.wy * rz - m.wz * ry);
-                un1 = m.uy + (m.wz * rx - m.wx * rz);
-                un2 = m.uz + (m.wx * ry - m.wy * rx);
+                un0 = m.ux + fmaf(m.wy, rz, -(m.wz * ry));
+                un1 = m.uy + fmaf(m.wz, rx, -(m.wx * rz));
+                un2 = m.uz + fmaf(m.wx, ry, -(m.wy * rx));
             };
             if ((unsigned)P0 < (unsigned)D.np) {
                 acc.P = P0;
                 node_velocity(P0);
             }
+            if (fl == LIQ && gas_in) atomicOr(D.err, ERR_LG);
 #pragma unroll
             for (int q = 1; q < Q; ++q) {
                 const int o = opp(q);
-                if (!INTERIOR && ((wm >> q) & 1u)) {
+                if ((gm >> q) & 1u) {
+                    // Laplace jump p_w = p_g + 2 sigma kappa in density form
+                    const float rgb = ((sameb >> q) & 1u) ? rg0 : D.rhog[bq[q] < D.maxB ? bq[q] : 0];
+                    const float rg = rgb + jump;
+                    const float cu = dir_dot(q, ut0, ut1, ut2);
+                    // Eq. (fsk) in shifted form: -h*_qbar + 2 (e+_q(rho_g, u) - w_q)
+                    fi[q] = fmaf(fmaf(fmaf(cu, 4.5f * cu, -uu15), rg, rg - 1.0f), 2.0f * wq(q), -fa[o]);
+                } else if (!INTERIOR && ((wm >> q) & 1u)) {
                     // half-way bounce-back; a moving face adds 6 w_q rho_t (c_q . u_w)
-                    // (Eq. bbrule), the face being the first crossed no-slip face.  A
-                    // link that crosses free-slip faces only reflects specularly.
-                    float add = 0.f;
+                    // (Eq. bbrule), the face being the first crossed no-slip face
+                    if ((rm >> q) & 1u) continue;  // reflected: pulled above
+                    fi[q] = fa[o];
                     if (MW) {
-                        const int sx = x - cx(q), sy = y - cy(q), sz = z - cz(q);
-                        const bool ox = !G.per[0] && (sx < 0 || sx >= nx);
-                        const bool oy = !G.per[1] && (sy < 0 || sy >= ny);
-                        const bool oz = !G.per[2] && (sz < 0 || sz >= nz);
-                        if ((!ox || Ph.slip[0]) && (!oy || Ph.slip[1]) && (!oz || Ph.slip[2])) {
-                            fi[q] = slip_link<ST>(G, Ph, D, tile, lx, ly, x, y, z, c, q, ox, oy, oz, ut0, ut1, ut2,
-                                                  fo(o));
-                            continue;
+                        if (!((slip >> q) & 1u)) {
+                            const int sx = x - cx(q), sy = y - cy(q), sz = z - cz(q);
+                            const bool ox = !G.per[0] && (sx < 0 || sx >= nx);
+                            const bool oy = !G.per[1] && (sy < 0 || sy >= ny);
+                            int a = 2, sd = sz < 0 ? 0 : 1;
+                            if (ox && !Ph.slip[0]) { a = 0; sd = sx < 0 ? 0 : 1; }
+                            else if (oy && !Ph.slip[1]) { a = 1; sd = sy < 0 ? 0 : 1; }
+                            const float *uw = wu + (a * 2 + sd) * 3;
+                            fi[q] = face_add<ST>(fa[o], 6.0f * wq(q) * rho_t, dir_dot(q, uw[0], uw[1], uw[2]));
                         }
-                        int a = 2, sd = sz < 0 ? 0 : 1;
-                        if (ox && !Ph.slip[0]) { a = 0; sd = sx < 0 ? 0 : 1; }
-                        else if (oy && !Ph.slip[1]) { a = 1; sd = sy < 0 ? 0 : 1; }
-                        const float *uw = D.wallu + (a * 2 + sd) * 3;
-                        add = 6.0f * wq(q) * rho_t * (cx(q) * uw[0] + cy(q) * uw[1] + cz(q) * uw[2]);
                     }
-                    fi[q] = fo(o) + add;
                 } else if ((sm >> q) & 1u) {
                     if (!((same >> q) & 1u) || acc.P != P0) {  // another particle (rare)
                         const int P = D.pid[src(q)];
                         if ((unsigned)P >= (unsigned)D.np) {  // inconsistent state: plain wall
-                            fi[q] = fo(o);
+                            fi[q] = fa[o];
                             atomicOr(D.err, ERR_LG);
                             continue;
                         }
@@ -452,10 +516,10 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
                             node_velocity(P);
                         }
                     }
-                    const float cu = cx(q) * un0 + cy(q) * un1 + cz(q) * un2;
-                    const float fin = fo(o) + 6.0f * wq(q) * rho_t * cu;  // Eq. (bbrule)
+                    const float cu = dir_dot(q, un0, un1, un2);
+                    const float fin = fmaf(6.0f * wq(q) * rho_t, cu, fa[o]);  // Eq. (bbrule)
                     fi[q] = fin;
-                    const float s2 = fo(o) + fin;
+                    const float s2 = fa[o] + fin;
                     acc.fs[0] -= cx(q) * s2;
                     acc.fs[1] -= cy(q) * s2;
                     acc.fs[2] -= cz(q) * s2;
@@ -466,16 +530,7 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
                     }
                     // the ledger pays the moving-wall mass of liquid cells only: an
                     // interface cell's mass is m, which the link does not change
-                    if (fl == LIQ) acc.dm += fin - fo(o);
-                } else if ((gm >> q) & 1u) {
-                    if (fl == LIQ) atomicOr(D.err, ERR_LG);
-                    const int bid = D.bub[src(q)];
-                    // Laplace jump p_w = p_g + 2 sigma kappa in density form
-                    const float rg = D.rhog[bid < D.maxB ? bid : 0] + (D.kappa ? Ph.s6 * D.kappa[c] : 0.f);
-                    const float cu = cx(q) * ut0 + cy(q) * ut1 + cz(q) * ut2;
-                    const float uu = ut0 * ut0 + ut1 * ut1 + ut2 * ut2;
-                    // Eq. (fsk) in shifted form: -h*_qbar + 2 (e+_q(rho_g, u) - w_q)
-                    fi[q] = -fo(o) + 2.0f * wq(q) * ((rg - 1.0f) + rg * (4.5f * cu * cu - 1.5f * uu));
+                    if (fl == LIQ) acc.dm += fin - fa[o];
                 }
             }
         }
@@ -490,7 +545,7 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
             for (int q = 1; q < Q; ++q) {
                 const uint8_t nf = tile[1 + cz(q)][ly + 1 + cy(q)][lx + 1 + cx(q)];
                 if (nf == LIQ || nf == IFC) {
-                    double d = (double)fi[opp(q)] - (double)fo(q);
+                    double d = (double)fi[opp(q)] - (double)fa[q];
                     if (nf == IFC) d *= 0.5 * (ph[1 + cz(q)][ly + 1 + cy(q)][lx + 1 + cx(q)] + phx);
                     dm += d;
                 } else if (MW && !INTERIOR && nf == WALL) {
@@ -504,7 +559,7 @@ __device__ __forceinline__ void sc_cell(const Geom &G, const Phys &Ph, const Dev
                         const int dx = ox ? 0 : cx(q), dy = oy ? 0 : cy(q), dz = oz ? 0 : cz(q);
                         const uint8_t pf = tile[1 + dz][ly + 1 + dy][lx + 1 + dx];
                         if (pf == LIQ || pf == IFC) {
-                            double d = (double)fi[opp(q)] - (double)fo(q);
+                            double d = (double)fi[opp(q)] - (double)fa[q];
                             if (pf == IFC) d *= 0.5 * (ph[1 + dz][ly + 1 + dy][lx + 1 + dx] + phx);
                             dm += d;
                         }
@@ -737,27 +792,6 @@ __device__ __forceinline__ void macc_atomic(const Dev &D, MarchLds &L, int t) {
     }
 }
 
-// FP64 wave sum with DPP on the two 32-bit halves (same pattern as wave_total_f)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add_d(double v) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xF, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xF, false);
-    return v + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ double wave_total_d(double v) {
-    v = dpp_add_d<0xB1, 0xF>(v);
-    v = dpp_add_d<0x4E, 0xF>(v);
-    v = dpp_add_d<0x141, 0xF>(v);
-    v = dpp_add_d<0x140, 0xF>(v);
-    v = dpp_add_d<0x142, 0xA>(v);
-    v = dpp_add_d<0x143, 0xC>(v);
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, 63);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 63);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 // the lanes' remaining sums at the end of a march, segmented by particle: one FP64
 // atomic instruction per (wave, particle).  Every lane of the wave must be active.
 __device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L) {
@@ -771,10 +805,10 @@ __device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L)
         const int leader = __ffsll((long long)act) - 1;
         const int k0 = __builtin_amdgcn_readlane(key, leader);
         const bool mine = key == k0;
-        const double s0 = wave_total_d(mine ? a0 : 0.0), s1 = wave_total_d(mine ? a1 : 0.0),
-                     s2 = wave_total_d(mine ? a2 : 0.0), s3 = wave_total_d(mine ? a3 : 0.0),
-                     s4 = wave_total_d(mine ? a4 : 0.0), s5 = wave_total_d(mine ? a5 : 0.0),
-                     s6 = wave_total_d(mine ? a6 : 0.0);
+        const double s0 = wave_sum(mine ? a0 : 0.0), s1 = wave_sum(mine ? a1 : 0.0),
+                     s2 = wave_sum(mine ? a2 : 0.0), s3 = wave_sum(mine ? a3 : 0.0),
+                     s4 = wave_sum(mine ? a4 : 0.0), s5 = wave_sum(mine ? a5 : 0.0),
+                     s6 = wave_sum(mine ? a6 : 0.0);
         const int ln = (int)lane_id();
         if (ln < 7) {
             const double v = ln == 0 ? s0 : ln == 1 ? s1 : ln == 2 ? s2 : ln == 3 ? s3 : ln == 4 ? s4 : ln == 5 ? s5 : s6;
@@ -1166,17 +1200,23 @@ __device__ __forceinline__ void stage_phi_tile(const Geom &G, const double *phi,
 // slipping face, for the tiles (64 x 4 of one plane) that k_stream_collide listed.
 // A tile's cells are compacted and handled by as few waves as they fill (sc_cell).
 template <int ST, bool MW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MW ? 1 : 5))) void k_general(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_general(
     Geom G, Phys Ph, Dev D, int tilesX, int tilesY, const int *gen, const int *ngen) {
     __shared__ uint8_t tile[3][TY + 2][TX + 2];
     __shared__ double ph[3][TY + 2][TX + 2];
     __shared__ unsigned long long b3[3 * (TY + 2)], b1[3 * (TY + 2)];
     __shared__ uint8_t list[TX * TY];
     __shared__ int wcount[4];
+    __shared__ float wu[18];
+    // the block's first tile is read beside the number of tiles (the list holds a word for
+    // every tile of the box, the launch no more blocks than that)
+    const int first = gen[blockIdx.x];
     const int n = *ngen;
+    if ((int)blockIdx.x >= n) return;
+    if (MW && threadIdx.x < 18) wu[threadIdx.x] = D.wallu[threadIdx.x];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
-        const int t = gen[i];
+        const int t = i == (int)blockIdx.x ? first : gen[i];
         const int x0 = (t % tilesX) * TX;
         const int rest = t / tilesX;
         const int y0 = (rest % tilesY) * TY;
@@ -1212,8 +1252,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MW ? 1 : 5)
             const bool has = (int)threadIdx.x < total;
             const int e = has ? list[threadIdx.x] : 0;
             const int ex = e & (TX - 1), ey = e >> 6;
-            if (interior) sc_cell<ST, true, MW>(G, Ph, D, tile, ph, ex, ey, x0 + ex, y0 + ey, z, has);
-            else sc_cell<ST, false, MW>(G, Ph, D, tile, ph, ex, ey, x0 + ex, y0 + ey, z, has);
+            if (interior) sc_cell<ST, true, MW>(G, Ph, D, tile, ph, wu, ex, ey, x0 + ex, y0 + ey, z, has);
+            else sc_cell<ST, false, MW>(G, Ph, D, tile, ph, wu, ex, ey, x0 + ex, y0 + ey, z, has);
         }
         __syncthreads();
     }
