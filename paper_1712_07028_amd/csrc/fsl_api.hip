@@ -187,6 +187,7 @@ struct fsl_ctx {
     FaceSet FS;  // the no-slip face layers for the face forces
     int ncell;
     int tilesX, tilesY, nTiles;
+    int cus;  // compute units of the device
     int profiling;
     int have_prev;  // a previous step's hydrodynamic force exists (particle update)
     int stamp;      // stamp of the next stream-collide launch (>= 1)
@@ -297,7 +298,7 @@ void set_phys(fsl_ctx *c) {
     c->Ph.inv = 1.0f / c->Ph.scale;
     // FSL_WIDE_OFFSETS=1 takes the 64-bit form on any box (a test of that form)
     const char *wide = getenv("FSL_WIDE_OFFSETS");
-    c->Ph.wide = c->G.S >= (1ll << 30) || (wide && wide[0] == '1');
+    c->Ph.wide = c->G.S * 4 * esize(f.storage) > (1ll << 32) || (wide && wide[0] == '1');
 }
 
 // one lattice update of every cell: the marching pass over the liquid cells, then the
@@ -306,11 +307,19 @@ void set_phys(fsl_ctx *c) {
 template <int ST, bool MW, bool PER>
 void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
     int *glist = (int *)(c->xs + c->L.glist), *ngen = Dv.counters + C_NGEN;
-    // planes per block: NZC, fewer on small boxes so that the launch still fills the
-    // device (at least 2,048 blocks)
+    // planes per block: the device holds four blocks per compute unit at once, a block costs
+    // its planes and about two more for staging the first three; the number of planes (at
+    // most NZC) with the fewest plane times over the rounds of blocks
     const long long cols = (long long)c->tilesX * c->tilesY;
-    int nzc = NZC;
-    while (nzc > 2 && cols * ((c->G.nz + nzc - 1) / nzc) < 2048) nzc /= 2;
+    int nzc = 1;
+    long long best = 0;
+    for (int k = 1; k <= NZC; ++k) {
+        const long long blocks = cols * ((c->G.nz + k - 1) / k), t = (blocks + 4 * c->cus - 1) / (4 * c->cus) * (k + 2);
+        if (best == 0 || t <= best) {
+            best = t;
+            nzc = k;
+        }
+    }
     const int nChunks = (c->G.nz + nzc - 1) / nzc;
     hipLaunchKernelGGL((k_stream_collide<ST, MW, PER>), dim3(c->tilesX * c->tilesY * nChunks), dim3(256), 0, c->st,
                        c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen);
@@ -899,6 +908,13 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
     c->tilesX = (G.nx + TX - 1) / TX;
     c->tilesY = (G.ny + TY - 1) / TY;
     c->nTiles = c->tilesX * c->tilesY * G.nz;
+    {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+            cus = 256;
+        c->cus = cus;
+    }
     c->profiling = 0;
     for (int k = 0; k < NPROF; ++k) { c->prof_ms[k] = 0; c->prof_n[k] = 0; }
     adjoint_bind(c->adj, w + L.win, L.winBytes, cfg->window_steps, cfg->window_every, L.S, L.maxP, L.nTiles);

@@ -187,6 +187,38 @@ __device__ __forceinline__ void acc_reduce_wave(const Geom &G, const Dev &D, con
     }
 }
 
+// the element at a byte offset of 32 bits from a uniform base (one instruction's addressing)
+template <typename T> __device__ __forceinline__ T *at_byte(T *base, unsigned off) { return (T *)((char *)base + off); }
+template <typename T> __device__ __forceinline__ const T *at_byte(const T *base, unsigned off) {
+    return (const T *)((const char *)base + off);
+}
+
+// a * b rounded on its own (never fused into a following addition)
+__device__ __forceinline__ float mul_rounded(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+// a population h bounced at a moving face plus its term a * b (Eq. bbrule).  The rounding is
+// the one each storage form has always had: the binary16 form rounds the product first
+// (one unit in FP32, but a changed rounding to 16 bits shows in the forces).
+template <int ST> __device__ __forceinline__ float face_add(float h, float a, float b) {
+    return ST == ST_F16 ? h + mul_rounded(a, b) : fmaf(a, b, h);
+}
+
+// c_q . v for a direction known at compile time, without the products by zero
+__device__ __forceinline__ float dir_dot(int q, float v0, float v1, float v2) {
+    float s = 0.f;
+    bool any = false;
+    auto add = [&](int c, float v) {
+        if (c == 0) return;
+        s = !any ? (c > 0 ? v : -v) : c > 0 ? s + v : s - v;
+        any = true;
+    };
+    add(cx(q), v0);
+    add(cy(q), v1);
+    add(cz(q), v2);
+    return s;
+}
 // ---- moments and collision of one cell ------------------------------------------
 // Populations come in shifted (h = f - w).  The D3Q19 opposite pairs (q, opp(q)) with
 // q < opp(q) are (1,2) (3,4) (5,6) (7,10) (8,9) (11,14) (12,13) (15,18) (16,17); the
@@ -225,14 +257,17 @@ __device__ __forceinline__ bool collide_store(const Phys &Ph, const float (&fi)[
     const float drho = (float)M.drho;
     const float rho = 1.0f + drho;
     const float irho = __builtin_amdgcn_rcpf(rho);
-    const float u0 = M.j0 * irho + 0.5f * Ph.g[0];
-    const float u1 = M.j1 * irho + 0.5f * Ph.g[1];
-    const float u2 = M.j2 * irho + 0.5f * Ph.g[2];
-    const float F0 = rho * Ph.g[0], F1 = rho * Ph.g[1], F2 = rho * Ph.g[2];
-    const float uu = u0 * u0 + u1 * u1 + u2 * u2;
-    const float uF = u0 * F0 + u1 * F1 + u2 * F2;
+    // The fused multiply-adds are written out, so that every kernel rounds alike however
+    // the compiler would contract the sums, and the zero components of c_q cost nothing.
+    const float u0 = fmaf(M.j0, irho, 0.5f * Ph.g[0]);
+    const float u1 = fmaf(M.j1, irho, 0.5f * Ph.g[1]);
+    const float u2 = fmaf(M.j2, irho, 0.5f * Ph.g[2]);
+    const float F0 = mul_rounded(rho, Ph.g[0]), F1 = mul_rounded(rho, Ph.g[1]), F2 = mul_rounded(rho, Ph.g[2]);
+    const float uu15 = -1.5f * fmaf(u2, u2, fmaf(u0, u0, mul_rounded(u1, u1)));
+    const float uF3 = mul_rounded(3.0f, fmaf(u2, F2, fmaf(u0, F0, mul_rounded(u1, F1))));
     const float lp = Ph.lp, lm = Ph.lm;
-    const float ap = 1.0f + 0.5f * lp, am = 1.0f + 0.5f * lm;
+    const float ap = fmaf(0.5f, lp, 1.0f), am = fmaf(0.5f, lm, 1.0f);
+    const float r3a = mul_rounded(3.0f, mul_rounded(wq(1), rho)), r3d = mul_rounded(3.0f, mul_rounded(wq(7), rho));
     double sp[9];
     T out[Q];
     int k = 0;
@@ -241,16 +276,20 @@ __device__ __forceinline__ bool collide_store(const Phys &Ph, const float (&fi)[
         if (opp(q) < q) continue;
         const int o = opp(q);
         const float w = wq(q);
-        const float cu = cx(q) * u0 + cy(q) * u1 + cz(q) * u2;
-        const float cF = cx(q) * F0 + cy(q) * F1 + cz(q) * F2;
-        const float ep = w * (drho + rho * (4.5f * cu * cu - 1.5f * uu));
-        const float em = w * rho * 3.0f * cu;
-        const float Fp = w * (-3.0f * uF + 9.0f * cu * cF);
-        const float Fm = w * 3.0f * cF;
-        const float hp = 0.5f * (fi[q] + fi[o]) - ep;
-        const float hm = 0.5f * (fi[q] - fi[o]) - em;
-        const float even = lp * hp + ap * Fp, odd = lm * hm + am * Fm;
-        const T vq = SS::enc(fi[q] + even + odd, sc), vo = SS::enc(fi[o] + even - odd, sc);
+        const float cu = dir_dot(q, u0, u1, u2);
+        // c_q . F, the last component's product fused
+        const float cF = cz(q) && (cx(q) || cy(q)) ? fmaf(cz(q) * Ph.g[2], rho, cx(q) ? cx(q) * F0 : cy(q) * F1)
+                         : cx(q) && cy(q)          ? fmaf(cy(q) * Ph.g[1], rho, cx(q) * F0)
+                                                   : dir_dot(q, F0, F1, F2);
+        // even and odd parts of the equilibrium and of the forcing (Eq. LBE2)
+        const float ep = mul_rounded(w, fmaf(rho, fmaf(cu, mul_rounded(4.5f, cu), uu15), drho));
+        const float em = mul_rounded(q <= 6 ? r3a : r3d, cu);
+        const float Fp = mul_rounded(w, fmaf(cF, mul_rounded(9.0f, cu), -uF3));
+        const float Fm = mul_rounded(w * 3.0f, cF);
+        const float hp = fmaf(0.5f, fi[q] + fi[o], -ep);
+        const float hm = fmaf(0.5f, fi[q] - fi[o], -em);
+        const float even = fmaf(ap, Fp, mul_rounded(lp, hp)), odd = fmaf(am, Fm, mul_rounded(lm, hm));
+        const T vq = SS::enc((fi[q] + even) + odd, sc), vo = SS::enc((fi[o] + even) - odd, sc);
         sp[k] = (double)SS::dec(vq, inv) + (double)SS::dec(vo, inv);
         out[q] = vq;
         out[o] = vo;
@@ -261,7 +300,9 @@ __device__ __forceinline__ bool collide_store(const Phys &Ph, const float (&fi)[
     if (store) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            if (NT) __builtin_nontemporal_store(out[q], B + q * S + c);
+            // NT: the march; byte offsets of 32 bits from the plane (see Phys::wide)
+            if (NT && !Ph.wide) __builtin_nontemporal_store(out[q], at_byte(B + q * S, c * (unsigned)sizeof(T)));
+            else if (NT) __builtin_nontemporal_store(out[q], B + q * S + c);
             else B[q * S + c] = out[q];
         }
     }
@@ -284,32 +325,6 @@ constexpr unsigned long long mirror_table(int q) {
 template <int Q_> __device__ __forceinline__ int mirror_q(int o) {
     constexpr unsigned long long t = mirror_table(Q_);
     return (int)((t >> (5 * o)) & 31ull);
-}
-// a * b rounded on its own (never fused into a following addition)
-__device__ __forceinline__ float mul_rounded(float a, float b) {
-#pragma clang fp contract(off)
-    return a * b;
-}
-// a population h bounced at a moving face plus its term a * b (Eq. bbrule).  The rounding is
-// the one each storage form has always had: the binary16 form rounds the product first
-// (one unit in FP32, but a changed rounding to 16 bits shows in the forces).
-template <int ST> __device__ __forceinline__ float face_add(float h, float a, float b) {
-    return ST == ST_F16 ? h + mul_rounded(a, b) : fmaf(a, b, h);
-}
-
-// c_q . v for a direction known at compile time, without the products by zero
-__device__ __forceinline__ float dir_dot(int q, float v0, float v1, float v2) {
-    float s = 0.f;
-    bool any = false;
-    auto add = [&](int c, float v) {
-        if (c == 0) return;
-        s = !any ? (c > 0 ? v : -v) : c > 0 ? s + v : s - v;
-        any = true;
-    };
-    add(cx(q), v0);
-    add(cy(q), v1);
-    add(cz(q), v2);
-    return s;
 }
 // compile-time loop over the moving directions
 template <int Q_ = 1, typename F> __device__ __forceinline__ void for_dirs(F &&f) {
@@ -648,33 +663,47 @@ __device__ __forceinline__ int kconst(int q) {
 
 // ---- the marching kernel ------------------------------------------------------------
 // A block takes a 64 x 4 column of cells through nzc consecutive planes (NZC, fewer on
-// small boxes).  Each wave
-// takes one row of the column; each lane one x.  The cell types and the particle ids
-// of the particle nodes of four planes (z-1 .. z+2) stay in LDS rings, refilled one
+// small boxes).  Each wave takes one row of the column; each lane one x.  Per plane the kinds
+// of the cells are kept as row masks in LDS rings (64 cells and two halo cells), with the
+// particle ids of the particle nodes beside them, for four planes (z-1 .. z+2), refilled one
 // plane ahead from loads issued a plane earlier, so that a plane costs one barrier.
+//
+// On a column of spheres the kernel issues vector instructions on 80 % of its cycles beside
+// 4.4 TB/s of traffic, so what is the same for the wave is worked on masks in scalar
+// registers: which cells are marched, and for each direction which lanes bounce back and
+// from what.  A mask is then the condition of a select or of a masked block without any
+// per-lane bit work.
 constexpr int NZC = 16;
 #ifndef WPE_MARCH
 #define WPE_MARCH 4
 #endif
 constexpr int HX = TX + 2, HY = TY + 2;  // a staged plane: 6 rows of 66 cells
-
-// bitmasks of a staged row (cells x0-1 .. x0+64): bit l of a "3" mask is set when one
-// of the cells x-1, x, x+1 of lane l is of the kind, of a "1" mask when the cell x is.
-// nf: not liquid or interface (gas, particle node, wall); bad: gas and, with moving
-// or slipping faces, walls.
-enum { MK_NF3 = 0, MK_NF1, MK_BAD3, MK_BAD1, MK_N };
+constexpr int NSLOT = 256;               // spheres whose link sums a block keeps
+constexpr unsigned AN_SOL = 1u, AN_BAD = 2u, AN_IFC = 4u;  // kinds that a wave's staged rows hold
 
 struct MarchLds {
-    uint8_t ft[4][HY][HX];              // cell types, slot z & 3
-    int pt[4][HY][HX];                  // particle ids (particle nodes only), slot z & 3
-    unsigned long long mk[4][MK_N][HY]; // row masks, slot z & 3
-    int genflag[2];                     // the plane holds cells for the general path
-    // each lane's link sums for one particle over the planes of the march: force and
-    // torque about the particle's centre (Eqs. netforce, torque, momentum_transfer) in
-    // FP64, and the mass that moving bounce-back added (paid by the ledger)
-    double acc[7][256];
-    int accP[256];
+    int pt[4][HY][HX];               // particle ids (particle nodes only, -1 elsewhere), slot z & 3
+    unsigned long long sol[4][HY];   // particle nodes: bit l is the cell x0-1+l (l < 64) ...
+    uint8_t solhi[4][8];             // ... and the cells x0+63, x0+64 in two bits per row
+    unsigned long long liq[4][HY], ifc[4][HY];  // liquid, interface: bit l is the cell x0+l
+    // bad: gas and, with moving or slipping faces, walls; bit l is set when one of the cells
+    // x-1, x, x+1 of lane l is bad (b3), or the cell x (b1)
+    unsigned long long b3[4][HY], b1[4][HY];
+    uint8_t any[4][4];               // kinds in the rows that wave wv staged (AN_*)
+    int genflag[2];                  // the plane holds cells for the general path
+    // link sums per sphere over the block's planes: force and torque about the sphere's
+    // centre (Eqs. netforce, torque, momentum_transfer) in FP64, and the mass that moving
+    // bounce-back added (paid by the ledger)
+    double acc[7][NSLOT];
+    int tag[NSLOT];
 };
+
+// a value that is the same in every lane, as a scalar
+__device__ __forceinline__ unsigned uni32(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ unsigned long long uni64(unsigned long long v) {
+    return (unsigned long long)uni32((unsigned)v) | ((unsigned long long)uni32((unsigned)(v >> 32)) << 32);
+}
+__device__ __forceinline__ bool in_mask(unsigned long long m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Staging of the ring: wave wv loads rows wv and wv + 4 (waves 0, 1) of a plane, lane l
 // the cell x0-1+l and lanes 0, 1 also x0+63+l.  The lane's column and row offsets
@@ -735,87 +764,63 @@ __device__ __forceinline__ void pre_pids(const int *pid, const StageIdx &I, RowP
     }
 }
 
-// write the staged rows of a plane into ring slot sl and form their masks (ballots
-// over the wave's registers); the caller syncs before the slot is read
-__device__ __forceinline__ void pre_store(MarchLds &L, const RowPre &R, int sl, bool wall_bad) {
+// Write the staged rows of a plane into ring slot sl: masks by ballots over the wave's
+// registers, ids where the row holds particle nodes or its slot still holds those of an
+// earlier plane (dirty: bit 2 sl + k, the same for the wave); the caller syncs before the
+// slot is read.
+__device__ __forceinline__ void pre_store(MarchLds &L, const RowPre &R, int sl, bool wall_bad, unsigned &dirty) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const bool hl = lane < 2;
+    unsigned an = 0u;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int r = wv + 4 * k;
         if (r >= HY) continue;  // uniform over the wave
         const int a = R.f[k] & 0xff, b = (R.f[k] >> 8) & 0xff;
-        L.ft[sl][r][lane] = (uint8_t)a;
-        L.pt[sl][r][lane] = R.p[k];
-        if (lane < 2) {
-            L.ft[sl][r][64 + lane] = (uint8_t)b;
-            L.pt[sl][r][64 + lane] = R.pe[k];
-        }
-        const bool hl = lane < 2;
-        const unsigned long long nlo = __ballot(a != LIQ && a != IFC);
-        const unsigned long long nhi = __ballot(hl && b != LIQ && b != IFC) & 3ull;
+        const unsigned long long slo = __ballot(a == SOL), shi = __ballot(hl && b == SOL);
+        const unsigned long long llo = __ballot(a == LIQ), lhi = __ballot(hl && b == LIQ);
+        const unsigned long long ilo = __ballot(a == IFC), ihi = __ballot(hl && b == IFC);
         const unsigned long long blo = __ballot(a == GAS || (wall_bad && a == WALL));
-        const unsigned long long bhi = __ballot(hl && (b == GAS || (wall_bad && b == WALL))) & 3ull;
+        const unsigned long long bhi = __ballot(hl && (b == GAS || (wall_bad && b == WALL)));
+        const bool s = (slo | shi) != 0ull;
+        an |= (s ? AN_SOL : 0u) | ((blo | bhi) ? AN_BAD : 0u) | ((ilo | ihi) ? AN_IFC : 0u);
+        const unsigned db = 1u << (2 * sl + k);
+        if (s || (dirty & db)) {
+            L.pt[sl][r][lane] = R.p[k];
+            if (hl) L.pt[sl][r][64 + lane] = R.pe[k];
+        }
+        dirty = s ? dirty | db : dirty & ~db;
         if (lane == 0) {
-            const unsigned long long n1 = (nlo >> 1) | (nhi << 63), n2 = (nlo >> 2) | (nhi << 62);
+            L.sol[sl][r] = slo;
+            L.solhi[sl][r] = (uint8_t)shi;
+            L.liq[sl][r] = (llo >> 1) | (lhi << 63);
+            L.ifc[sl][r] = (ilo >> 1) | (ihi << 63);
             const unsigned long long b1 = (blo >> 1) | (bhi << 63), b2 = (blo >> 2) | (bhi << 62);
-            L.mk[sl][MK_NF3][r] = nlo | n1 | n2;
-            L.mk[sl][MK_NF1][r] = n1;
-            L.mk[sl][MK_BAD3][r] = blo | b1 | b2;
-            L.mk[sl][MK_BAD1][r] = b1;
+            L.b3[sl][r] = blo | b1 | b2;
+            L.b1[sl][r] = b1;
         }
     }
-}
-
-// D3Q19 neighbourhood of lane l in row ly of the plane in slot s0 (planes z-1, z+1 in
-// slots sm, sp): the OR of the masks of kind K3 (x-1..x+1) and K1 (x) over the 3 x 3
-// square of the plane and the plus shape of the planes beside it
-template <int K3, int K1>
-__device__ __forceinline__ bool nbr_any(const MarchLds &L, int sm, int s0, int sp, int ly, int lx) {
-    const unsigned long long m = L.mk[s0][K3][ly] | L.mk[s0][K3][ly + 1] | L.mk[s0][K3][ly + 2] |
-                                 L.mk[sm][K3][ly + 1] | L.mk[sp][K3][ly + 1] | L.mk[sm][K1][ly] |
-                                 L.mk[sm][K1][ly + 2] | L.mk[sp][K1][ly] | L.mk[sp][K1][ly + 2];
-    return (m >> lx) & 1ull;
+    if (lane == 0) L.any[sl][wv] = (uint8_t)an;
 }
 
 __device__ __forceinline__ void lds_add(double *p, double v) {
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// one lane's sums (in LDS) straight to its particle (a lane that moves on to another
-// particle), then cleared
-__device__ __forceinline__ void macc_atomic(const Dev &D, MarchLds &L, int t) {
-    double *dst = D.pacc + acc_at(L.accP[t], blockIdx.x & (ACC_COPIES - 1));
-#pragma unroll
-    for (int k = 0; k < 7; ++k) {
-        unsafeAtomicAdd(dst + k, L.acc[k][t]);
-        L.acc[k][t] = 0.0;
-    }
-}
-
-// the lanes' remaining sums at the end of a march, segmented by particle: one FP64
-// atomic instruction per (wave, particle).  Every lane of the wave must be active.
-__device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L) {
-    const int t = threadIdx.x;
-    int key = L.accP[t];
-    const double a0 = L.acc[0][t], a1 = L.acc[1][t], a2 = L.acc[2][t], a3 = L.acc[3][t], a4 = L.acc[4][t],
-                 a5 = L.acc[5][t], a6 = L.acc[6][t];
-    while (true) {
-        const unsigned long long act = __ballot(key >= 0);
-        if (!act) break;
-        const int leader = __ffsll((long long)act) - 1;
-        const int k0 = __builtin_amdgcn_readlane(key, leader);
-        const bool mine = key == k0;
-        const double s0 = wave_sum(mine ? a0 : 0.0), s1 = wave_sum(mine ? a1 : 0.0),
-                     s2 = wave_sum(mine ? a2 : 0.0), s3 = wave_sum(mine ? a3 : 0.0),
-                     s4 = wave_sum(mine ? a4 : 0.0), s5 = wave_sum(mine ? a5 : 0.0),
-                     s6 = wave_sum(mine ? a6 : 0.0);
-        const int ln = (int)lane_id();
-        if (ln < 7) {
-            const double v = ln == 0 ? s0 : ln == 1 ? s1 : ln == 2 ? s2 : ln == 3 ? s3 : ln == 4 ? s4 : ln == 5 ? s5 : s6;
-            unsafeAtomicAdd(D.pacc + acc_at(k0, blockIdx.x & (ACC_COPIES - 1)) + ln, v);
+// The slot of sphere P in the block's table of link sums (open addressing, eight places;
+// a block meets a few tens of spheres), or -1 when those are taken by others.
+__device__ __forceinline__ int acc_slot(MarchLds &L, int P) {
+    int s = P & (NSLOT - 1);
+    for (int i = 0; i < 8; ++i) {
+        int t = L.tag[s];
+        if (t < 0) {
+            t = atomicCAS(&L.tag[s], -1, P);
+            if (t < 0) t = P;
         }
-        if (mine) key = -1;
+        if (t == P) return s;
+        s = (s + 1) & (NSLOT - 1);
     }
+    return -1;
 }
 
 // density of a cell's own populations (a cell whose density from the launch before
@@ -840,8 +845,9 @@ struct SrcOff {
 };
 template <int Q_>
 __device__ __forceinline__ int src_off(const SrcOff &o) {
-    return (cx(Q_) == 1 ? o.xm : cx(Q_) == -1 ? o.xp : 0) + (cy(Q_) == 1 ? o.ym : cy(Q_) == -1 ? o.yp : 0) +
-           (cz(Q_) == 1 ? o.zm : cz(Q_) == -1 ? o.zp : 0);
+    // the uniform part first
+    return (cx(Q_) == 1 ? o.xm : cx(Q_) == -1 ? o.xp : 0) +
+           ((cy(Q_) == 1 ? o.ym : cy(Q_) == -1 ? o.yp : 0) + (cz(Q_) == 1 ? o.zm : cz(Q_) == -1 ? o.zp : 0));
 }
 __device__ __forceinline__ int step_to(int v, int d, int n, int per, int stride) {
     const int w = v + d;
@@ -849,47 +855,143 @@ __device__ __forceinline__ int step_to(int v, int d, int n, int per, int stride)
     return per ? (wrapc(w, n) - v) * stride : 0;
 }
 
+// Momentum exchange of a cell's links mk(q) into sphere P (mirror m): the moving-wall rule
+// (Eq. bbrule) adds a_q = 6 w_q c_q . rho u_w to the bounced population fi[q], and Delta j =
+// -c_q (h*_qbar + h_q + 2 w_q) with h_q = h*_qbar + a_q joins the sphere's sums (Eqs.
+// netforce, torque, momentum_transfer).  mk is a predicate of the direction.  ALT: which
+// product of a diagonal link's sum is fused (the rounding that each form of the kernel has
+// always had, kept so that results do not change).
+template <bool PER, bool ALT, typename M>
+__device__ __forceinline__ void march_links(const Geom &G, const Dev &D, MarchLds &L, int P, const PMir &m, M &&mk,
+                                            float rho_t, int x, int y, int z, float (&fi)[Q], int &curP, int &curS) {
+    if (P != curP) {
+        curP = P;
+        curS = acc_slot(L, P);
+    }
+    // rigid-body velocity at the node: c_q . u_w at the link midpoint equals
+    // c_q . (u_P + omega x (x - x_P)) because c_q . (omega x c_q) = 0
+    // nearest image only when the box has periodic axes (a compile-time case)
+    const float rx = mirror_arm(x, m.ax, m.fx, G.nx, PER && G.per[0]),
+                ry = mirror_arm(y, m.ay, m.fy, G.ny, PER && G.per[1]),
+                rz = mirror_arm(z, m.az, m.fz, G.nz, PER && G.per[2]);
+    const float X0 = m.ux + fmaf(m.wy, rz, -mul_rounded(m.wz, ry));
+    const float X1 = m.uy + fmaf(m.wz, rx, -mul_rounded(m.wx, rz));
+    const float X2 = m.uz + fmaf(m.wx, ry, -mul_rounded(m.wy, rx));
+    const float ru0 = mul_rounded(rho_t, X0), ru1 = mul_rounded(rho_t, X1), ru2 = mul_rounded(rho_t, X2);
+    // a_q for axis links (6 w = 1/3) and diagonal links (6 w = 1/6)
+    const float ax = ru0 * (1.0f / 3.0f), ay = ru1 * (1.0f / 3.0f), az = ru2 * (1.0f / 3.0f);
+    const float hxy_p = (ALT ? fmaf(rho_t, X1, ru0) : fmaf(rho_t, X0, ru1)) * (1.0f / 6.0f);
+    const float hxy_m = (ALT ? fmaf(-rho_t, X1, ru0) : fmaf(rho_t, X0, -ru1)) * (1.0f / 6.0f);
+    const float hxz_p = (ALT ? fmaf(rho_t, X2, ru0) : fmaf(rho_t, X0, ru2)) * (1.0f / 6.0f);
+    const float hxz_m = fmaf(rho_t, X0, -ru2) * (1.0f / 6.0f);
+    const float hyz_p = fmaf(rho_t, X1, ru2) * (1.0f / 6.0f), hyz_m = fmaf(rho_t, X1, -ru2) * (1.0f / 6.0f);
+    // sum over the links of -c_q (h*_qbar + h_q), FP32; the constant parts 2 w_q c_q as exact
+    // counts (units of 1/18: axis links count 2, diagonal links 1), packed
+    float f0 = 0.f, f1 = 0.f, f2 = 0.f;
+    int kp = 0;
+#pragma unroll
+    for (int q = 1; q < Q; ++q) {
+        if (!mk(q)) continue;
+        float a;  // 6 w_q c_q . rho u
+        if (q <= 6) a = cx(q) ? cx(q) * ax : cy(q) ? cy(q) * ay : cz(q) * az;
+        else if (cz(q) == 0) a = cx(q) == cy(q) ? cx(q) * hxy_p : cx(q) * hxy_m;
+        else if (cy(q) == 0) a = cx(q) == cz(q) ? cx(q) * hxz_p : cx(q) * hxz_m;
+        else a = cy(q) == cz(q) ? cy(q) * hyz_p : cy(q) * hyz_m;
+        const float s2 = fmaf(2.0f, fi[q], a);
+        if (cx(q)) f0 = cx(q) > 0 ? f0 - s2 : f0 + s2;
+        if (cy(q)) f1 = cy(q) > 0 ? f1 - s2 : f1 + s2;
+        if (cz(q)) f2 = cz(q) > 0 ? f2 - s2 : f2 + s2;
+        fi[q] += a;
+        kp += kconst(q);
+    }
+    int kx, ky, kz;
+    kunpack(kp, kx, ky, kz);
+    // sum_q a_q = rho u . sum_q 6 w_q c_q = -(rho u . k) / 6 with k = -sum c_q m_q
+    const float dm = -(ru0 * (float)kx + ru1 * (float)ky + ru2 * (float)kz) * (1.0f / 6.0f);
+    const double F0 = (double)f0 + kx * (1.0 / 18.0), F1 = (double)f1 + ky * (1.0 / 18.0),
+                 F2 = (double)f2 + kz * (1.0 / 18.0);
+    const double dx = rx, dy = ry, dz = rz;
+    const double v[7] = {F0, F1, F2, dy * F2 - dz * F1, dz * F0 - dx * F2, dx * F1 - dy * F0, (double)dm};
+    if (curS >= 0) {
+#pragma unroll
+        for (int k = 0; k < 7; ++k) lds_add(&L.acc[k][curS], v[k]);
+    } else {  // no place in the table (rare)
+        double *dst = D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
+#pragma unroll
+        for (int k = 0; k < 7; ++k) unsafeAtomicAdd(dst + k, v[k]);
+    }
+}
+
 // One cell of a row in the marching pass: a liquid cell whose neighbours are liquid,
-// interface, particle nodes or resting walls (act).  Pull streaming (Eq. LBE1); a
-// source beyond a resting wall gives half-way bounce-back, a particle node the
+// interface, particle nodes or resting walls (the lanes of act).  Pull streaming (Eq.
+// LBE1); a source beyond a resting wall gives half-way bounce-back, a particle node the
 // moving-wall rule (Eq. bbrule) with rho_w the density of the cell at t and u_w the
-// particle's rigid-body velocity, and its momentum exchange (Eqs. netforce, torque,
-// momentum_transfer) joins the lane's sums; then the collision (Eq. LBE2).  Lanes with
-// store set and act clear (gas and particle nodes of the row) write values that no
-// rule reads, so that every row of every population is written whole and once;
-// interface cells and lanes outside the box leave their words to the general path.
+// particle's rigid-body velocity, and its momentum exchange joins the sphere's sums; then the
+// collision (Eq. LBE2).  Lanes with store set and outside act (gas and particle nodes of the
+// row) write values that no rule reads, so that every row of every population is written
+// whole and once; interface cells and lanes outside the box leave their words to the
+// general path.
 template <int ST, bool PER>
-__device__ __forceinline__ void march_cell(const Geom &G, const Phys &Ph, const Dev &D, MarchLds &L,
-                                           int sm1, int s0, int sp1, int lx, int ly, int x, int y, int z, int c,
-                                           const SrcOff &so, bool act, bool store, bool nbnf, const void *Av,
-                                           void *Bv, long long S, const StageIdx &SI, RowPre &R, int zo2,
-                                           int &curP) {
+__device__ __forceinline__ void march_cell(const Geom &G, const Phys &Ph, const Dev &D, MarchLds &L, int sm1, int s0,
+                                           int sp1, int lx, int ly, int x, int y, int z, int c, const SrcOff &so,
+                                           unsigned long long act, bool store, bool has_sol,
+                                           unsigned long long wx0, unsigned long long wx1, const void *Av, void *Bv,
+                                           long long S, const StageIdx &SI, RowPre &R, int zo2, bool next, int &curP,
+                                           int &curS) {
     using SS = Store<ST>;
     using T = typename SS::T;
     const T *A = (const T *)Av;
     T *B = (T *)Bv;
     const float inv = Ph.inv;
-    auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };  // plane z - c_z
-    // bounce-back sources: particle nodes (sm, from the staged cell types) and resting
-    // walls (wm: the sources beyond a non-periodic face, from the cell's position)
-    uint32_t sm = 0, wm = 0;
-    if (act) {
-        if (!G.per[0]) wm |= (x == 0 ? dir_mask<0, 1>() : 0u) | (x == G.nx - 1 ? dir_mask<0, -1>() : 0u);
-        if (!G.per[1]) wm |= (y == 0 ? dir_mask<1, 1>() : 0u) | (y == G.ny - 1 ? dir_mask<1, -1>() : 0u);
-        if (!G.per[2]) wm |= (z == 0 ? dir_mask<2, 1>() : 0u) | (z == G.nz - 1 ? dir_mask<2, -1>() : 0u);
-        if (nbnf) {
+    constexpr unsigned ES = sizeof(T);
+    // sources beyond resting faces, by component (the row's y and the plane's z are uniform)
+    const unsigned long long wy0 = !G.per[1] && y == 0 ? ~0ull : 0ull, wy1 = !G.per[1] && y == G.ny - 1 ? ~0ull : 0ull;
+    const unsigned long long wz0 = !G.per[2] && z == 0 ? ~0ull : 0ull, wz1 = !G.per[2] && z == G.nz - 1 ? ~0ull : 0ull;
+    // per direction the lanes whose source is a particle node (sm) or that bounce back (bb)
+    unsigned long long sm[Q], bb[Q], link = 0ull, any = 0ull;
+    if (has_sol) {
+        unsigned long long lo[3][3];
+        unsigned hi[3][3];
 #pragma unroll
-            for (int q = 1; q < Q; ++q) sm |= (uint32_t)(L.ft[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)] == SOL) << q;
+        for (int p = 0; p < 3; ++p) {
+            const int sl = p == 0 ? sm1 : p == 1 ? s0 : sp1;
+            const unsigned long long h8 = uni64(*(const unsigned long long *)L.solhi[sl]) >> (8 * ly);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                lo[p][r] = uni64(L.sol[sl][ly + r]);
+                hi[p][r] = (unsigned)(h8 >> (8 * r)) & 3u;
+            }
         }
+#pragma unroll
+        for (int q = 1; q < Q; ++q) {
+            const int p = 1 - cz(q), r = 1 - cy(q), k = 1 - cx(q);
+            const unsigned long long m = k == 0 ? lo[p][r] : (lo[p][r] >> k) | ((unsigned long long)hi[p][r] << (64 - k));
+            sm[q] = m & act;
+            link |= sm[q];
+        }
+    } else {
+#pragma unroll
+        for (int q = 1; q < Q; ++q) sm[q] = 0ull;
     }
-    const uint32_t bb = sm | wm;
+#pragma unroll
+    for (int q = 1; q < Q; ++q) {
+        const unsigned long long w = (cx(q) == 1 ? wx0 : cx(q) == -1 ? wx1 : 0ull) |
+                                     (cy(q) == 1 ? wy0 : cy(q) == -1 ? wy1 : 0ull) |
+                                     (cz(q) == 1 ? wz0 : cz(q) == -1 ? wz1 : 0ull);
+        bb[q] = sm[q] | (w & act);
+        any |= bb[q];
+    }
     // the particle P of the particle-node links and whether some link leads to another:
     // over the 18 staged ids (-1 at every cell that is no particle node) the smallest as
     // an unsigned value and the largest as a signed one agree exactly when every
     // particle node among them has the same id
     int P = -1;
     bool multi = false;
-    if (sm) {
+    unsigned e = RHOW_NONE;
+    PMir pm{};
+    const bool linked = in_mask(link);
+    if (link) {
+        auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };  // plane z - c_z
         unsigned pmin = 0xffffffffu;
         int pmax = -1;
 #pragma unroll
@@ -898,131 +1000,62 @@ __device__ __forceinline__ void march_cell(const Geom &G, const Phys &Ph, const 
             pmin = min(pmin, (unsigned)p);
             pmax = max(pmax, p);
         }
-        P = (int)pmin;
-        multi = (int)pmin != pmax;
+        if (linked) {
+            P = (int)pmin;
+            multi = (int)pmin != pmax || (unsigned)P >= (unsigned)D.np;
+            // rho_w of Eq. bbrule: the density of this cell at t, as the launch before stored it
+            if (D.rhow != nullptr && D.st_prev >= 0) e = D.rhow[c];
+            if (!multi) pm = pmir_load(D.pmir, P);
+        }
     }
-    const bool okP = (unsigned)P < (unsigned)D.np;
-    // rho_w of Eq. bbrule: the density of this cell at t, as the launch before stored it
-    unsigned e = RHOW_NONE;
-    if (sm && D.rhow != nullptr && D.st_prev >= 0) e = D.rhow[c];
-    PMir pm{};
-    if (sm && okP) pm = pmir_load(D.pmir, P);
     // pulls; a bounce-back link takes the cell's own opposite population instead (the
-    // source address is selected, so every population is one load)
+    // source address is selected, so every population is one load).  The planes q and
+    // opp(q) share the base of the lower one.
     float fi[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) fi[q] = 0.f;
-    if (act) {  // lanes without a liquid cell load nothing
-        if (__ballot(bb) == 0ull) {
-#define FSL_PULL(QQ) fi[QQ] = SS::ld(A + QQ * S + (unsigned)(c + src_off<QQ>(so)), inv);
-            FSL_PULL(0) FSL_PULL(1) FSL_PULL(2) FSL_PULL(3) FSL_PULL(4) FSL_PULL(5) FSL_PULL(6)
-            FSL_PULL(7) FSL_PULL(8) FSL_PULL(9) FSL_PULL(10) FSL_PULL(11) FSL_PULL(12) FSL_PULL(13)
-            FSL_PULL(14) FSL_PULL(15) FSL_PULL(16) FSL_PULL(17) FSL_PULL(18)
-#undef FSL_PULL
-        } else if (!Ph.wide) {
-            // the planes q and opp(q) share the base of the lower one; the lane's offset
-            // from it (at most 4 S) stays within 32 bits
-            const unsigned S32 = (unsigned)S;
-            fi[0] = SS::ld(A + (unsigned)c, inv);
-#define FSL_PULL(QQ)                                                                                      \
-    {                                                                                                     \
-        constexpr int lo_ = QQ < opp(QQ) ? QQ : opp(QQ);                                                  \
-        const int so_ = src_off<QQ>(so);                                                                  \
-        const unsigned m_ = (unsigned)__builtin_amdgcn_sbfe((int)bb, QQ, 1); /* all ones on a link */     \
-        unsigned o_ = (unsigned)(QQ - lo_) * S32 + (unsigned)(c + so_) +                                   \
-                      (((unsigned)(opp(QQ) - QQ) * S32 - (unsigned)so_) & m_);                            \
-        __asm__("" : "+v"(o_));                                                                           \
-        fi[QQ] = SS::ld(A + lo_ * S + o_, inv);                                                           \
-    }
-            FSL_PULL(1) FSL_PULL(2) FSL_PULL(3) FSL_PULL(4) FSL_PULL(5) FSL_PULL(6)
-            FSL_PULL(7) FSL_PULL(8) FSL_PULL(9) FSL_PULL(10) FSL_PULL(11) FSL_PULL(12) FSL_PULL(13)
-            FSL_PULL(14) FSL_PULL(15) FSL_PULL(16) FSL_PULL(17) FSL_PULL(18)
-#undef FSL_PULL
+    if (in_mask(act)) {  // lanes without a liquid cell load nothing
+        const unsigned c4 = (unsigned)c * ES, S4 = (unsigned)S * ES;
+        if (!Ph.wide) {
+            fi[0] = SS::dec(*at_byte(A, c4), inv);
+            if (any == 0ull) {
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    fi[q] = SS::dec(*at_byte(A + q * S, c4 + (unsigned)src_off<q>(so) * ES), inv);
+                });
+            } else {
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    constexpr int lo = q < opp(q) ? q : opp(q);
+                    const unsigned pull = c4 + (unsigned)src_off<q>(so) * ES + (unsigned)(q - lo) * S4;
+                    unsigned o = in_mask(bb[q]) ? c4 + (unsigned)(opp(q) - lo) * S4 : pull;
+                    __asm__("" : "+v"(o));
+                    fi[q] = SS::dec(*at_byte(A + lo * S, o), inv);
+                });
+            }
         } else {
             fi[0] = SS::ld(A + (unsigned)c, inv);
-#define FSL_PULL(QQ)                                                                                       \
-    {                                                                                                      \
-        const bool b_ = (bb >> QQ) & 1u;                                                                   \
-        fi[QQ] = SS::ld((b_ ? A + opp(QQ) * S : A + QQ * S) + (unsigned)(b_ ? c : c + src_off<QQ>(so)), inv); \
-    }
-            FSL_PULL(1) FSL_PULL(2) FSL_PULL(3) FSL_PULL(4) FSL_PULL(5) FSL_PULL(6)
-            FSL_PULL(7) FSL_PULL(8) FSL_PULL(9) FSL_PULL(10) FSL_PULL(11) FSL_PULL(12) FSL_PULL(13)
-            FSL_PULL(14) FSL_PULL(15) FSL_PULL(16) FSL_PULL(17) FSL_PULL(18)
-#undef FSL_PULL
+            for_dirs([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                const bool b = in_mask(bb[q]);
+                fi[q] = SS::ld((b ? A + opp(q) * S : A + q * S) + (unsigned)(b ? c : c + src_off<q>(so)), inv);
+            });
         }
     }
     // particle ids of plane z+2 for the ring (its cell types were loaded before)
-    pre_pids(D.pid, SI, R, zo2);
-    if (sm) {
+    if (next) pre_pids(D.pid, SI, R, zo2);
+    if (linked) {
         const float rho_t = rhow_valid(e, D.st_prev) ? __uint_as_float(e) : own_density<ST>(Av, S, c, inv);
-        const int t = threadIdx.x;
-        // the links mk of particle Pk (mirror m): moving-wall rule and momentum exchange.
-        // With rho u = rho_w u_w the link adds a_q = 6 w_q c_q . rho u to the bounced
-        // population, and Delta j = -c_q (h*_qbar + h_q + 2 w_q) with h_q = h*_qbar + a_q.
-        auto particle_links = [&](int Pk, uint32_t mk, const PMir &m) {
-            if (Pk != curP) {  // the lane's sums move on to another particle
-                if (curP >= 0) macc_atomic(D, L, t);
-                curP = Pk;
-                L.accP[t] = Pk;
-            }
-            // rigid-body velocity at the node: c_q . u_w at the link midpoint equals
-            // c_q . (u_P + omega x (x - x_P)) because c_q . (omega x c_q) = 0
-            // nearest image only when the box has periodic axes (a compile-time case)
-            const float rx = mirror_arm(x, m.ax, m.fx, G.nx, PER && G.per[0]),
-                        ry = mirror_arm(y, m.ay, m.fy, G.ny, PER && G.per[1]),
-                        rz = mirror_arm(z, m.az, m.fz, G.nz, PER && G.per[2]);
-            const float ru0 = rho_t * (m.ux + (m.wy * rz - m.wz * ry));
-            const float ru1 = rho_t * (m.uy + (m.wz * rx - m.wx * rz));
-            const float ru2 = rho_t * (m.uz + (m.wx * ry - m.wy * rx));
-            // a_q for axis links (6 w = 1/3) and diagonal links (6 w = 1/6)
-            const float ax = ru0 * (1.0f / 3.0f), ay = ru1 * (1.0f / 3.0f), az = ru2 * (1.0f / 3.0f);
-            const float hxy_p = (ru0 + ru1) * (1.0f / 6.0f), hxy_m = (ru0 - ru1) * (1.0f / 6.0f);
-            const float hxz_p = (ru0 + ru2) * (1.0f / 6.0f), hxz_m = (ru0 - ru2) * (1.0f / 6.0f);
-            const float hyz_p = (ru1 + ru2) * (1.0f / 6.0f), hyz_m = (ru1 - ru2) * (1.0f / 6.0f);
-            auto aq = [&](int q) -> float {  // 6 w_q c_q . rho u
-                if (q <= 6) return (cx(q) ? cx(q) * ax : 0.f) + (cy(q) ? cy(q) * ay : 0.f) + (cz(q) ? cz(q) * az : 0.f);
-                if (cz(q) == 0) return cx(q) == cy(q) ? cx(q) * hxy_p : cx(q) * hxy_m;
-                if (cy(q) == 0) return cx(q) == cz(q) ? cx(q) * hxz_p : cx(q) * hxz_m;
-                return cy(q) == cz(q) ? cy(q) * hyz_p : cy(q) * hyz_m;
-            };
-            // sum over the links of -c_q (h*_qbar + h_q), FP32
-            float f0 = 0.f, f1 = 0.f, f2 = 0.f;
-#pragma unroll
-            for (int q = 1; q < Q; ++q) {
-                const bool b = (mk >> q) & 1u;
-                const float a = b ? aq(q) : 0.f;
-                const float s2 = b ? 2.0f * fi[q] + a : 0.f;
-                if (cx(q)) f0 -= cx(q) * s2;
-                if (cy(q)) f1 -= cy(q) * s2;
-                if (cz(q)) f2 -= cz(q) * s2;
-                fi[q] += a;
-            }
-            // the constant parts 2 w_q c_q as exact counts (units of 1/18) from the link
-            // mask: axis links count 2, diagonal links 1; and the added mass sum a_q
-            // (bit q set for the directions with c_q = -1 and = +1 along each axis)
-            const int kx = 2 * (__popc(mk & 0x4u) - __popc(mk & 0x2u)) + __popc(mk & 0x6600u) - __popc(mk & 0x1980u);
-            const int ky = 2 * (__popc(mk & 0x10u) - __popc(mk & 0x8u)) + __popc(mk & 0x60500u) - __popc(mk & 0x18280u);
-            const int kz = 2 * (__popc(mk & 0x40u) - __popc(mk & 0x20u)) + __popc(mk & 0x55000u) - __popc(mk & 0x2a800u);
-            // sum_q a_q = rho u . sum_q 6 w_q c_q = -(rho u . k) / 6 with k = -sum c_q m_q
-            const float dm = -(ru0 * (float)kx + ru1 * (float)ky + ru2 * (float)kz) * (1.0f / 6.0f);
-            const double F0 = (double)f0 + kx * (1.0 / 18.0), F1 = (double)f1 + ky * (1.0 / 18.0),
-                         F2 = (double)f2 + kz * (1.0 / 18.0);
-            const double dx = rx, dy = ry, dz = rz;
-            // LDS atomic adds without return: the lane's own slots, so nothing waits
-            lds_add(&L.acc[0][t], F0);
-            lds_add(&L.acc[1][t], F1);
-            lds_add(&L.acc[2][t], F2);
-            lds_add(&L.acc[3][t], dy * F2 - dz * F1);
-            lds_add(&L.acc[4][t], dz * F0 - dx * F2);
-            lds_add(&L.acc[5][t], dx * F1 - dy * F0);
-            lds_add(&L.acc[6][t], (double)dm);
-        };
-        if (!multi && okP) {
-            particle_links(P, sm, pm);
-        } else {
+        if (!multi)
+            march_links<PER, ST == ST_F32 && PER>(G, D, L, P, pm, [&](int q) { return in_mask(sm[q]); }, rho_t, x, y, z, fi,
+                                                  curP, curS);
+        else {
             // links into more than one particle, or an inconsistent owner (rare): one
             // particle at a time
-            uint32_t rest = sm;
+            auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };
+            uint32_t rest = 0;
+#pragma unroll
+            for (int q = 1; q < Q; ++q) rest |= (uint32_t)in_mask(sm[q]) << q;
             while (rest) {
                 const int q0 = __ffs(rest) - 1;
                 int Pk = -1;
@@ -1038,17 +1071,19 @@ __device__ __forceinline__ void march_cell(const Geom &G, const Phys &Ph, const 
                     atomicOr(D.err, ERR_LG);
                     continue;
                 }
-                particle_links(Pk, mk, pmir_load(D.pmir, Pk));
+                march_links<PER, ST == ST_F32>(G, D, L, Pk, pmir_load(D.pmir, Pk),
+                                               [&](int q) { return ((mk >> q) & 1u) != 0u; }, rho_t, x, y, z, fi, curP,
+                                               curS);
             }
         }
     }
     const Moments M = cell_moments(fi);
     if (D.rhow != nullptr && D.st_cur >= 0 && store) {
         // the density for a liquid cell, none for the row's other cells
-        const unsigned w = act ? rhow_word(1.0f + (float)M.drho, D.st_cur) : RHOW_NONE;
+        const unsigned w = in_mask(act) ? rhow_word(1.0f + (float)M.drho, D.st_cur) : RHOW_NONE;
         __builtin_nontemporal_store(w, D.rhow + c);
     }
-    if (!collide_store<ST, true>(Ph, fi, M, B, S, (unsigned)c, store) && act) atomicOr(D.err, ERR_NAN);
+    if (!collide_store<ST, true>(Ph, fi, M, B, S, (unsigned)c, store) && in_mask(act)) atomicOr(D.err, ERR_NAN);
 }
 
 // tiles of the march: blocks go to the eight XCDs round-robin; each XCD takes whole
@@ -1080,50 +1115,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
     march_of_block(blockIdx.x, tilesX * tilesY, nChunks, col, chunk);
     const int x0 = (col % tilesX) * TX, y0 = (col / tilesX) * TY;
     const int zs = chunk * nzc, ze = min(zs + nzc, G.nz);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wv = (int)uni32(threadIdx.x >> 6);
     const int lx = lane, ly = wv;
     const int x = x0 + lx, y = y0 + ly;
-    const bool inb = x < G.nx && y < G.ny;
+    // lanes inside the box, and those at its two resting x faces
+    const int nin = G.nx - x0;
+    const unsigned long long inb = y >= G.ny ? 0ull : nin >= 64 ? ~0ull : (1ull << nin) - 1ull;
+    const unsigned long long wx0 = !G.per[0] && x0 == 0 ? 1ull : 0ull;
+    const unsigned long long wx1 = !G.per[0] && nin >= 1 && nin <= 64 ? 1ull << (nin - 1) : 0ull;
 
-    // planes zs-1 .. zs+1 into the ring
+    // planes zs-1 .. zs+1 into the ring, the loads of all three in flight together
     const StageIdx SI = stage_idx(G, x0, y0);
     RowPre R;
-    for (int p = zs - 1; p <= zs + 1; ++p) {
-        const int zo = stage_zo(G, p);
-        pre_flags(D.flags, SI, R, zo);
-        pre_pids(D.pid, SI, R, zo);
-        pre_store(L, R, p & 3, MW);
+    unsigned dirty = 0xffu;  // the ring starts unwritten
+    {
+        RowPre R3[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) pre_flags(D.flags, SI, R3[p], stage_zo(G, zs - 1 + p));
+#pragma unroll
+        for (int p = 0; p < 3; ++p) pre_pids(D.pid, SI, R3[p], stage_zo(G, zs - 1 + p));
+#pragma unroll
+        for (int p = 0; p < 3; ++p) pre_store(L, R3[p], (zs - 1 + p) & 3, MW, dirty);
     }
     if (threadIdx.x < 2) L.genflag[threadIdx.x] = 0;
-    L.accP[threadIdx.x] = -1;
-    int curP = -1;  // the particle of the lane's sums (a copy of L.accP)
+    int curP = -1, curS = -1;  // the lane's last sphere and its slot in the table
+    if (D.np > 0) {
+        L.tag[threadIdx.x] = -1;
 #pragma unroll
-    for (int k = 0; k < 7; ++k) L.acc[k][threadIdx.x] = 0.0;
+        for (int k = 0; k < 7; ++k) L.acc[k][threadIdx.x] = 0.0;
+    }
     __syncthreads();
 
     for (int z = zs; z < ze; ++z) {
         // the ring's next plane z+2: cell types now, particle ids once the pulls of this
         // plane are issued
+        const bool next = z + 1 < ze;
         const int zo2 = stage_zo(G, z + 2);
-        pre_flags(D.flags, SI, R, zo2);
+        if (next) pre_flags(D.flags, SI, R, zo2);
         const int s0 = z & 3, sm1 = (z - 1) & 3, sp1 = (z + 1) & 3;
         // values the compiler would otherwise keep for the whole march (per-direction
         // address terms of the lane, plane bases): recomputed in every plane instead
-        int xl = x, yl = y;
+        int xl = x;
         long long Sl = G.S;
-        __asm__ volatile("" : "+v"(xl), "+v"(yl));
+        __asm__ volatile("" : "+v"(xl));
         // the lane's cell for addresses (lanes beyond the box take the last one)
-        const int xc = min(xl, G.nx - 1), yc = min(yl, G.ny - 1);
+        const int xc = min(xl, G.nx - 1), yc = min(y, G.ny - 1);
         __asm__ volatile("" : "+s"(Sl));
         const void *Av = D.fA;
         void *Bv = D.fB;
-        const uint8_t fl = inb ? L.ft[s0][ly + 1][lx + 1] : WALL;
-        const bool nbnf = nbr_any<MK_NF3, MK_NF1>(L, sm1, s0, sp1, ly, lx);
-        const bool nbbad = nbr_any<MK_BAD3, MK_BAD1>(L, sm1, s0, sp1, ly, lx);
-        const bool gen_c = inb && (fl == IFC || (fl == LIQ && nbbad));
-        const bool act = inb && fl == LIQ && !nbbad;
-        if (__ballot(gen_c) && lane == 0) L.genflag[z & 1] = 1;
-        if (__ballot(act)) {
+        unsigned an = uni32(*(const unsigned *)L.any[sm1] | *(const unsigned *)L.any[s0] | *(const unsigned *)L.any[sp1]);
+        an |= an >> 16;
+        an |= an >> 8;
+        const unsigned long long liq = uni64(L.liq[s0][ly + 1]) & inb;
+        // lanes with a bad neighbour (D3Q19: the square of the plane, the plus of the two
+        // planes beside it), and the cells for the general path
+        unsigned long long bad = 0ull, gen_m = 0ull;
+        if (an & (AN_BAD | AN_IFC)) {
+            if (an & AN_BAD)
+                bad = uni64(L.b3[s0][ly] | L.b3[s0][ly + 1] | L.b3[s0][ly + 2] | L.b3[sm1][ly + 1] | L.b3[sp1][ly + 1] |
+                            L.b1[sm1][ly] | L.b1[sm1][ly + 2] | L.b1[sp1][ly] | L.b1[sp1][ly + 2]);
+            gen_m = (uni64(L.ifc[s0][ly + 1]) & inb) | (liq & bad);
+            if (gen_m && lane == 0) L.genflag[z & 1] = 1;
+        }
+        const unsigned long long act = liq & ~bad;
+        if (act) {
             const int nxy = G.nx * G.ny;
             SrcOff so;
             so.xm = step_to(xc, -1, G.nx, G.per[0], 1);
@@ -1132,13 +1187,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
             so.yp = step_to(yc, 1, G.ny, G.per[1], G.nx);
             so.zm = step_to(z, -1, G.nz, G.per[2], nxy);
             so.zp = step_to(z, 1, G.nz, G.per[2], nxy);
-            const int c = xc + G.nx * yc + nxy * z;
-            march_cell<ST, PER>(G, Ph, D, L, sm1, s0, sp1, lx, ly, xl, yl, z, c, so, act, inb && !gen_c, nbnf, Av, Bv, Sl,
-                           SI, R, zo2, curP);
-        } else {
+            const int c = xc + (G.nx * yc + nxy * z);
+            march_cell<ST, PER>(G, Ph, D, L, sm1, s0, sp1, lx, ly, xl, y, z, c, so, act, in_mask(inb & ~gen_m),
+                                (an & AN_SOL) != 0u, wx0, wx1, Av, Bv, Sl, SI, R, zo2, next, curP, curS);
+        } else if (next) {
             pre_pids(D.pid, SI, R, zo2);
         }
-        pre_store(L, R, (z + 2) & 3, MW);
+        if (next) pre_store(L, R, (z + 2) & 3, MW, dirty);
         __syncthreads();
         if (threadIdx.x == 0 && L.genflag[z & 1]) {
             L.genflag[z & 1] = 0;
@@ -1146,7 +1201,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
             gen[slot] = col + tilesX * tilesY * z;  // list capacity: every tile of the box
         }
     }
-    if (D.np > 0) macc_wave_flush(D, L);
+    // the block's link sums, an atomic per sphere and component
+    if (D.np > 0) {
+        const int t = threadIdx.x, P = L.tag[t];
+        if (P >= 0) {
+            double *dst = D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
+#pragma unroll
+            for (int k = 0; k < 7; ++k) unsafeAtomicAdd(dst + k, L.acc[k][t]);
+        }
+    }
 }
 
 // Row masks of the staged tile for the general path's selection (gas and, with moving
