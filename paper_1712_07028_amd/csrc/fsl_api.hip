@@ -322,7 +322,7 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
     }
     const int nChunks = (c->G.nz + nzc - 1) / nzc;
     hipLaunchKernelGGL((k_stream_collide<ST, MW, PER>), dim3(c->tilesX * c->tilesY * nChunks), dim3(256), 0, c->st,
-                       c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen);
+                       MarchArgs{c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen});
     if (!c->gas && !MW) return;  // the list is empty
     hipLaunchKernelGGL((k_general<ST, MW>), dim3(std::min(c->nTiles, 4096)), dim3(256), 0, c->st, c->G, c->Ph, Dv,
                        c->tilesX, c->tilesY, (const int *)glist, (const int *)ngen);

@@ -922,6 +922,47 @@ __device__ __forceinline__ void march_links(const Geom &G, const Dev &D, MarchLd
     }
 }
 
+// The launch's arguments, read from where the launch put them: again at every call, so that
+// the compiler holds none of them over the whole march (about 60 scalars, for which the
+// scalar registers that the masks leave do not suffice; it would keep them in lanes of
+// vector registers and spend two vector instructions on each use).
+struct MarchArgs {
+    Geom G;
+    Phys Ph;
+    Dev D;
+    int tilesX, tilesY, nChunks, nzc;
+    int *gen, *ngen;
+};
+__device__ __forceinline__ const MarchArgs &march_args() {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(p));
+    return *(const MarchArgs *)p;
+}
+
+// Per direction the lanes of act whose source (x - c_q) is a particle node, from the staged
+// rows ly .. ly+2 of the three planes
+__device__ __forceinline__ void solid_masks(const MarchLds &L, int sm1, int s0, int sp1, int ly, unsigned long long act,
+                                            unsigned long long (&sm)[Q]) {
+    unsigned long long lo[3][3];
+    unsigned hi[3][3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        const int sl = p == 0 ? sm1 : p == 1 ? s0 : sp1;
+        const unsigned long long h8 = uni64(*(const unsigned long long *)L.solhi[sl]) >> (8 * ly);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            lo[p][r] = uni64(L.sol[sl][ly + r]);
+            hi[p][r] = (unsigned)(h8 >> (8 * r)) & 3u;
+        }
+    }
+#pragma unroll
+    for (int q = 1; q < Q; ++q) {
+        const int p = 1 - cz(q), r = 1 - cy(q), k = 1 - cx(q);
+        const unsigned long long m = k == 0 ? lo[p][r] : (lo[p][r] >> k) | ((unsigned long long)hi[p][r] << (64 - k));
+        sm[q] = m & act;
+    }
+}
+
 // One cell of a row in the marching pass: a liquid cell whose neighbours are liquid,
 // interface, particle nodes or resting walls (the lanes of act).  Pull streaming (Eq.
 // LBE1); a source beyond a resting wall gives half-way bounce-back, a particle node the
@@ -932,158 +973,154 @@ __device__ __forceinline__ void march_links(const Geom &G, const Dev &D, MarchLd
 // whole and once; interface cells and lanes outside the box leave their words to the
 // general path.
 template <int ST, bool PER>
-__device__ __forceinline__ void march_cell(const Geom &G, const Phys &Ph, const Dev &D, MarchLds &L, int sm1, int s0,
-                                           int sp1, int lx, int ly, int x, int y, int z, int c, const SrcOff &so,
-                                           unsigned long long act, bool store, bool has_sol,
-                                           unsigned long long wx0, unsigned long long wx1, const void *Av, void *Bv,
-                                           long long S, const StageIdx &SI, RowPre &R, int zo2, bool next, int &curP,
-                                           int &curS) {
+__device__ __forceinline__ void march_cell(MarchLds &L, int sm1, int s0, int sp1, int lx, int ly, int x, int y, int z,
+                                           int c, const SrcOff &so, unsigned long long act, bool store, bool has_sol,
+                                           unsigned long long wx0, unsigned long long wx1, const StageIdx &SI, RowPre &R,
+                                           int zo2, bool next, int &curP, int &curS) {
     using SS = Store<ST>;
     using T = typename SS::T;
-    const T *A = (const T *)Av;
-    T *B = (T *)Bv;
-    const float inv = Ph.inv;
     constexpr unsigned ES = sizeof(T);
-    // sources beyond resting faces, by component (the row's y and the plane's z are uniform)
-    const unsigned long long wy0 = !G.per[1] && y == 0 ? ~0ull : 0ull, wy1 = !G.per[1] && y == G.ny - 1 ? ~0ull : 0ull;
-    const unsigned long long wz0 = !G.per[2] && z == 0 ? ~0ull : 0ull, wz1 = !G.per[2] && z == G.nz - 1 ? ~0ull : 0ull;
-    // per direction the lanes whose source is a particle node (sm) or that bounce back (bb)
-    unsigned long long sm[Q], bb[Q], link = 0ull, any = 0ull;
-    if (has_sol) {
-        unsigned long long lo[3][3];
-        unsigned hi[3][3];
+    unsigned long long link = 0ull;  // lanes with a particle link
+    float fi[Q];
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const int sl = p == 0 ? sm1 : p == 1 ? s0 : sp1;
-            const unsigned long long h8 = uni64(*(const unsigned long long *)L.solhi[sl]) >> (8 * ly);
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                lo[p][r] = uni64(L.sol[sl][ly + r]);
-                hi[p][r] = (unsigned)(h8 >> (8 * r)) & 3u;
-            }
-        }
-#pragma unroll
-        for (int q = 1; q < Q; ++q) {
-            const int p = 1 - cz(q), r = 1 - cy(q), k = 1 - cx(q);
-            const unsigned long long m = k == 0 ? lo[p][r] : (lo[p][r] >> k) | ((unsigned long long)hi[p][r] << (64 - k));
-            sm[q] = m & act;
-            link |= sm[q];
-        }
-    } else {
-#pragma unroll
-        for (int q = 1; q < Q; ++q) sm[q] = 0ull;
-    }
-#pragma unroll
-    for (int q = 1; q < Q; ++q) {
-        const unsigned long long w = (cx(q) == 1 ? wx0 : cx(q) == -1 ? wx1 : 0ull) |
-                                     (cy(q) == 1 ? wy0 : cy(q) == -1 ? wy1 : 0ull) |
-                                     (cz(q) == 1 ? wz0 : cz(q) == -1 ? wz1 : 0ull);
-        bb[q] = sm[q] | (w & act);
-        any |= bb[q];
-    }
-    // the particle P of the particle-node links and whether some link leads to another:
-    // over the 18 staged ids (-1 at every cell that is no particle node) the smallest as
-    // an unsigned value and the largest as a signed one agree exactly when every
-    // particle node among them has the same id
+    for (int q = 0; q < Q; ++q) fi[q] = 0.f;
     int P = -1;
     bool multi = false;
     unsigned e = RHOW_NONE;
     PMir pm{};
-    const bool linked = in_mask(link);
-    if (link) {
-        auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };  // plane z - c_z
-        unsigned pmin = 0xffffffffu;
-        int pmax = -1;
+    {
+        const MarchArgs &M = march_args();
+        const Geom &G = M.G;
+        const long long S = G.S;
+        const T *A = (const T *)M.D.fA;
+        const float inv = M.Ph.inv;
+        unsigned long long sm[Q];
+        if (has_sol) {
+            solid_masks(L, sm1, s0, sp1, ly, act, sm);
 #pragma unroll
-        for (int q = 1; q < Q; ++q) {
-            const int p = L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)];
-            pmin = min(pmin, (unsigned)p);
-            pmax = max(pmax, p);
-        }
-        if (linked) {
-            P = (int)pmin;
-            multi = (int)pmin != pmax || (unsigned)P >= (unsigned)D.np;
-            // rho_w of Eq. bbrule: the density of this cell at t, as the launch before stored it
-            if (D.rhow != nullptr && D.st_prev >= 0) e = D.rhow[c];
-            if (!multi) pm = pmir_load(D.pmir, P);
-        }
-    }
-    // pulls; a bounce-back link takes the cell's own opposite population instead (the
-    // source address is selected, so every population is one load).  The planes q and
-    // opp(q) share the base of the lower one.
-    float fi[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) fi[q] = 0.f;
-    if (in_mask(act)) {  // lanes without a liquid cell load nothing
-        const unsigned c4 = (unsigned)c * ES, S4 = (unsigned)S * ES;
-        if (!Ph.wide) {
-            fi[0] = SS::dec(*at_byte(A, c4), inv);
-            if (any == 0ull) {
-                for_dirs([&](auto qc) {
-                    constexpr int q = decltype(qc)::value;
-                    fi[q] = SS::dec(*at_byte(A + q * S, c4 + (unsigned)src_off<q>(so) * ES), inv);
-                });
-            } else {
-                for_dirs([&](auto qc) {
-                    constexpr int q = decltype(qc)::value;
-                    constexpr int lo = q < opp(q) ? q : opp(q);
-                    const unsigned pull = c4 + (unsigned)src_off<q>(so) * ES + (unsigned)(q - lo) * S4;
-                    unsigned o = in_mask(bb[q]) ? c4 + (unsigned)(opp(q) - lo) * S4 : pull;
-                    __asm__("" : "+v"(o));
-                    fi[q] = SS::dec(*at_byte(A + lo * S, o), inv);
-                });
-            }
+            for (int q = 1; q < Q; ++q) link |= sm[q];
         } else {
-            fi[0] = SS::ld(A + (unsigned)c, inv);
-            for_dirs([&](auto qc) {
-                constexpr int q = decltype(qc)::value;
-                const bool b = in_mask(bb[q]);
-                fi[q] = SS::ld((b ? A + opp(q) * S : A + q * S) + (unsigned)(b ? c : c + src_off<q>(so)), inv);
-            });
+#pragma unroll
+            for (int q = 1; q < Q; ++q) sm[q] = 0ull;
         }
-    }
-    // particle ids of plane z+2 for the ring (its cell types were loaded before)
-    if (next) pre_pids(D.pid, SI, R, zo2);
-    if (linked) {
-        const float rho_t = rhow_valid(e, D.st_prev) ? __uint_as_float(e) : own_density<ST>(Av, S, c, inv);
-        if (!multi)
-            march_links<PER, ST == ST_F32 && PER>(G, D, L, P, pm, [&](int q) { return in_mask(sm[q]); }, rho_t, x, y, z, fi,
-                                                  curP, curS);
-        else {
-            // links into more than one particle, or an inconsistent owner (rare): one
-            // particle at a time
-            auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };
-            uint32_t rest = 0;
+        // the particle P of the particle-node links and whether some link leads to another:
+        // over the 18 staged ids (-1 at every cell that is no particle node) the smallest as
+        // an unsigned value and the largest as a signed one agree exactly when every
+        // particle node among them has the same id
+        if (link) {
+            auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };  // plane z - c_z
+            unsigned pmin = 0xffffffffu;
+            int pmax = -1;
 #pragma unroll
-            for (int q = 1; q < Q; ++q) rest |= (uint32_t)in_mask(sm[q]) << q;
-            while (rest) {
-                const int q0 = __ffs(rest) - 1;
-                int Pk = -1;
-#pragma unroll
-                for (int q = 1; q < Q; ++q)
-                    if (q == q0) Pk = L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)];
-                uint32_t mk = 0;
-#pragma unroll
-                for (int q = 1; q < Q; ++q)
-                    mk |= (uint32_t)(((rest >> q) & 1u) && L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)] == Pk) << q;
-                rest &= ~mk;
-                if ((unsigned)Pk >= (unsigned)D.np) {  // not a particle: plain bounce-back
-                    atomicOr(D.err, ERR_LG);
-                    continue;
+            for (int q = 1; q < Q; ++q) {
+                const int p = L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)];
+                pmin = min(pmin, (unsigned)p);
+                pmax = max(pmax, p);
+            }
+            if (in_mask(link)) {
+                P = (int)pmin;
+                multi = (int)pmin != pmax || (unsigned)P >= (unsigned)M.D.np;
+                // rho_w of Eq. bbrule: the density of this cell at t, as the launch before
+                // stored it
+                if (M.D.rhow != nullptr && M.D.st_prev >= 0) e = M.D.rhow[c];
+                if (!multi) pm = pmir_load(M.D.pmir, P);
+            }
+        }
+        // sources beyond resting faces, by component (the row's y and the plane's z are
+        // uniform)
+        const unsigned long long wy0 = !G.per[1] && y == 0 ? act : 0ull, wy1 = !G.per[1] && y == G.ny - 1 ? act : 0ull;
+        const unsigned long long wz0 = !G.per[2] && z == 0 ? act : 0ull, wz1 = !G.per[2] && z == G.nz - 1 ? act : 0ull;
+        wx0 &= act;
+        wx1 &= act;
+        auto bounce = [&](auto qc) {  // the lanes that bounce back along q
+            constexpr int q = decltype(qc)::value;
+            return sm[q] | (cx(q) == 1 ? wx0 : cx(q) == -1 ? wx1 : 0ull) | (cy(q) == 1 ? wy0 : cy(q) == -1 ? wy1 : 0ull) |
+                   (cz(q) == 1 ? wz0 : cz(q) == -1 ? wz1 : 0ull);
+        };
+        // pulls; a bounce-back link takes the cell's own opposite population instead (the
+        // source address is selected, so every population is one load).  The planes q and
+        // opp(q) share the base of the lower one.
+        if (in_mask(act)) {  // lanes without a liquid cell load nothing
+            const unsigned c4 = (unsigned)c * ES, S4 = (unsigned)S * ES;
+            if (!M.Ph.wide) {
+                fi[0] = SS::dec(*at_byte(A, c4), inv);
+                if ((link | wx0 | wx1 | wy0 | wy1 | wz0 | wz1) == 0ull) {
+                    for_dirs([&](auto qc) {
+                        constexpr int q = decltype(qc)::value;
+                        fi[q] = SS::dec(*at_byte(A + q * S, c4 + (unsigned)src_off<q>(so) * ES), inv);
+                    });
+                } else {
+                    for_dirs([&](auto qc) {
+                        constexpr int q = decltype(qc)::value;
+                        constexpr int lo = q < opp(q) ? q : opp(q);
+                        const unsigned pull = c4 + (unsigned)src_off<q>(so) * ES + (unsigned)(q - lo) * S4;
+                        unsigned o = in_mask(bounce(qc)) ? c4 + (unsigned)(opp(q) - lo) * S4 : pull;
+                        __asm__("" : "+v"(o));
+                        fi[q] = SS::dec(*at_byte(A + lo * S, o), inv);
+                    });
                 }
-                march_links<PER, ST == ST_F32>(G, D, L, Pk, pmir_load(D.pmir, Pk),
-                                               [&](int q) { return ((mk >> q) & 1u) != 0u; }, rho_t, x, y, z, fi, curP,
-                                               curS);
+            } else {
+                fi[0] = SS::ld(A + (unsigned)c, inv);
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    const bool b = in_mask(bounce(qc));
+                    fi[q] = SS::ld((b ? A + opp(q) * S : A + q * S) + (unsigned)(b ? c : c + src_off<q>(so)), inv);
+                });
+            }
+        }
+        // particle ids of plane z+2 for the ring (its cell types were loaded before)
+        if (next) pre_pids(M.D.pid, SI, R, zo2);
+    }
+    if (link) {
+        // the masks are formed again rather than held over the pulls (36 scalars)
+        __asm__ volatile("" ::: "memory");
+        const MarchArgs &M = march_args();
+        unsigned long long sm[Q];
+        solid_masks(L, sm1, s0, sp1, ly, act, sm);
+        if (in_mask(link)) {
+            const float rho_t = rhow_valid(e, M.D.st_prev) ? __uint_as_float(e)
+                                                           : own_density<ST>(M.D.fA, M.G.S, c, M.Ph.inv);
+            if (!multi) {
+                march_links<PER, ST == ST_F32 && PER>(M.G, M.D, L, P, pm, [&](int q) { return in_mask(sm[q]); }, rho_t, x,
+                                                      y, z, fi, curP, curS);
+            } else {
+                // links into more than one particle, or an inconsistent owner (rare): one
+                // particle at a time
+                auto slot = [&](int q) { return cz(q) == 1 ? sm1 : (cz(q) == -1 ? sp1 : s0); };
+                uint32_t rest = 0;
+#pragma unroll
+                for (int q = 1; q < Q; ++q) rest |= (uint32_t)in_mask(sm[q]) << q;
+                while (rest) {
+                    const int q0 = __ffs(rest) - 1;
+                    int Pk = -1;
+#pragma unroll
+                    for (int q = 1; q < Q; ++q)
+                        if (q == q0) Pk = L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)];
+                    uint32_t mk = 0;
+#pragma unroll
+                    for (int q = 1; q < Q; ++q)
+                        mk |= (uint32_t)(((rest >> q) & 1u) && L.pt[slot(q)][ly + 1 - cy(q)][lx + 1 - cx(q)] == Pk) << q;
+                    rest &= ~mk;
+                    if ((unsigned)Pk >= (unsigned)M.D.np) {  // not a particle: plain bounce-back
+                        atomicOr(M.D.err, ERR_LG);
+                        continue;
+                    }
+                    march_links<PER, ST == ST_F32>(M.G, M.D, L, Pk, pmir_load(M.D.pmir, Pk),
+                                                   [&](int q) { return ((mk >> q) & 1u) != 0u; }, rho_t, x, y, z, fi,
+                                                   curP, curS);
+                }
             }
         }
     }
-    const Moments M = cell_moments(fi);
-    if (D.rhow != nullptr && D.st_cur >= 0 && store) {
+    const MarchArgs &M = march_args();
+    const Moments Mo = cell_moments(fi);
+    if (M.D.rhow != nullptr && M.D.st_cur >= 0 && store) {
         // the density for a liquid cell, none for the row's other cells
-        const unsigned w = in_mask(act) ? rhow_word(1.0f + (float)M.drho, D.st_cur) : RHOW_NONE;
-        __builtin_nontemporal_store(w, D.rhow + c);
+        const unsigned w = in_mask(act) ? rhow_word(1.0f + (float)Mo.drho, M.D.st_cur) : RHOW_NONE;
+        __builtin_nontemporal_store(w, M.D.rhow + c);
     }
-    if (!collide_store<ST, true>(Ph, fi, M, B, S, (unsigned)c, store) && in_mask(act)) atomicOr(D.err, ERR_NAN);
+    if (!collide_store<ST, true>(M.Ph, fi, Mo, (T *)M.D.fB, M.G.S, (unsigned)c, store) && in_mask(act))
+        atomicOr(M.D.err, ERR_NAN);
 }
 
 // tiles of the march: blocks go to the eight XCDs round-robin; each XCD takes whole
@@ -1105,16 +1142,19 @@ __device__ __forceinline__ void march_of_block(int b, int nCols, int nChunks, in
 // the column that holds one is appended to the list gen.
 template <int ST, bool MW, bool PER>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))) void k_stream_collide(
-    Geom G, Phys Ph, Dev D, int tilesX, int tilesY, int nChunks, int nzc, int *gen, int *ngen) {
+    MarchArgs) {
     __shared__ MarchLds L;
+    const MarchArgs &M = march_args();
+    const Geom &G = M.G;
+    const Dev &D = M.D;
     if (blockIdx.x == 0 && D.counters_nxt) {  // nothing reads these before the next step
         if (threadIdx.x < C_COUNT) D.counters_nxt[threadIdx.x] = 0;
         if (threadIdx.x < 18 && D.wallF_nxt) D.wallF_nxt[threadIdx.x] = 0.0;
     }
     int col, chunk;
-    march_of_block(blockIdx.x, tilesX * tilesY, nChunks, col, chunk);
-    const int x0 = (col % tilesX) * TX, y0 = (col / tilesX) * TY;
-    const int zs = chunk * nzc, ze = min(zs + nzc, G.nz);
+    march_of_block(blockIdx.x, M.tilesX * M.tilesY, M.nChunks, col, chunk);
+    const int x0 = (col % M.tilesX) * TX, y0 = (col / M.tilesX) * TY;
+    const int zs = chunk * M.nzc, ze = min(zs + M.nzc, G.nz);
     const int lane = threadIdx.x & 63, wv = (int)uni32(threadIdx.x >> 6);
     const int lx = lane, ly = wv;
     const int x = x0 + lx, y = y0 + ly;
@@ -1149,20 +1189,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
     for (int z = zs; z < ze; ++z) {
         // the ring's next plane z+2: cell types now, particle ids once the pulls of this
         // plane are issued
+        const MarchArgs &M = march_args();
+        const Geom &G = M.G;
         const bool next = z + 1 < ze;
         const int zo2 = stage_zo(G, z + 2);
-        if (next) pre_flags(D.flags, SI, R, zo2);
+        if (next) pre_flags(M.D.flags, SI, R, zo2);
         const int s0 = z & 3, sm1 = (z - 1) & 3, sp1 = (z + 1) & 3;
         // values the compiler would otherwise keep for the whole march (per-direction
         // address terms of the lane, plane bases): recomputed in every plane instead
         int xl = x;
-        long long Sl = G.S;
         __asm__ volatile("" : "+v"(xl));
         // the lane's cell for addresses (lanes beyond the box take the last one)
         const int xc = min(xl, G.nx - 1), yc = min(y, G.ny - 1);
-        __asm__ volatile("" : "+s"(Sl));
-        const void *Av = D.fA;
-        void *Bv = D.fB;
         unsigned an = uni32(*(const unsigned *)L.any[sm1] | *(const unsigned *)L.any[s0] | *(const unsigned *)L.any[sp1]);
         an |= an >> 16;
         an |= an >> 8;
@@ -1188,24 +1226,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
             so.zm = step_to(z, -1, G.nz, G.per[2], nxy);
             so.zp = step_to(z, 1, G.nz, G.per[2], nxy);
             const int c = xc + (G.nx * yc + nxy * z);
-            march_cell<ST, PER>(G, Ph, D, L, sm1, s0, sp1, lx, ly, xl, y, z, c, so, act, in_mask(inb & ~gen_m),
-                                (an & AN_SOL) != 0u, wx0, wx1, Av, Bv, Sl, SI, R, zo2, next, curP, curS);
+            march_cell<ST, PER>(L, sm1, s0, sp1, lx, ly, xl, y, z, c, so, act, in_mask(inb & ~gen_m), (an & AN_SOL) != 0u,
+                                wx0, wx1, SI, R, zo2, next, curP, curS);
         } else if (next) {
-            pre_pids(D.pid, SI, R, zo2);
+            pre_pids(M.D.pid, SI, R, zo2);
         }
         if (next) pre_store(L, R, (z + 2) & 3, MW, dirty);
         __syncthreads();
         if (threadIdx.x == 0 && L.genflag[z & 1]) {
             L.genflag[z & 1] = 0;
-            const int slot = atomicAdd(ngen, 1);
-            gen[slot] = col + tilesX * tilesY * z;  // list capacity: every tile of the box
+            const int slot = atomicAdd(M.ngen, 1);
+            M.gen[slot] = col + M.tilesX * M.tilesY * z;  // list capacity: every tile of the box
         }
     }
     // the block's link sums, an atomic per sphere and component
-    if (D.np > 0) {
+    const MarchArgs &Me = march_args();
+    if (Me.D.np > 0) {
         const int t = threadIdx.x, P = L.tag[t];
         if (P >= 0) {
-            double *dst = D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
+            double *dst = Me.D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
 #pragma unroll
             for (int k = 0; k < 7; ++k) unsafeAtomicAdd(dst + k, L.acc[k][t]);
         }
