@@ -305,16 +305,24 @@ void set_phys(fsl_ctx *c) {
 // general path over the tiles it listed (interface cells, liquid cells next to gas or
 // a moving or slipping face)
 template <int ST, bool MW, bool PER>
-void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
+void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv, const SolidArgs &SA) {
     int *glist = (int *)(c->xs + c->L.glist), *ngen = Dv.counters + C_NGEN;
-    // planes per block: the device holds four blocks per compute unit at once, a block costs
-    // its planes and about two more for staging the first three; the number of planes (at
-    // most NZC) with the fewest plane times over the rounds of blocks
-    const long long cols = (long long)c->tilesX * c->tilesY;
+    // Planes per block, k of 1 .. NZC: the device holds D = 4 blocks per compute unit at once;
+    // a block costs its planes and about half a plane for staging the first three.  Blocks
+    // differ in cost (rows with particle links against gas), so that a launch of r = blocks / D
+    // rounds takes about max(r + 1/2, ceil r) times a block, not ceil r: thin blocks on
+    // boxes of a few rounds (128^3 bed, us a launch: 2 planes 105, 3: 106, 4: 111, 8: 111, 10:
+    // 117, 16: 150; 114 x 116 x 180 suspension: 2: 168, 3: 164, 5: 167, 8: 190, 12: 178), thick
+    // ones on large boxes.  Powers of two beyond 2 are left out, 6 % slower where the box is
+    // one too (384 x 256 x 512, us: 3: 1564, 4: 1631, 6: 1518, 8: 1609, 10: 1519, 12: 1513, 14: 1529,
+    // 16: 1605), and so are odd numbers, 2 to 4 % slower on the 512 x 512 x 1024 column (ms, 10 to
+    // 15: 10.29, 10.57, 10.17, 10.49, 10.12, 10.45).
+    const long long cols = (long long)c->tilesX * c->tilesY, dev = 4ll * c->cus;
     int nzc = 1;
     long long best = 0;
-    for (int k = 1; k <= NZC; ++k) {
-        const long long blocks = cols * ((c->G.nz + k - 1) / k), t = (blocks + 4 * c->cus - 1) / (4 * c->cus) * (k + 2);
+    for (int k : {1, 2, 3, 6, 10, 12, NZC}) {
+        const long long blocks = cols * ((c->G.nz + k - 1) / k);
+        const long long t = std::max(2 * blocks + dev, 2 * dev * ((blocks + dev - 1) / dev)) * (2 * k + 1);
         if (best == 0 || t <= best) {
             best = t;
             nzc = k;
@@ -323,27 +331,34 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv) {
     const int nChunks = (c->G.nz + nzc - 1) / nzc;
     hipLaunchKernelGGL((k_stream_collide<ST, MW, PER>), dim3(c->tilesX * c->tilesY * nChunks), dim3(256), 0, c->st,
                        MarchArgs{c->G, c->Ph, Dv, c->tilesX, c->tilesY, nChunks, nzc, glist, ngen});
-    if (!c->gas && !MW) return;  // the list is empty
-    hipLaunchKernelGGL((k_general<ST, MW>), dim3(std::min(c->nTiles, 4096)), dim3(256), 0, c->st, c->G, c->Ph, Dv,
-                       c->tilesX, c->tilesY, (const int *)glist, (const int *)ngen);
+    const int gb = !c->gas && !MW ? 0 : std::min(c->nTiles, 4096);  // 0: the list is empty
+    if (SA.n && gb)
+        hipLaunchKernelGGL((k_general_links<ST, MW>), dim3(SA.n + gb), dim3(256), 0, c->st, c->G, c->Ph, Dv, c->tilesX,
+                           c->tilesY, (const int *)glist, (const int *)ngen, SA);
+    else if (SA.n)
+        hipLaunchKernelGGL(k_solid_links, dim3(SA.n), dim3(256), 0, c->st, c->G, c->Ph, Dv, SA);
+    else if (gb)
+        hipLaunchKernelGGL((k_general<ST, MW>), dim3(gb), dim3(256), 0, c->st, c->G, c->Ph, Dv, c->tilesX, c->tilesY,
+                           (const int *)glist, (const int *)ngen);
 }
+// SA: the solid links to take along (n = 0: none)
 template <int ST>
-void launch_stream_collide(fsl_ctx *c, const Dev &Dv) {
+void launch_stream_collide(fsl_ctx *c, const Dev &Dv, const SolidArgs &SA = SolidArgs{}) {
     // the lever arms of particle links take nearest images only on boxes with a
     // periodic axis
     const bool per = c->G.per[0] || c->G.per[1] || c->G.per[2];
     if (c->Ph.moving_walls) {
-        if (per) launch_stream_collide_mw<ST, true, true>(c, Dv);
-        else launch_stream_collide_mw<ST, true, false>(c, Dv);
+        if (per) launch_stream_collide_mw<ST, true, true>(c, Dv, SA);
+        else launch_stream_collide_mw<ST, true, false>(c, Dv, SA);
     } else {
-        if (per) launch_stream_collide_mw<ST, false, true>(c, Dv);
-        else launch_stream_collide_mw<ST, false, false>(c, Dv);
+        if (per) launch_stream_collide_mw<ST, false, true>(c, Dv, SA);
+        else launch_stream_collide_mw<ST, false, false>(c, Dv, SA);
     }
 }
 
 template <int ST> int enqueue_steps(fsl_ctx *c, int n);
-template <int ST> int enqueue_integration(fsl_ctx *c);
-template <int ST> int enqueue_pair_forces(fsl_ctx *c);
+template <int ST> int enqueue_integration(fsl_ctx *c, bool conversions);
+template <int ST> int enqueue_pair_forces(fsl_ctx *c, bool joined);
 template <int ST> int enqueue_coverage_step(fsl_ctx *c);
 template <int ST> int enqueue_coverage_full(fsl_ctx *c);
 template <int ST> int enqueue_bubbles(fsl_ctx *c, double *phi, int init, int test);
@@ -436,25 +451,44 @@ int enqueue_coverage_step(fsl_ctx *c) {
     return FSL_OK;
 }
 
+// Small tables: launches of independent work put into one (each costs 4.5 us and, alone,
+// leaves the device idle): pairs beside face forces, sphere links beside the general path, the
+// particle update beside the conversions.  Per-phase timing takes them apart.
+bool joined_phases(const fsl_ctx *c) { return c->D.np > 0 && c->D.np <= INT_BLOCK_MAX && !c->profiling; }
+
+// face forces of the state at t and a small table's candidate pairs (positions at t)
 template <int ST>
-int enqueue_particles(fsl_ctx *c) {
-    int rc = enqueue_pair_forces<ST>(c);
-    if (rc || !c->cfg.integrate) return rc;
-    rc = enqueue_integration<ST>(c);
-    if (rc) return rc;
-    return enqueue_coverage_step<ST>(c);
+int enqueue_before(fsl_ctx *c) {
+    Dev &D = c->D;
+    const bool faces = c->FS.n > 0 && D.wallF, pairs = D.np > 0 && D.np <= PAIRS_DIRECT;
+    const PairsDirect PD = pairs_direct_of(c->PG, c->L.pcap, D.np);
+    const int nb = faces ? grid_for(c->FS.start[c->FS.n] / c->FS.n, 256, 512) : 0;
+    const int nf = nb * c->FS.n;
+    if (faces && pairs && joined_phases(c)) {
+        hipLaunchKernelGGL(k_before<ST>, dim3(nf + PD.n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, nb, PD);
+    } else {
+        if (faces) hipLaunchKernelGGL(k_before<ST>, dim3(nf), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, nb, PD);
+        if (pairs) {
+            ProfScope ps(c, 3);
+            hipLaunchKernelGGL(k_before<ST>, dim3(PD.n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, 0, PD);
+        }
+    }
+    LAUNCHCHK(c);
+    return FSL_OK;
 }
 
+SolidArgs solid_args_of(const fsl_ctx *c) {
+    return solid_args(c->L.pcap, c->D.np, !c->G.per[0] || !c->G.per[1] || !c->G.per[2]);
+}
+
+// joined: the links between spheres went with the lattice update
 template <int ST>
-int enqueue_pair_forces(fsl_ctx *c) {
+int enqueue_pair_forces(fsl_ctx *c, bool joined) {
     Dev &D = c->D;
     const int np = D.np;
     ProfScope ps(c, 3);
     // candidate pairs (positions at t): particle-particle links and lubrication
-    if (np <= PAIRS_DIRECT) {
-        hipLaunchKernelGGL(k_pairs_direct, dim3((np + PDIR_P - 1) / PDIR_P, (np + 255) / 256), dim3(256), 0, c->st, D,
-                           c->PG, c->L.pcap);
-    } else {
+    if (np > PAIRS_DIRECT) {
         hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(c->ncell)), dim3(256), 0, c->st, D, c->ncell);
         hipLaunchKernelGGL(k_grid_count, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
         const int chunk = std::max(256, (c->ncell + 1023) / 1024 + 255) / 256 * 256;
@@ -466,21 +500,19 @@ int enqueue_pair_forces(fsl_ctx *c) {
         hipLaunchKernelGGL(k_grid_fill, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
         hipLaunchKernelGGL(k_pairs, dim3(grid_for((long long)np * 27, 256, 2048)), dim3(256), 0, c->st, D, c->PG, c->L.pcap);
     }
-    const bool faces = !c->G.per[0] || !c->G.per[1] || !c->G.per[2];
-    const int chunk = np <= INT_BLOCK_MAX ? 1 : 8;
-    // two waves per group of listed pairs (a few per sphere as a rule), a wave per group of
-    // spheres
-    const int pb = grid_for(4LL * np, 2 * chunk, 8192);
-    hipLaunchKernelGGL(k_solid_links, dim3(pb + (faces ? (np + 4 * chunk - 1) / (4 * chunk) : 0)), dim3(256), 0, c->st,
-                       c->G, c->Ph, D, c->L.pcap, pb, chunk);
+    if (!joined) {
+        const SolidArgs SA = solid_args_of(c);
+        hipLaunchKernelGGL(k_solid_links, dim3(SA.n), dim3(256), 0, c->st, c->G, c->Ph, D, SA);
+    }
     hipLaunchKernelGGL(k_part_forces, dim3(std::min(2048, np <= 2048 ? (np + 3) / 4 : (np + 15) / 16)), dim3(256), 0,
                        c->st, D, c->cfg.integrate && np > INT_BLOCK_MAX);
     LAUNCHCHK(c);
     return FSL_OK;
 }
 
+// conversions: the step's conversions in the same launch (fused_phases, small tables)
 template <int ST>
-int enqueue_integration(fsl_ctx *c) {
+int enqueue_integration(fsl_ctx *c, bool conversions) {
     Dev &D = c->D;
     const int np = D.np;
     ProfScope ps(c, 4);
@@ -490,12 +522,15 @@ int enqueue_integration(fsl_ctx *c) {
     for (int a = 0; a < 3; ++a)
         if (c->cfg.boundary[a] == FSL_NOSLIP) wmask |= 1 << a;
     if (np <= INT_BLOCK_MAX) {
-        if (np <= 1024)
-            hipLaunchKernelGGL(k_integrate_block<1>, dim3(1), dim3(1024), 0, c->st, c->G, D, ns, mu, c->cfg.contact_k,
-                               c->L.pcap, c->cfg.g[0], c->cfg.g[1], c->cfg.g[2], c->have_prev, wmask);
-        else
-            hipLaunchKernelGGL(k_integrate_block<2>, dim3(1), dim3(1024), 0, c->st, c->G, D, ns, mu, c->cfg.contact_k,
-                               c->L.pcap, c->cfg.g[0], c->cfg.g[1], c->cfg.g[2], c->have_prev, wmask);
+        const IntArgs A{ns, mu, c->cfg.contact_k, c->L.pcap, {c->cfg.g[0], c->cfg.g[1], c->cfg.g[2]}, c->have_prev, wmask};
+        const dim3 g(int_blocks(np)), gc(SYNC_BIG + int_blocks(np)), b(1024);
+        if (conversions) {
+            if (np <= 1024) hipLaunchKernelGGL((k_conv_integrate<ST, 1>), gc, b, 0, c->st, c->G, c->Ph, D, A);
+            else hipLaunchKernelGGL((k_conv_integrate<ST, 2>), gc, b, 0, c->st, c->G, c->Ph, D, A);
+        } else {
+            if (np <= 1024) hipLaunchKernelGGL(k_integrate<1>, g, b, 0, c->st, c->G, D, A);
+            else hipLaunchKernelGGL(k_integrate<2>, g, b, 0, c->st, c->G, D, A);
+        }
     } else {
         for (int s = 0; s < ns; ++s) {
             hipLaunchKernelGGL(k_lub, dim3(grid_for(c->L.pcap, 256, 1024)), dim3(256), 0, c->st, c->G, D, mu,
@@ -527,9 +562,9 @@ int enqueue_steps(fsl_ctx *c, int n) {
     for (int s = 0; s < n; ++s) {
         Dev &D = c->D;
         if (!c->counters_clear) hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, D);
-        if (c->FS.n > 0 && D.wallF)  // face forces from the state at t
-            hipLaunchKernelGGL(k_wall_forces<ST>, dim3(grid_for(c->FS.start[c->FS.n] / c->FS.n, 256, 512), c->FS.n),
-                               dim3(256), 0, c->st, c->G, c->Ph, D, c->FS);
+        int rc = enqueue_before<ST>(c);
+        if (rc) return rc;
+        const bool joined = joined_phases(c);
         if (D.kappa && c->gas) {  // curvature of the interface at t for the Laplace jump
             ProfScope ps(c, 6);
             enqueue_curvature(c, D.counters + C_NKT);
@@ -543,7 +578,7 @@ int enqueue_steps(fsl_ctx *c, int n) {
         D.st_cur = c->stamp;
         {
             ProfScope ps(c, 0);
-            launch_stream_collide<ST>(c, D);
+            launch_stream_collide<ST>(c, D, joined ? solid_args_of(c) : SolidArgs{});
         }
         LAUNCHCHK(c);
         if (++c->stamp >= (1 << 30)) {  // restart the stamps on entries that all read 0
@@ -555,10 +590,15 @@ int enqueue_steps(fsl_ctx *c, int n) {
         } else {
             c->rhow_ok = 1;
         }
-        int rc = c->gas ? enqueue_conversions<ST>(c) : FSL_OK;
-        if (rc) return rc;
+        const bool conv = c->gas, both = conv && joined && c->cfg.integrate && fused_phases(c);
+        if (conv && !both) {
+            rc = enqueue_conversions<ST>(c);
+            if (rc) return rc;
+        }
         if (D.np > 0) {
-            rc = enqueue_particles<ST>(c);
+            rc = enqueue_pair_forces<ST>(c, joined);
+            if (!rc && c->cfg.integrate) rc = enqueue_integration<ST>(c, both);
+            if (!rc && c->cfg.integrate) rc = enqueue_coverage_step<ST>(c);
             if (rc) return rc;
         }
         if (c->gas) {

@@ -340,9 +340,9 @@ __global__ __launch_bounds__(256) void k_conv_fill(Geom G, Phys Ph, Dev D) {
 // block a fraction of one and a grid barrier about three.  As many blocks take part as the
 // lists fill, two cells per half wave; the others leave.
 template <int ST>
-__global__ __launch_bounds__(1024) void k_conversions(Geom G, Phys Ph, Dev D) {
+__device__ __forceinline__ void conversions(const Geom &G, const Phys &Ph, const Dev &D, int nmax) {
     const int n = list_len(D, C_NF) + list_len(D, C_NE0);
-    const int nblk = min((int)gridDim.x, (n + 63) / 64);
+    const int nblk = min(nmax, (n + 63) / 64);
     if ((int)blockIdx.x >= nblk) return;
     GridBarrier B{D.counters + C_BAR, nblk, 0, D.err};
     const Items W(blockIdx.x, nblk);
@@ -352,6 +352,10 @@ __global__ __launch_bounds__(1024) void k_conversions(Geom G, Phys Ph, Dev D) {
     B.wait();
     conv_fill<ST>(G, Ph, D, W, blockIdx.x * blockDim.x + threadIdx.x, nblk * blockDim.x);
     if (last_block(D.counters + C_DONEC, nblk) && threadIdx.x == 0) merge_bubbles(D);
+}
+template <int ST>
+__global__ __launch_bounds__(1024) void k_conversions(Geom G, Phys Ph, Dev D) {
+    conversions<ST>(G, Ph, D, gridDim.x);
 }
 
 // ---- bubble volumes: dense pass over the cell types ------------------------------

@@ -312,16 +312,25 @@ __global__ __launch_bounds__(256) void k_pairs(Dev D, PGrid PG, int pcap) {
 
 // Small tables (up to PAIRS_DIRECT spheres): every pair tested, in one launch instead of the
 // seven that build and walk the grid (4.6 us each whatever the size).  A block takes
-// PDIR_P spheres (x) against 256 later ones (y), one per thread, so that the launch is one
+// PDIR_P spheres against 256 later ones, one per thread, so that the launch is one
 // round of loads deep.  A first test in FP32 on the axes' distances (nearest images of
 // centres in [0, n); half a cell of slack, far beyond the rounding of coordinates below
 // 2^16) leaves the distance itself to the near ones.
 constexpr int PAIRS_DIRECT = 2048, PDIR_P = 16;
-__global__ __launch_bounds__(256) void k_pairs_direct(Dev D, PGrid PG, int pcap) {
+struct PairsDirect {
+    PGrid PG;
+    int pcap, nx, n;  // blocks: nx along the spheres, n in all
+};
+inline PairsDirect pairs_direct_of(const PGrid &PG, int pcap, int np) {
+    const int nx = (np + PDIR_P - 1) / PDIR_P;
+    return {PG, pcap, nx, nx * ((np + 255) / 256)};
+}
+__device__ __forceinline__ void pairs_direct(const Dev &D, const PairsDirect &A, int b) {
     __shared__ PairLds L;
     __shared__ float c[PDIR_P][4];
-    const int P0 = blockIdx.x * PDIR_P, n = min(PDIR_P, D.np - P0);
-    const int Q0 = blockIdx.y * 256;
+    const PGrid &PG = A.PG;
+    const int P0 = b % A.nx * PDIR_P, n = min(PDIR_P, D.np - P0);
+    const int Q0 = b / A.nx * 256;
     if (Q0 + 255 <= P0) return;  // every sphere of the chunk comes before
     if (threadIdx.x == 0) L.cnt = 0;
     if ((int)threadIdx.x < 4 * n) {
@@ -341,10 +350,13 @@ __global__ __launch_bounds__(256) void k_pairs_direct(Dev D, PGrid PG, int pcap)
         const float d0 = apart(y0 - c[p][0], 0), d1 = apart(y1 - c[p][1], 1), d2 = apart(y2 - c[p][2], 2);
         const float r = c[p][3] + yr;
         if (P0 + p < Qp && Qp < D.np && d0 * d0 + d1 * d1 + d2 * d2 < r * r)
-            pair_test(D, PG, L, P0 + p, D.ptab + (long long)(P0 + p) * P_STRIDE, Qp, y, pcap);
+            pair_test(D, PG, L, P0 + p, D.ptab + (long long)(P0 + p) * P_STRIDE, Qp, y, A.pcap);
     }
-    pairs_flush(D, L, pcap);
+    pairs_flush(D, L, A.pcap);
 }
+
+// tables of up to INT_BLOCK_MAX spheres take the particle update in one launch (integrate)
+constexpr int INT_BLOCK_MAX = 2048;
 
 // Momentum exchange between two particles (Sec. 2.3): a node inside particle P'
 // with a link into particle P contributes with equilibrium populations at rho = 1
@@ -537,12 +549,22 @@ __device__ __forceinline__ void face_links(const Geom &G, const Phys &Ph, const 
 // takes `chunk` of them at a time (at most 64), a lane testing each, and works those that
 // have such links in turn: one on small tables, where the waves are few and a chain of
 // several is latency; eight on large ones, where few of the 1e5 spheres touch anything.
-__global__ __launch_bounds__(256) void k_solid_links(Geom G, Phys Ph, Dev D, int pcap, int pair_blocks, int chunk) {
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if ((int)blockIdx.x < pair_blocks) {
-        const int n = min(D.counters[C_NPAIRS], pcap);
+struct SolidArgs {
+    int pcap, pair_blocks, chunk, n;  // n: blocks in all
+};
+inline SolidArgs solid_args(int pcap, int np, bool faces) {
+    const int chunk = np <= INT_BLOCK_MAX ? 1 : 8;
+    // two waves per group of listed pairs (a few per sphere as a rule), a wave per group of
+    // spheres
+    const int pb = np < 1 ? 0 : std::min(8192, std::max(1, (int)((4LL * np + 2 * chunk - 1) / (2 * chunk))));
+    return {pcap, pb, chunk, pb + (faces ? (np + 4 * chunk - 1) / (4 * chunk) : 0)};
+}
+__device__ __forceinline__ void solid_links(const Geom &G, const Phys &Ph, const Dev &D, const SolidArgs &A, int b) {
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, chunk = A.chunk;
+    if (b < A.pair_blocks) {
+        const int n = min(D.counters[C_NPAIRS], A.pcap);
         // two waves per group of pairs, one for each direction of their links
-        for (int k0 = (blockIdx.x * 2 + (wv >> 1)) * chunk; k0 < n; k0 += pair_blocks * 2 * chunk) {
+        for (int k0 = (b * 2 + (wv >> 1)) * chunk; k0 < n; k0 += A.pair_blocks * 2 * chunk) {
             const int k = k0 + lane;
             const bool has = lane < chunk && k < n;
             const int2 pr = has ? D.pairs[k] : make_int2(0, 0);
@@ -550,14 +572,14 @@ __global__ __launch_bounds__(256) void k_solid_links(Geom G, Phys Ph, Dev D, int
             while (m) {
                 const int l = __ffsll((long long)m) - 1;
                 m &= m - 1ull;
-                const int a = __builtin_amdgcn_readlane(pr.x, l), b = __builtin_amdgcn_readlane(pr.y, l);
-                if (wv & 1) solid_pair(G, D, b, a, k0 + l);
-                else solid_pair(G, D, a, b, k0 + l);
+                const int a = __builtin_amdgcn_readlane(pr.x, l), b2 = __builtin_amdgcn_readlane(pr.y, l);
+                if (wv & 1) solid_pair(G, D, b2, a, k0 + l);
+                else solid_pair(G, D, a, b2, k0 + l);
             }
         }
         return;
     }
-    const int P0 = ((blockIdx.x - pair_blocks) * 4 + wv) * chunk;
+    const int P0 = ((b - A.pair_blocks) * 4 + wv) * chunk;
     const int P = P0 + lane;
     unsigned long long m = __ballot(lane < chunk && P < D.np && touches_face(G, D, min(P, D.np - 1)));
     while (m) {
@@ -566,20 +588,28 @@ __global__ __launch_bounds__(256) void k_solid_links(Geom G, Phys Ph, Dev D, int
         face_links(G, Ph, D, P0 + l);
     }
 }
+__global__ __launch_bounds__(256) void k_solid_links(Geom G, Phys Ph, Dev D, SolidArgs A) {
+    solid_links(G, Ph, D, A, blockIdx.x);
+}
 
 // Pair force of one candidate pair (x, u of each sphere; f: force on sphere 1, sphere 2
 // takes -f).  Contact (the paper gives no contact model; reading): overlapping spheres
 // repel by a linear spring of stiffness kc along the line of centres, -kc (R1 + R2 -
 // |d|) d/|d|.  Eq. (lubrication): only for gaps below Delta_c = 2/3, the gap limited
 // from below by 0.2 Delta_c.  The partner is taken at its nearest periodic image.
-// Returns false when there is no force.
-__device__ __forceinline__ bool pair_force(const Geom &G, const double *x1, const double *u1, double R1,
-                                           const double *x2, const double *u2, double R2, double mu, double kc,
-                                           double f[3]) {
+// Returns false when there is no force.  sR: R1 + R2; lub(): lub_factor of the radii, taken
+// only where the force acts.
+__device__ __forceinline__ double lub_factor(double R1, double R2, double mu) {
+    const double rr = R1 * R2, sR = R1 + R2;
+    return -6.0 * M_PI * mu * (rr * rr) / (sR * sR);
+}
+template <typename Lub>
+__device__ __forceinline__ bool pair_force(const Geom &G, const double *x1, const double *u1, const double *x2,
+                                           const double *u2, double sR, Lub lub, double kc, double f[3]) {
     const double dc = 2.0 / 3.0;
     const double d0 = min_img(x2[0] - x1[0], G.nx, G.per[0]), d1 = min_img(x2[1] - x1[1], G.ny, G.per[1]),
                  d2 = min_img(x2[2] - x1[2], G.nz, G.per[2]);
-    const double sR = R1 + R2, dd = d0 * d0 + d1 * d1 + d2 * d2;
+    const double dd = d0 * d0 + d1 * d1 + d2 * d2;
     f[0] = f[1] = f[2] = 0.0;
     if (dd > (sR + dc) * (sR + dc) * (1.0 + 1e-12)) return false;  // beyond Delta_c: no root taken
     const double dist = sqrt(dd);
@@ -593,8 +623,7 @@ __device__ __forceinline__ bool pair_force(const Geom &G, const double *x1, cons
     if (gap < dc && dist > 0.0) {
         if (gap < 0.2 * dc) gap = 0.2 * dc;
         const double n0 = d0 / dist, n1 = d1 / dist, n2 = d2 / dist;
-        const double rr = R1 * R2;
-        const double coef = -6.0 * M_PI * mu * (rr * rr) / (sR * sR) * (1.0 / gap - 1.0 / dc);
+        const double coef = lub() * (1.0 / gap - 1.0 / dc);
         const double vn = n0 * (u1[0] - u2[0]) + n1 * (u1[1] - u2[1]) + n2 * (u1[2] - u2[2]);
         f[0] += coef * vn * n0;
         f[1] += coef * vn * n1;
@@ -618,12 +647,13 @@ __device__ __forceinline__ void face_force(const Geom &G, int wmask, const doubl
     for (int a = 0; a < 3; ++a) {
         if (!((wmask >> a) & 1)) continue;
         const double hl = x[a] + 0.5, hh = (n[a] - 0.5) - x[a];
+        const double gl = hl - R, gh = hh - R;
+        if (!(fmin(gl, gh) < dc)) continue;  // neither face is near
         if (kc > 0.0) {
             if (hl < R) f[a] += kc * (R - hl);
             if (hh < R) f[a] -= kc * (R - hh);
         }
         const double c = 6.0 * M_PI * mu * R * R;
-        double gl = hl - R, gh = hh - R;
         if (gl < dc) f[a] -= c * (1.0 / fmax(gl, 0.2 * dc) - 1.0 / dc) * u[a];
         if (gh < dc) f[a] -= c * (1.0 / fmax(gh, 0.2 * dc) - 1.0 / dc) * u[a];
     }
@@ -635,7 +665,9 @@ __global__ void k_lub(Geom G, Dev D, double mu, double kc, int pcap) {
         const int a = D.pairs[k].x, b = D.pairs[k].y;
         const double *p1 = D.ptab + (long long)a * P_STRIDE, *p2 = D.ptab + (long long)b * P_STRIDE;
         double f[3];
-        if (!pair_force(G, p1 + P_X, p1 + P_U, p1[P_R], p2 + P_X, p2 + P_U, p2[P_R], mu, kc, f)) continue;
+        const double R1 = p1[P_R], R2 = p2[P_R];
+        if (!pair_force(G, p1 + P_X, p1 + P_U, p2 + P_X, p2 + P_U, R1 + R2, [&] { return lub_factor(R1, R2, mu); }, kc, f))
+            continue;
         unsafeAtomicAdd(D.pFl + 3 * a, f[0]);
         unsafeAtomicAdd(D.pFl + 3 * a + 1, f[1]);
         unsafeAtomicAdd(D.pFl + 3 * a + 2, f[2]);
@@ -651,7 +683,7 @@ __global__ void k_lub(Geom G, Dev D, double mu, double kc, int pcap) {
 // F: F_hyd + m g, du: the change of velocity in a substep without pair and face forces, dw:
 // that of the angular velocity.
 struct SubstepConst {
-    double R, mP, F[3], du[3], dw[3];
+    double R, mP, F[3], du[3];
 };
 __device__ __forceinline__ SubstepConst substep_const(const Dev &D, int P, int have_prev, double dt, const double gg[3]) {
     const double *t = D.ptab + (long long)P * P_STRIDE;
@@ -659,33 +691,46 @@ __device__ __forceinline__ SubstepConst substep_const(const Dev &D, int P, int h
     SubstepConst c;
     c.R = t[P_R];
     c.mP = t[P_RHO] * (4.0 / 3.0) * M_PI * c.R * c.R * c.R;
-    const double IP = 0.4 * c.mP * c.R * c.R;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const double Fh = have_prev ? 0.5 * (FTn[d] + FTp[d]) : FTn[d];
-        const double Th = have_prev ? 0.5 * (FTn[3 + d] + FTp[3 + d]) : FTn[3 + d];
         c.F[d] = Fh + c.mP * gg[d];
         c.du[d] = dt * c.F[d] / c.mP;
-        c.dw[d] = dt * Th / IP;
     }
     return c;
 }
-
-// one semi-implicit Euler substep of a sphere: velocity from F_hyd + m g + F_pair (fl,
-// consumed), then position; angular velocity from T_hyd; the no-slip faces act through
-// face_force at the position and velocity the substep starts from; normal velocity
-// reversed when closer than R to a wall face and moving towards it; along a periodic axis
-// the centre kept in [0, n)
-__device__ __forceinline__ void substep_one(const Geom &G, const SubstepConst &c, double *x, double *u, double *w,
-                                            double *fl, double dt, double mu, double kc, int wmask) {
-    if (wmask) face_force(G, wmask, x, u, c.R, mu, kc, fl);
-    const int n[3] = {G.nx, G.ny, G.nz};
+// n substeps of the angular velocity
+__device__ __forceinline__ void substep_spin(const Dev &D, int P, const SubstepConst &c, int have_prev, double dt, int n,
+                                             double w[3]) {
+    const double *FTn = D.pFT + (long long)P * 6, *FTp = D.pFTp + (long long)P * 6;
+    const double IP = 0.4 * c.mP * c.R * c.R;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        u[d] += fl[d] == 0.0 ? c.du[d] : dt * (c.F[d] + fl[d]) / c.mP;
+        const double Th = have_prev ? 0.5 * (FTn[3 + d] + FTp[3 + d]) : FTn[3 + d];
+        const double dw = dt * Th / IP;
+        for (int s = 0; s < n; ++s) w[d] += dw;
+    }
+}
+
+// one semi-implicit Euler substep of a sphere: velocity from F_hyd + m g + F_pair (fl,
+// consumed), then position; the no-slip faces act through face_force at the position and
+// velocity the substep starts from; normal velocity reversed when closer than R to a wall
+// face and moving towards it; along a periodic axis the centre kept in [0, n)
+__device__ __forceinline__ void substep_one(const Geom &G, const SubstepConst &c, double *x, double *u, double *fl,
+                                            double dt, double mu, double kc, int wmask) {
+    if (wmask) face_force(G, wmask, x, u, c.R, mu, kc, fl);
+    const int n[3] = {G.nx, G.ny, G.nz};
+    double du[3] = {c.du[0], c.du[1], c.du[2]};
+    if (fl[0] != 0.0 || fl[1] != 0.0 || fl[2] != 0.0) {  // the divisions only where a force acts
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            if (fl[d] != 0.0) du[d] = dt * (c.F[d] + fl[d]) / c.mP;
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        u[d] += du[d];
         x[d] += dt * u[d];
         if (G.per[d]) x[d] = wrap_coord(x[d], n[d]);
-        w[d] += c.dw[d];
         if (!G.per[d]) {
             if (x[d] < c.R - 0.5 && u[d] < 0) u[d] = -u[d];
             if (x[d] > n[d] - 0.5 - c.R && u[d] > 0) u[d] = -u[d];
@@ -699,8 +744,9 @@ __global__ void k_substep(Dev D, Geom G, double dt, double g0, double g1, double
     GRID_STRIDE(P, D.np) {
         double *t = D.ptab + (long long)P * P_STRIDE;
         const double gg[3] = {g0, g1, g2};
-        substep_one(G, substep_const(D, P, have_prev, dt, gg), t + P_X, t + P_U, t + P_W, D.pFl + (long long)P * 3, dt,
-                    mu, kc, wmask);
+        const SubstepConst c = substep_const(D, P, have_prev, dt, gg);
+        substep_spin(D, P, c, have_prev, dt, 1, t + P_W);
+        substep_one(G, c, t + P_X, t + P_U, D.pFl + (long long)P * 3, dt, mu, kc, wmask);
         const int n[3] = {G.nx, G.ny, G.nz};
         if (!sphere_supported(t + P_X, t[P_R], n, G.per)) atomicOr(D.err, ERR_PART);
     }
@@ -711,94 +757,228 @@ __device__ __forceinline__ bool moved_far(const Geom &G, const double *x, const 
     return fmax(fabs(min_img(x[0] - xo[0], G.nx, G.per[0])),
                 fmax(fabs(min_img(x[1] - xo[1], G.ny, G.per[1])), fabs(min_img(x[2] - xo[2], G.nz, G.per[2])))) >= 0.5;
 }
-// nodes of the two spheres may lie inside both (see k_cov_flag_init)
-__device__ __forceinline__ bool may_overlap(const Geom &G, const double *a, double Ra, const double *b, double Rb) {
+// nodes of the two spheres may lie inside both (see k_cov_flag_init); sR: sum of the radii
+__device__ __forceinline__ bool may_overlap(const Geom &G, const double *a, const double *b, double sR) {
     const double d0 = min_img(a[0] - b[0], G.nx, G.per[0]), d1 = min_img(a[1] - b[1], G.ny, G.per[1]),
                  d2 = min_img(a[2] - b[2], G.nz, G.per[2]);
-    const double r = Ra + Rb + 1.0;
+    const double r = sR + 1.0;
     return d0 * d0 + d1 * d1 + d2 * d2 < r * r;
 }
 
-// The particle update of a step in one block, for tables of up to INT_BLOCK_MAX spheres:
-// the ns substeps, the coverage flags and the mirror.  A thread keeps its NPT spheres' constants, centres and velocities in registers
-// and shares centres and velocities through LDS, where the pair forces are summed; the
-// first 1,024 pairs stay in registers too, so that a substep reads no global memory (with
-// a launch per half substep, 20 launches: 110 us for 1,400 spheres).  The same arithmetic as
-// k_lub and k_substep.
-constexpr int INT_BLOCK_MAX = 2048;
-template <int NPT>
-__global__ __launch_bounds__(1024) void k_integrate_block(Geom G, Dev D, int ns, double mu, double kc, int pcap,
-                                                          double g0, double g1, double g2, int have_prev,
-                                                          int wmask) {
-    __shared__ double sx[NPT * 1024][3], su[NPT * 1024][3], sf[NPT * 1024][3];
-    const int np = D.np, npair = min(D.counters[C_NPAIRS], pcap);
-    const int tid = threadIdx.x;
-    const double dt = 1.0 / ns, gg[3] = {g0, g1, g2};
-    SubstepConst c[NPT];
-    double w[NPT][3], xo[NPT][3];
+// The particle update of a step, for tables of up to INT_BLOCK_MAX spheres: the ns substeps,
+// the coverage flags and the mirror, in one launch of int_blocks(np) blocks.  Spheres of
+// no listed pair are on their own through all substeps: INT_LONE of them to a block, one per
+// lane of its first wave, all in registers.  The others are block 0's: centres and velocities
+// in LDS, where the pair forces are summed, their constants and those of the first pairs in
+// registers, so that a substep reads no global memory; what bounds it is the chain of one
+// substep (0.9 us without, 1.7 us with acting pairs).  Every block marks the paired spheres from the
+// list for itself.  20 launches, one per half substep, took 110 us for 1,400 spheres
+// with 174 pairs, one block for all of them 48 us, this 23 us.  The same arithmetic as k_lub
+// and k_substep.
+constexpr int INT_LONE = 64;
+inline int int_blocks(int np) { return 1 + (np + INT_LONE - 1) / INT_LONE; }
+struct IntArgs {
+    int ns;
+    double mu, kc;
+    int pcap;
+    double g[3];
+    int have_prev, wmask;
+};
+template <int NPT>  // up to 1,024 NPT spheres
+struct IntLds {
+    unsigned mark[NPT * 32];
+    short before[NPT * 32], slot[NPT * 1024], id[NPT * 1024];
+    double x[NPT * 1024][3], u[NPT * 1024][3], f[NPT * 1024][3];
+};
+// what a sphere's substeps start from, with the angular velocity (which nothing in them
+// reads) taken over all of them
+__device__ __forceinline__ SubstepConst integrate_load(const Dev &D, int P, const IntArgs &A, double dt, double *x,
+                                                       double *u, double *w) {
+    const double *t = D.ptab + (long long)P * P_STRIDE;
+    const SubstepConst c = substep_const(D, P, A.have_prev, dt, A.g);
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int P = tid + 1024 * j;
-        if (P >= np) continue;
-        const double *t = D.ptab + (long long)P * P_STRIDE;
-        c[j] = substep_const(D, P, have_prev, dt, gg);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            xo[j][d] = sx[P][d] = t[P_X + d];
-            su[P][d] = t[P_U + d];
-            w[j][d] = t[P_W + d];
-            sf[P][d] = 0.0;
-        }
+    for (int d = 0; d < 3; ++d) {
+        x[d] = t[P_X + d];
+        u[d] = t[P_U + d];
+        w[d] = t[P_W + d];
     }
-    const bool hp = tid < npair;
-    const int2 pr = hp ? D.pairs[tid] : make_int2(0, 0);
-    const double Ra = hp ? D.ptab[(long long)pr.x * P_STRIDE + P_R] : 0.0, Rb = hp ? D.ptab[(long long)pr.y * P_STRIDE + P_R] : 0.0;
+    substep_spin(D, P, c, A.have_prev, dt, A.ns, w);
+    return c;
+}
+__device__ __forceinline__ void integrate_store(const Geom &G, const Dev &D, int P, double R, const double *x,
+                                                const double *u, const double *w) {
+    double *t = D.ptab + (long long)P * P_STRIDE;
+    const int n[3] = {G.nx, G.ny, G.nz};
+    const double xo[3] = {t[P_X], t[P_X + 1], t[P_X + 2]};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        t[P_XOLD + d] = xo[d];
+        t[P_X + d] = x[d];
+        t[P_U + d] = u[d];
+        t[P_W + d] = w[d];
+    }
+    t[P_OVL] = 0.0;
+    if (moved_far(G, x, xo)) atomicOr(D.counters + C_COVALL, 1);
+    if (!sphere_supported(x, R, n, G.per)) atomicOr(D.err, ERR_PART);
+    mirror_store(D, P, x, u, w);
+}
+template <int NPT>
+__device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const IntArgs &A, int blk) {
+    __shared__ IntLds<NPT> L;
+    const int np = D.np, npair = min(D.counters[C_NPAIRS], A.pcap);
+    const int tid = threadIdx.x;
+    const double dt = 1.0 / A.ns;
+    for (int i = tid; i < NPT * 32; i += 1024) L.mark[i] = 0u;
     __syncthreads();
-    auto pair_add = [&](int a, int b, double R1, double R2) {
+    constexpr int NPR = 2;  // pairs that a thread of block 0 keeps in registers
+    int2 pr[NPR];
+    double Ra[NPR], Rb[NPR];
+    auto mark = [&](int2 q) {
+        atomicOr(&L.mark[q.x >> 5], 1u << (q.x & 31));
+        atomicOr(&L.mark[q.y >> 5], 1u << (q.y & 31));
+    };
+#pragma unroll
+    for (int j = 0; j < NPR; ++j) {
+        const int k = tid + 1024 * j;
+        pr[j] = make_int2(-1, -1);
+        if (k >= npair) continue;
+        pr[j] = D.pairs[k];
+        if (blk == 0) {
+            Ra[j] = D.ptab[(long long)pr[j].x * P_STRIDE + P_R];
+            Rb[j] = D.ptab[(long long)pr[j].y * P_STRIDE + P_R];
+        }
+        mark(pr[j]);
+    }
+    for (int k = tid + 1024 * NPR; k < npair; k += 1024) mark(D.pairs[k]);
+    __syncthreads();
+    if (blk > 0) {
+        const int P = (blk - 1) * INT_LONE + tid;
+        if (tid >= INT_LONE || P >= np || ((L.mark[P >> 5] >> (P & 31)) & 1u)) return;
+        double x[3], u[3], w[3], f[3] = {0.0, 0.0, 0.0};
+        const SubstepConst c = integrate_load(D, P, A, dt, x, u, w);
+        for (int s = 0; s < A.ns; ++s) substep_one(G, c, x, u, f, dt, A.mu, A.kc, A.wmask);
+        integrate_store(G, D, P, c.R, x, u, w);
+        return;
+    }
+    if (npair == 0) return;
+    // the marked spheres' places in LDS
+    if (tid < 64) {
+        const int n = tid < NPT * 32 ? __popc(L.mark[tid]) : 0;
+        int sum = n;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(sum, o);
+            if (tid >= o) sum += v;
+        }
+        if (tid < NPT * 32) L.before[tid] = (short)(sum - n);
+    }
+    __syncthreads();
+    for (int P = tid; P < np; P += 1024)
+        if ((L.mark[P >> 5] >> (P & 31)) & 1u) {
+            const int s = L.before[P >> 5] + __popc(L.mark[P >> 5] & ((1u << (P & 31)) - 1u));
+            L.slot[P] = (short)s;
+            L.id[s] = (short)P;
+        }
+    const int last = NPT * 32 - 1, nm = L.before[last] + __popc(L.mark[last]);
+    __syncthreads();
+    int pa[NPR], pb[NPR];  // their places, sum of radii and lub_factor
+    double sR[NPR], lub[NPR];
+#pragma unroll
+    for (int j = 0; j < NPR; ++j) {
+        pa[j] = -1;
+        if (pr[j].x < 0) continue;
+        pa[j] = L.slot[pr[j].x];
+        pb[j] = L.slot[pr[j].y];
+        sR[j] = Ra[j] + Rb[j];
+        lub[j] = lub_factor(Ra[j], Rb[j], A.mu);
+    }
+    // the constants of the first 1,024 spheres too; the few beyond, on crowded tables, form
+    // theirs again in each substep
+    SubstepConst c;
+    double x[3], u[3], w[3];
+    for (int i = tid; i < nm; i += 1024) {
+        double wi[3];
+        const SubstepConst ci = integrate_load(D, L.id[i], A, dt, L.x[i], L.u[i], wi);
+        if (i == tid) {
+            c = ci;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                w[d] = wi[d];
+                x[d] = L.x[i][d];
+                u[d] = L.u[i][d];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) L.f[i][d] = 0.0;
+    }
+    __syncthreads();
+    auto pair_add = [&](int a, int b, double s, auto l) {
         double f[3];
-        if (!pair_force(G, sx[a], su[a], R1, sx[b], su[b], R2, mu, kc, f)) return;
+        if (!pair_force(G, L.x[a], L.u[a], L.x[b], L.u[b], s, l, A.kc, f)) return;
         for (int d = 0; d < 3; ++d) {
-            atomicAdd(&sf[a][d], f[d]);
-            atomicAdd(&sf[b][d], -f[d]);
+            atomicAdd(&L.f[a][d], f[d]);
+            atomicAdd(&L.f[b][d], -f[d]);
         }
     };
-    for (int s = 0; s < ns; ++s) {
-        if (hp) pair_add(pr.x, pr.y, Ra, Rb);
-        for (int k = tid + 1024; k < npair; k += 1024) {
+    for (int s = 0; s < A.ns; ++s) {
+#pragma unroll
+        for (int j = 0; j < NPR; ++j)
+            if (pa[j] >= 0) pair_add(pa[j], pb[j], sR[j], [&] { return lub[j]; });
+        for (int k = tid + 1024 * NPR; k < npair; k += 1024) {
             const int2 q = D.pairs[k];
-            pair_add(q.x, q.y, D.ptab[(long long)q.x * P_STRIDE + P_R], D.ptab[(long long)q.y * P_STRIDE + P_R]);
+            const double Ra = D.ptab[(long long)q.x * P_STRIDE + P_R], Rb = D.ptab[(long long)q.y * P_STRIDE + P_R];
+            pair_add(L.slot[q.x], L.slot[q.y], Ra + Rb, [&] { return lub_factor(Ra, Rb, A.mu); });
         }
         __syncthreads();
+        for (int i = tid; i < nm; i += 1024) {
+            if (i == tid) {
+                double f[3];
 #pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const int P = tid + 1024 * j;
-            if (P < np) substep_one(G, c[j], sx[P], su[P], w[j], sf[P], dt, mu, kc, wmask);
+                for (int d = 0; d < 3; ++d) {
+                    f[d] = L.f[i][d];
+                    L.f[i][d] = 0.0;
+                }
+                substep_one(G, c, x, u, f, dt, A.mu, A.kc, A.wmask);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    L.x[i][d] = x[d];
+                    L.u[i][d] = u[d];
+                }
+                continue;
+            }
+            substep_one(G, substep_const(D, L.id[i], A.have_prev, dt, A.g), L.x[i], L.u[i], L.f[i], dt, A.mu, A.kc, A.wmask);
         }
         __syncthreads();
     }
-    const int n[3] = {G.nx, G.ny, G.nz};
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int P = tid + 1024 * j;
-        if (P >= np) continue;
-        double *t = D.ptab + (long long)P * P_STRIDE;
-        for (int d = 0; d < 3; ++d) {
-            t[P_XOLD + d] = xo[j][d];
-            t[P_X + d] = sx[P][d];
-            t[P_U + d] = su[P][d];
-            t[P_W + d] = w[j][d];
+    for (int i = tid; i < nm; i += 1024) {
+        if (i >= 1024) {
+            double xi[3], ui[3];
+            c = integrate_load(D, L.id[i], A, dt, xi, ui, w);
         }
-        t[P_OVL] = 0.0;
-        if (moved_far(G, sx[P], xo[j])) atomicOr(D.counters + C_COVALL, 1);
-        if (!sphere_supported(sx[P], c[j].R, n, G.per)) atomicOr(D.err, ERR_PART);
-        mirror_store(D, P, sx[P], su[P], w[j]);
+        integrate_store(G, D, L.id[i], c.R, L.x[i], L.u[i], w);
     }
     block_phase();
-    for (int k = tid; k < npair; k += 1024) {
-        const int2 q = k == tid ? pr : D.pairs[k];
-        double *ta = D.ptab + (long long)q.x * P_STRIDE, *tb = D.ptab + (long long)q.y * P_STRIDE;
-        if (may_overlap(G, sx[q.x], ta[P_R], sx[q.y], tb[P_R])) ta[P_OVL] = tb[P_OVL] = 1.0;
+    auto flag = [&](int2 q, double s) {
+        if (may_overlap(G, L.x[L.slot[q.x]], L.x[L.slot[q.y]], s))
+            D.ptab[(long long)q.x * P_STRIDE + P_OVL] = D.ptab[(long long)q.y * P_STRIDE + P_OVL] = 1.0;
+    };
+#pragma unroll
+    for (int j = 0; j < NPR; ++j)
+        if (pr[j].x >= 0) flag(pr[j], sR[j]);
+    for (int k = tid + 1024 * NPR; k < npair; k += 1024) {
+        const int2 q = D.pairs[k];
+        flag(q, D.ptab[(long long)q.x * P_STRIDE + P_R] + D.ptab[(long long)q.y * P_STRIDE + P_R]);
     }
+}
+template <int NPT>
+__global__ __launch_bounds__(1024) void k_integrate(Geom G, Dev D, IntArgs A) {
+    integrate<NPT>(G, D, A, blockIdx.x);
+}
+// ... beside the conversions of the step, which neither read nor write the sphere table (the
+// first SYNC_BIG blocks; apart 18 and 23 us on a bed of 128^3, together 34)
+template <int ST, int NPT>
+__global__ __launch_bounds__(1024) void k_conv_integrate(Geom G, Phys Ph, Dev D, IntArgs A) {
+    if ((int)blockIdx.x < SYNC_BIG) conversions<ST>(G, Ph, D, SYNC_BIG);
+    else integrate<NPT>(G, D, A, blockIdx.x - SYNC_BIG);
 }
 
 // ---- coverage update --------------------------------------------------------------
@@ -826,7 +1006,7 @@ __global__ void k_cov_flag_pairs(Geom G, Dev D, int pcap) {
     GRID_STRIDE(k, n) {
         const int a = D.pairs[k].x, b = D.pairs[k].y;
         double *ta = D.ptab + (long long)a * P_STRIDE, *tb = D.ptab + (long long)b * P_STRIDE;
-        if (may_overlap(G, ta + P_X, ta[P_R], tb + P_X, tb[P_R])) ta[P_OVL] = tb[P_OVL] = 1.0;
+        if (may_overlap(G, ta + P_X, tb + P_X, ta[P_R] + tb[P_R])) ta[P_OVL] = tb[P_OVL] = 1.0;
     }
 }
 
