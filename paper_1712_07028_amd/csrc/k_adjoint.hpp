@@ -191,47 +191,84 @@ __device__ __forceinline__ void adj_cell(const Geom &G, const Phys &Ph, const De
     }
     const uint32_t miss = sm | wm;
 
-    // ---- f_t = S(s_{t-1}) at x: pull with bounce-back (same rules as the step) ----
-    float fi[Q];
+    // the particle P of the links and whether some link leads to another (or to none): the
+    // ids in one batch, then one mirror and one direction for all links (one after the other
+    // per link, three dependent loads each, they were half of the launch on a box of spheres)
+    bool multi = false;
+    float pu0 = 0.f, pu1 = 0.f, pu2 = 0.f;
+    float4 pe = make_float4(0.f, 0.f, 0.f, 0.f);
+    const unsigned c4 = (unsigned)c * 4u, S4 = (unsigned)S * 4u;
     float rho_t = 1.0f;
-    if (miss) {
-        float fo[Q];
+    if (sm) {
+        float fo[Q], d = 0.f;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) fo[q] = sPrev[q * S + c];
-        float d = 0.f;
+        for (int q = 0; q < Q; ++q) fo[q] = *at_byte(sPrev + q * S, c4);
 #pragma unroll
         for (int q = 0; q < Q; ++q) d += fo[q];
-        rho_t = 1.0f + d;
-        fi[0] = fo[0];
+        rho_t += d;
+        unsigned pmin = 0xffffffffu, pmax = 0u;
 #pragma unroll
         for (int q = 1; q < Q; ++q) {
-            if (!((miss >> q) & 1u)) {
-                fi[q] = sPrev[q * S + src(q)];
-            } else if ((sm >> q) & 1u) {
-                const int P = D.pid[src(q)];
-                float u0 = 0.f, u1 = 0.f, u2 = 0.f;
-                if ((unsigned)P < (unsigned)D.np) node_velocity(P, u0, u1, u2);
-                const float cu = cx(q) * u0 + cy(q) * u1 + cz(q) * u2;
-                fi[q] = fo[opp(q)] + 6.0f * wq(q) * rho_t * cu;
-            } else {
-                fi[q] = fo[opp(q)];
-            }
+            const bool b = (sm >> q) & 1u;
+            const unsigned p = (unsigned)D.pid[b ? src(q) : c];
+            pmin = min(pmin, b ? p : 0xffffffffu);
+            pmax = max(pmax, b ? p : 0u);
         }
+        multi = pmin != pmax || pmin >= (unsigned)D.np;
+        if (!multi) {
+            node_velocity((int)pmin, pu0, pu1, pu2);
+            pe = uh[pmin];
+        }
+    }
+    // a link's own particle where they differ (false: it has none)
+    auto of_link = [&](int q, float &u0, float &u1, float &u2, float4 &e) -> bool {
+        u0 = pu0;
+        u1 = pu1;
+        u2 = pu2;
+        e = pe;
+        if (!multi) return true;
+        const int P = D.pid[src(q)];
+        if ((unsigned)P >= (unsigned)D.np) return false;
+        node_velocity(P, u0, u1, u2);
+        e = uh[P];
+        return true;
+    };
+
+    // ---- f_t = S(s_{t-1}) at x: pull with bounce-back (same rules as the step); a link
+    // takes the cell's own opposite population, by a selected address ----
+    float fi[Q];
+    // plane q of X at cell idx, or plane opp(q) at c (b); a selected offset of 32 bits from the
+    // lower of the two planes, unless the box is too large for that (see Phys::wide)
+    auto either = [&](const float *X, int q, bool b, int idx) -> float {
+        const int lo = q < opp(q) ? q : opp(q);
+        if (Ph.wide) return X[b ? opp(q) * S + c : q * S + idx];
+        unsigned o = (unsigned)idx * 4u + (unsigned)(q - lo) * S4;
+        o = b ? c4 + (unsigned)(opp(q) - lo) * S4 : o;
+        __asm__("" : "+v"(o));
+        return *at_byte(X + lo * S, o);
+    };
+    fi[0] = *at_byte(sPrev, c4);
+    if (miss) {
+#pragma unroll
+        for (int q = 1; q < Q; ++q)
+            fi[q] = either(sPrev, q, (miss >> q) & 1u, src(q));
     } else {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) fi[q] = sPrev[q * S + (q ? src(q) : c)];
+        for (int q = 1; q < Q; ++q) fi[q] = *at_byte(sPrev + q * S, (unsigned)src(q) * 4u);
     }
 
     // ---- sbar_t = S^T mu_{t+1} + dJ_t/ds_t ----
     // s_q(x) moves to x + c_q; when that cell is an obstacle it is bounced back into
     // the pull direction opp(q) at x, which is the link with bit opp(q) set above
     float sb[Q];
-    sb[0] = muN[c];
+    sb[0] = *at_byte(muN, c4);
+    if (miss) {
 #pragma unroll
-    for (int q = 1; q < Q; ++q) {
-        const int o = opp(q);
-        if (!((miss >> o) & 1u)) sb[q] = muN[q * S + nbr(q)];
-        else sb[q] = muN[o * S + c];
+        for (int q = 1; q < Q; ++q)
+            sb[q] = either(muN, q, (miss >> opp(q)) & 1u, nbr(q));
+    } else {
+#pragma unroll
+        for (int q = 1; q < Q; ++q) sb[q] = *at_byte(muN + q * S, (unsigned)nbr(q) * 4u);
     }
     if (sm) {
         // moving bounce-back f_o(x) = s_q(x) + 6 w rho_t (c_o . u_w): its density term
@@ -241,13 +278,12 @@ __device__ __forceinline__ void adj_cell(const Geom &G, const Phys &Ph, const De
         for (int o = 1; o < Q; ++o) {
             if (!((sm >> o) & 1u)) continue;
             const int q = opp(o);
-            const int P = D.pid[src(o)];
-            if ((unsigned)P >= (unsigned)D.np) continue;
             float u0, u1, u2;
-            node_velocity(P, u0, u1, u2);
-            const float4 e = uh[P];
+            float4 e;
+            if (!of_link(o, u0, u1, u2, e)) continue;
             const float cu = cx(o) * u0 + cy(o) * u1 + cz(o) * u2;
             const float ce = cx(o) * e.x + cy(o) * e.y + cz(o) * e.z;
+            fi[o] = fi[o] + 6.0f * wq(o) * rho_t * cu;
             K += 6.0f * wq(o) * cu * (sb[q] + ce);
             sb[q] += 2.0f * ce;
         }
@@ -335,8 +371,10 @@ __device__ __forceinline__ void adj_cell(const Geom &G, const Phys &Ph, const De
     gr[4] = rho * (0.5f * D2 + Gg2);
 }
 
-// five waves per SIMD (91 VGPRs, no spill): at 256^3 the backward sweep takes 393 ms
-// against 425 ms at the four that the register count alone allows; six waves spill
+// Bound by memory: 228 bytes a cell, 3.8 GB on 256^3, 0.87 ms at a large copy's rate.  At 256^3
+// with 1,280 spheres a launch takes 0.95 ms (4.0 TB/s); 1.32 ms when each link loaded its own
+// particle, mirror and direction in turn and the pulls were branches.  Five waves per SIMD (90
+// VGPRs, no spill).
 __global__ __launch_bounds__(256, 5) void k_adj_step(Geom G, Phys Ph, Dev D, const float *__restrict__ sPrev,
                                                   const float *__restrict__ muN, float *__restrict__ muO,
                                                   const float4 *__restrict__ uh, double *part, int tilesX,
