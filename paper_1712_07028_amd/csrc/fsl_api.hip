@@ -307,7 +307,7 @@ void set_phys(fsl_ctx *c) {
 template <int ST, bool MW, bool PER>
 void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv, const SolidArgs &SA) {
     int *glist = (int *)(c->xs + c->L.glist), *ngen = Dv.counters + C_NGEN;
-    // Planes per block, k of 1 .. NZC: the device holds D = 4 blocks per compute unit at once;
+    // Planes per block, k of 1 .. 14: the device holds D = 4 blocks per compute unit at once;
     // a block costs its planes and about half a plane for staging the first three.  Blocks
     // differ in cost (rows with particle links against gas), so that a launch of r = blocks / D
     // rounds takes about max(r + 1/2, ceil r) times a block, not ceil r: thin blocks on
@@ -317,15 +317,25 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv, const SolidArgs &SA) {
     // one too (384 x 256 x 512, us: 3: 1564, 4: 1631, 6: 1518, 8: 1609, 10: 1519, 12: 1513, 14: 1529,
     // 16: 1605), and so are odd numbers, 2 to 4 % slower on the 512 x 512 x 1024 column (ms, 10 to
     // 15: 10.29, 10.57, 10.17, 10.49, 10.12, 10.45).
+    // With spheres a lane sums its links over a block's planes, so that their number decides
+    // the last bits of the forces: it depends on the box alone then, the largest power of two
+    // up to 16 that leaves 2,048 blocks (column 16 planes, 10.3 ms a launch against 10.1 with
+    // 14; 128^3 bed 4 planes, 111 us against 106 with 3).
     const long long cols = (long long)c->tilesX * c->tilesY, dev = 4ll * c->cus;
+    auto blocks = [&](int k) { return cols * ((c->G.nz + k - 1) / k); };
     int nzc = 1;
-    long long best = 0;
-    for (int k : {1, 2, 3, 6, 10, 12, NZC}) {
-        const long long blocks = cols * ((c->G.nz + k - 1) / k);
-        const long long t = std::max(2 * blocks + dev, 2 * dev * ((blocks + dev - 1) / dev)) * (2 * k + 1);
-        if (best == 0 || t <= best) {
-            best = t;
-            nzc = k;
+    if (c->D.np > 0) {
+        nzc = NZC;
+        while (nzc > 2 && blocks(nzc) < 2048) nzc /= 2;
+    } else {
+        long long best = 0;
+        for (int k : {1, 2, 3, 6, 10, 12, 14}) {
+            const long long r = blocks(k);
+            const long long t = std::max(2 * r + dev, 2 * dev * ((r + dev - 1) / dev)) * (2 * k + 1);
+            if (best == 0 || t <= best) {
+                best = t;
+                nzc = k;
+            }
         }
     }
     const int nChunks = (c->G.nz + nzc - 1) / nzc;

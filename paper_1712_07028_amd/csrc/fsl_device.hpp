@@ -391,5 +391,12 @@ __device__ __forceinline__ double wave_sum(double v) {
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 63);
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
+// The same by halves of the wave (32, 16, ... 1).  The links between spheres and at faces take
+// this tree: the last bits of a force depend on it.
+__device__ __forceinline__ double wave_sum_halves(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
 
 }  // namespace fsl

@@ -439,7 +439,7 @@ __device__ __forceinline__ void solid_pair(const Geom &G, const Dev &D, int Pp, 
     if (!__ballot(some)) return;
     double *dst = D.pacc + acc_at(Po, copy & (ACC_COPIES - 1));
     for (int a = 0; a < 6; ++a) {
-        const double v = wave_sum(acc[a]);
+        const double v = wave_sum_halves(acc[a]);
         if (lane == 0 && v != 0.0) unsafeAtomicAdd(dst + a, v);
     }
 }
@@ -539,7 +539,7 @@ __device__ __forceinline__ void face_links(const Geom &G, const Phys &Ph, const 
     }
     double *dst = D.pacc + acc_at(P, P & (ACC_COPIES - 1));
     for (int a = 0; a < 6; ++a) {
-        const double v = wave_sum(acc[a]);
+        const double v = wave_sum_halves(acc[a]);
         if (lane == 0 && v != 0.0) unsafeAtomicAdd(dst + a, v);
     }
 }

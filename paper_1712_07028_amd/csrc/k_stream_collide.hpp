@@ -675,12 +675,11 @@ __device__ __forceinline__ int kconst(int q) {
 // from what.  A mask is then the condition of a select or of a masked block without any
 // per-lane bit work.  512 x 512 x 1024 cells with 1e5 spheres: 10.8 ms a launch per lane, 10.2 ms
 // with masks (49.6 GB, 4.9 TB/s, what a large copy reaches); 128^3 with 1,400: 115 and 107 us.
-constexpr int NZC = 14;
+constexpr int NZC = 16;  // planes per block at most
 #ifndef WPE_MARCH
 #define WPE_MARCH 4
 #endif
 constexpr int HX = TX + 2, HY = TY + 2;  // a staged plane: 6 rows of 66 cells
-constexpr int NSLOT = 256;               // spheres whose link sums a block keeps
 constexpr unsigned AN_SOL = 1u, AN_BAD = 2u, AN_IFC = 4u;  // kinds that a wave's staged rows hold
 
 struct MarchLds {
@@ -693,11 +692,11 @@ struct MarchLds {
     unsigned long long b3[4][HY], b1[4][HY];
     uint8_t any[4][4];               // kinds in the rows that wave wv staged (AN_*)
     int genflag[2];                  // the plane holds cells for the general path
-    // link sums per sphere over the block's planes: force and torque about the sphere's
-    // centre (Eqs. netforce, torque, momentum_transfer) in FP64, and the mass that moving
-    // bounce-back added (paid by the ledger)
-    double acc[7][NSLOT];
-    int tag[NSLOT];
+    // each lane's link sums for one sphere over the planes of the march: force and torque
+    // about the sphere's centre (Eqs. netforce, torque, momentum_transfer) in FP64, and the
+    // mass that moving bounce-back added (paid by the ledger)
+    double acc[7][256];
+    int accP[256];
 };
 
 // a value that is the same in every lane, as a scalar
@@ -809,20 +808,49 @@ __device__ __forceinline__ void lds_add(double *p, double v) {
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// The slot of sphere P in the block's table of link sums (open addressing, eight places;
-// a block meets a few tens of spheres), or -1 when those are taken by others.
-__device__ __forceinline__ int acc_slot(MarchLds &L, int P) {
-    int s = P & (NSLOT - 1);
-    for (int i = 0; i < 8; ++i) {
-        int t = L.tag[s];
-        if (t < 0) {
-            t = atomicCAS(&L.tag[s], -1, P);
-            if (t < 0) t = P;
-        }
-        if (t == P) return s;
-        s = (s + 1) & (NSLOT - 1);
+// The order of a sphere's link sums is fixed within a wave: a lane sums its own cells plane by
+// plane, the lanes join in a fixed tree, and only what waves add to the sphere comes in any
+// order.  Sums of the whole block in a table in LDS, which its 256 lanes add to as they come,
+// save the lanes' atomics (512 x 512 x 1024 column 114.3 against 121.7 ms for ten steps, 128^3
+// bed 15.5 against 16.2 ms for fifty) but change the last bits of every force, and the
+// constant parts of the links, which cancel over a sphere, make that the same way in every
+// step: within 50 steps a 16-bit population rounds differently and the states part.
+
+// one lane's sums (in LDS) straight to its sphere (a lane that moves on to another one),
+// then cleared
+__device__ __forceinline__ void macc_lane_flush(const Dev &D, MarchLds &L, int t) {
+    double *dst = D.pacc + acc_at(L.accP[t], blockIdx.x & (ACC_COPIES - 1));
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        unsafeAtomicAdd(dst + k, L.acc[k][t]);
+        L.acc[k][t] = 0.0;
     }
-    return -1;
+}
+
+// the lanes' remaining sums at the end of a march, segmented by sphere: one FP64 atomic
+// instruction per (wave, sphere).  Every lane of the wave must be active.
+__device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L) {
+    const int t = threadIdx.x;
+    int key = L.accP[t];
+    double a[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) a[k] = L.acc[k][t];
+    while (true) {
+        const unsigned long long act = __ballot(key >= 0);
+        if (!act) break;
+        const int leader = __ffsll((long long)act) - 1;
+        const int k0 = __builtin_amdgcn_readlane(key, leader);
+        const bool mine = key == k0;
+        double s[7];
+#pragma unroll
+        for (int k = 0; k < 7; ++k) s[k] = wave_sum(mine ? a[k] : 0.0);
+        const int ln = (int)lane_id();
+        if (ln < 7) {
+            const double v = ln == 0 ? s[0] : ln == 1 ? s[1] : ln == 2 ? s[2] : ln == 3 ? s[3] : ln == 4 ? s[4] : ln == 5 ? s[5] : s[6];
+            unsafeAtomicAdd(D.pacc + acc_at(k0, blockIdx.x & (ACC_COPIES - 1)) + ln, v);
+        }
+        if (mine) key = -1;
+    }
 }
 
 // density of a cell's own populations (a cell whose density from the launch before
@@ -865,10 +893,12 @@ __device__ __forceinline__ int step_to(int v, int d, int n, int per, int stride)
 // always had, kept so that results do not change).
 template <bool PER, bool ALT, typename M>
 __device__ __forceinline__ void march_links(const Geom &G, const Dev &D, MarchLds &L, int P, const PMir &m, M &&mk,
-                                            float rho_t, int x, int y, int z, float (&fi)[Q], int &curP, int &curS) {
-    if (P != curP) {
+                                            float rho_t, int x, int y, int z, float (&fi)[Q], int &curP) {
+    const int t = threadIdx.x;
+    if (P != curP) {  // the lane's sums move on to another sphere
+        if (curP >= 0) macc_lane_flush(D, L, t);
         curP = P;
-        curS = acc_slot(L, P);
+        L.accP[t] = P;
     }
     // rigid-body velocity at the node: c_q . u_w at the link midpoint equals
     // c_q . (u_P + omega x (x - x_P)) because c_q . (omega x c_q) = 0
@@ -914,14 +944,9 @@ __device__ __forceinline__ void march_links(const Geom &G, const Dev &D, MarchLd
                  F2 = (double)f2 + kz * (1.0 / 18.0);
     const double dx = rx, dy = ry, dz = rz;
     const double v[7] = {F0, F1, F2, dy * F2 - dz * F1, dz * F0 - dx * F2, dx * F1 - dy * F0, (double)dm};
-    if (curS >= 0) {
+    // LDS atomic adds without return: the lane's own slots, so nothing waits
 #pragma unroll
-        for (int k = 0; k < 7; ++k) lds_add(&L.acc[k][curS], v[k]);
-    } else {  // no place in the table (rare)
-        double *dst = D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
-#pragma unroll
-        for (int k = 0; k < 7; ++k) unsafeAtomicAdd(dst + k, v[k]);
-    }
+    for (int k = 0; k < 7; ++k) lds_add(&L.acc[k][t], v[k]);
 }
 
 // The launch's arguments, read from where the launch put them: again at every call, so that
@@ -978,7 +1003,7 @@ template <int ST, bool PER>
 __device__ __forceinline__ void march_cell(MarchLds &L, int sm1, int s0, int sp1, int lx, int ly, int x, int y, int z,
                                            int c, const SrcOff &so, unsigned long long act, bool store, bool has_sol,
                                            unsigned long long wx0, unsigned long long wx1, const StageIdx &SI, RowPre &R,
-                                           int zo2, bool next, int &curP, int &curS) {
+                                           int zo2, bool next, int &curP) {
     using SS = Store<ST>;
     using T = typename SS::T;
     constexpr unsigned ES = sizeof(T);
@@ -1084,7 +1109,7 @@ __device__ __forceinline__ void march_cell(MarchLds &L, int sm1, int s0, int sp1
                                                            : own_density<ST>(M.D.fA, M.G.S, c, M.Ph.inv);
             if (!multi) {
                 march_links<PER, ST == ST_F32 && PER>(M.G, M.D, L, P, pm, [&](int q) { return in_mask(sm[q]); }, rho_t, x,
-                                                      y, z, fi, curP, curS);
+                                                      y, z, fi, curP);
             } else {
                 // links into more than one particle, or an inconsistent owner (rare): one
                 // particle at a time
@@ -1109,7 +1134,7 @@ __device__ __forceinline__ void march_cell(MarchLds &L, int sm1, int s0, int sp1
                     }
                     march_links<PER, ST == ST_F32>(M.G, M.D, L, Pk, pmir_load(M.D.pmir, Pk),
                                                    [&](int q) { return ((mk >> q) & 1u) != 0u; }, rho_t, x, y, z, fi,
-                                                   curP, curS);
+                                                   curP);
                 }
             }
         }
@@ -1180,9 +1205,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
         for (int p = 0; p < 3; ++p) pre_store(L, R3[p], (zs - 1 + p) & 3, MW, dirty);
     }
     if (threadIdx.x < 2) L.genflag[threadIdx.x] = 0;
-    int curP = -1, curS = -1;  // the lane's last sphere and its slot in the table
+    int curP = -1;  // the sphere of the lane's sums (a copy of L.accP)
     if (D.np > 0) {
-        L.tag[threadIdx.x] = -1;
+        L.accP[threadIdx.x] = -1;
 #pragma unroll
         for (int k = 0; k < 7; ++k) L.acc[k][threadIdx.x] = 0.0;
     }
@@ -1229,7 +1254,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
             so.zp = step_to(z, 1, G.nz, G.per[2], nxy);
             const int c = xc + (G.nx * yc + nxy * z);
             march_cell<ST, PER>(L, sm1, s0, sp1, lx, ly, xl, y, z, c, so, act, in_mask(inb & ~gen_m), (an & AN_SOL) != 0u,
-                                wx0, wx1, SI, R, zo2, next, curP, curS);
+                                wx0, wx1, SI, R, zo2, next, curP);
         } else if (next) {
             pre_pids(M.D.pid, SI, R, zo2);
         }
@@ -1241,16 +1266,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE_MARCH))
             M.gen[slot] = col + M.tilesX * M.tilesY * z;  // list capacity: every tile of the box
         }
     }
-    // the block's link sums, an atomic per sphere and component
     const MarchArgs &Me = march_args();
-    if (Me.D.np > 0) {
-        const int t = threadIdx.x, P = L.tag[t];
-        if (P >= 0) {
-            double *dst = Me.D.pacc + acc_at(P, blockIdx.x & (ACC_COPIES - 1));
-#pragma unroll
-            for (int k = 0; k < 7; ++k) unsafeAtomicAdd(dst + k, L.acc[k][t]);
-        }
-    }
+    if (Me.D.np > 0) macc_wave_flush(Me.D, L);
 }
 
 // Row masks of the staged tile for the general path's selection (gas and, with moving
