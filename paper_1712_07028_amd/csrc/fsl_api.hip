@@ -195,7 +195,6 @@ struct fsl_ctx {
     // run.  They come from gas alone, so a box without any stays without (2: none in the
     // cell types just set; one more step with them brings the bubble table up to date)
     int gas;
-    int counters_clear;  // the counters of the next step are zero
     int rhow_ok;    // the density words of stamp - 1 hold the densities of the populations in A
     // two steps captured as a HIP graph from a steady state (stored densities valid, the
     // particle update past its first step): fsl_step replays it while lattice A is the
@@ -415,6 +414,18 @@ int enqueue_split(fsl_ctx *c, const double *phi, int force) {
     return FSL_OK;
 }
 
+// labels the current state, whatever was set.  The counters are clear again afterwards, as
+// between steps: a step clears the set of the next one only, and steps that a caller has
+// captured into a graph of its own count on it.
+template <int ST>
+int enqueue_label(fsl_ctx *c, const double *phi) {
+    const int rc = enqueue_split<ST>(c, phi, 1);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, c->D);
+    LAUNCHCHK(c);
+    return FSL_OK;
+}
+
 template <int ST>
 int enqueue_conversions(fsl_ctx *c) {
     ProfScope ps(c, 1);
@@ -574,7 +585,6 @@ template <int ST>
 int enqueue_steps(fsl_ctx *c, int n) {
     for (int s = 0; s < n; ++s) {
         Dev &D = c->D;
-        if (!c->counters_clear) hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, D);
         int rc = enqueue_before<ST>(c);
         if (rc) return rc;
         const bool joined = joined_phases(c);
@@ -625,7 +635,6 @@ int enqueue_steps(fsl_ctx *c, int n) {
         std::swap(D.phi_cur, D.phi_nxt);
         std::swap(D.counters, D.counters_nxt);  // cleared by this step's first kernel
         std::swap(D.wallF, D.wallF_nxt);
-        c->counters_clear = 1;
     }
     return FSL_OK;
 }
@@ -635,7 +644,6 @@ template <int ST>
 int enqueue_coverage_full(fsl_ctx *c) {
     Dev Dv = c->D;
     Dv.fB = c->D.fA;  // the current state is in lattice A between steps
-    c->counters_clear = 0;
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, Dv);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
@@ -649,7 +657,7 @@ int enqueue_coverage_full(fsl_ctx *c) {
     LAUNCHCHK(c);
     int rc = enqueue_bubbles<ST>(c, Dv.phi_cur, 0, 0);
     if (rc) return rc;
-    return enqueue_split<ST>(c, Dv.phi_cur, 1);
+    return enqueue_label<ST>(c, Dv.phi_cur);
 }
 
 template <int ST>
@@ -663,7 +671,7 @@ int dispatch_init(fsl_ctx *c, const InitGeo &I) {
     LAUNCHCHK(c);
     int rc = enqueue_bubbles<ST>(c, D.phi_cur, 1, 0);
     if (rc) return rc;
-    return enqueue_split<ST>(c, D.phi_cur, 1);
+    return enqueue_label<ST>(c, D.phi_cur);
 }
 
 template <typename Fn>
@@ -890,7 +898,6 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
     D.counters_nxt = D.counters + C_SET;
     c->gas = !(cfg->zs < 0.0) || cfg->n_gas_spheres > 0;
     D.bused = D.counters + C_BUSED;
-    c->counters_clear = 0;
     D.err = (unsigned *)(w + L.ctl);
     D.ledger = (double *)(w + L.ctl + 8);
     D.ptab = (double *)(w + L.ptab);
@@ -1283,10 +1290,9 @@ int fsl_bubbles_set(fsl_ctx *c, int n, const double *M, const int *root, const i
     HIPCHK(c, hipStreamSynchronize(c->st));
     // the lists a step leaves are not read again: the splitting pass below clears no marks
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, c->st, c->D);
-    c->counters_clear = 0;
     int rc = by_storage(c, [&](auto st) {
         int r = enqueue_bubbles<decltype(st)::value>(c, c->D.phi_cur, 0, 0);
-        return r ? r : enqueue_split<decltype(st)::value>(c, c->D.phi_cur, 1);
+        return r ? r : enqueue_label<decltype(st)::value>(c, c->D.phi_cur);
     });
     if (rc) return rc;
     return read_error(c);
