@@ -776,6 +776,9 @@ __device__ __forceinline__ bool may_overlap(const Geom &G, const double *a, cons
 // with 174 pairs, one block for all of them 48 us, this 23 us.  The same arithmetic as k_lub
 // and k_substep.
 constexpr int INT_LONE = 64;
+// tables above this report a centre outside the box after any substep, as with a launch per
+// substep; smaller ones after the last
+constexpr int INT_WATCH = 512;
 inline int int_blocks(int np) { return 1 + (np + INT_LONE - 1) / INT_LONE; }
 struct IntArgs {
     int ns;
@@ -828,6 +831,9 @@ __device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const Int
     const int np = D.np, npair = min(D.counters[C_NPAIRS], A.pcap);
     const int tid = threadIdx.x;
     const double dt = 1.0 / A.ns;
+    const int n[3] = {G.nx, G.ny, G.nz};
+    bool left = false;  // a centre left the box between two substeps (and may be back)
+    auto watch = [&](const double *x, double R) { left |= np > INT_WATCH && !sphere_supported(x, R, n, G.per); };
     for (int i = tid; i < NPT * 32; i += 1024) L.mark[i] = 0u;
     __syncthreads();
     constexpr int NPR = 2;  // pairs that a thread of block 0 keeps in registers
@@ -856,8 +862,12 @@ __device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const Int
         if (tid >= INT_LONE || P >= np || ((L.mark[P >> 5] >> (P & 31)) & 1u)) return;
         double x[3], u[3], w[3], f[3] = {0.0, 0.0, 0.0};
         const SubstepConst c = integrate_load(D, P, A, dt, x, u, w);
-        for (int s = 0; s < A.ns; ++s) substep_one(G, c, x, u, f, dt, A.mu, A.kc, A.wmask);
+        for (int s = 0; s < A.ns; ++s) {
+            substep_one(G, c, x, u, f, dt, A.mu, A.kc, A.wmask);
+            watch(x, c.R);
+        }
         integrate_store(G, D, P, c.R, x, u, w);
+        if (left) atomicOr(D.err, ERR_PART);
         return;
     }
     if (npair == 0) return;
@@ -938,6 +948,7 @@ __device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const Int
                     L.f[i][d] = 0.0;
                 }
                 substep_one(G, c, x, u, f, dt, A.mu, A.kc, A.wmask);
+                watch(x, c.R);
 #pragma unroll
                 for (int d = 0; d < 3; ++d) {
                     L.x[i][d] = x[d];
@@ -945,7 +956,9 @@ __device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const Int
                 }
                 continue;
             }
-            substep_one(G, substep_const(D, L.id[i], A.have_prev, dt, A.g), L.x[i], L.u[i], L.f[i], dt, A.mu, A.kc, A.wmask);
+            const SubstepConst ci = substep_const(D, L.id[i], A.have_prev, dt, A.g);
+            substep_one(G, ci, L.x[i], L.u[i], L.f[i], dt, A.mu, A.kc, A.wmask);
+            watch(L.x[i], ci.R);
         }
         __syncthreads();
     }
@@ -956,6 +969,7 @@ __device__ __forceinline__ void integrate(const Geom &G, const Dev &D, const Int
         }
         integrate_store(G, D, L.id[i], c.R, L.x[i], L.u[i], w);
     }
+    if (left) atomicOr(D.err, ERR_PART);
     block_phase();
     auto flag = [&](int2 q, double s) {
         if (may_overlap(G, L.x[L.slot[q.x]], L.x[L.slot[q.y]], s))
