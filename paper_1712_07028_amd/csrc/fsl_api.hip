@@ -475,16 +475,23 @@ int enqueue_coverage_step(fsl_ctx *c) {
     return FSL_OK;
 }
 
+// every pair of the table tested instead of those of the grid
+bool direct_pairs(const fsl_ctx *c) {
+    return c->D.np > 0 && c->D.np <= PAIRS_DIRECT && pairs_direct_box(c->G.nx, c->G.ny, c->G.nz);
+}
+
 // Small tables: launches of independent work put into one (each costs 4.5 us and, alone,
 // leaves the device idle): pairs beside face forces, sphere links beside the general path, the
 // particle update beside the conversions.  Per-phase timing takes them apart.
-bool joined_phases(const fsl_ctx *c) { return c->D.np > 0 && c->D.np <= INT_BLOCK_MAX && !c->profiling; }
+bool joined_phases(const fsl_ctx *c) {
+    return c->D.np > 0 && c->D.np <= INT_BLOCK_MAX && direct_pairs(c) && !c->profiling;
+}
 
 // face forces of the state at t and a small table's candidate pairs (positions at t)
 template <int ST>
 int enqueue_before(fsl_ctx *c) {
     Dev &D = c->D;
-    const bool faces = c->FS.n > 0 && D.wallF, pairs = D.np > 0 && D.np <= PAIRS_DIRECT;
+    const bool faces = c->FS.n > 0 && D.wallF, pairs = direct_pairs(c);
     const PairsDirect PD = pairs_direct_of(c->PG, c->L.pcap, D.np);
     const int nb = faces ? grid_for(c->FS.start[c->FS.n] / c->FS.n, 256, 512) : 0;
     const int nf = nb * c->FS.n;
@@ -512,7 +519,7 @@ int enqueue_pair_forces(fsl_ctx *c, bool joined) {
     const int np = D.np;
     ProfScope ps(c, 3);
     // candidate pairs (positions at t): particle-particle links and lubrication
-    if (np > PAIRS_DIRECT) {
+    if (!direct_pairs(c)) {
         hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(c->ncell)), dim3(256), 0, c->st, D, c->ncell);
         hipLaunchKernelGGL(k_grid_count, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
         const int chunk = std::max(256, (c->ncell + 1023) / 1024 + 255) / 256 * 256;

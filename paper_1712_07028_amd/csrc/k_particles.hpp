@@ -7,6 +7,7 @@
 
 #include "cov_column.hpp"
 #include "k_free_surface.hpp"
+#include "pair_near.hpp"
 
 namespace fsl {
 
@@ -313,9 +314,8 @@ __global__ __launch_bounds__(256) void k_pairs(Dev D, PGrid PG, int pcap) {
 // Small tables (up to PAIRS_DIRECT spheres): every pair tested, in one launch instead of the
 // seven that build and walk the grid (4.6 us each whatever the size).  A block takes
 // PDIR_P spheres against 256 later ones, one per thread, so that the launch is one
-// round of loads deep.  A first test in FP32 on the axes' distances (nearest images of
-// centres in [0, n); half a cell of slack, far beyond the rounding of coordinates below
-// 2^16) leaves the distance itself to the near ones.
+// round of loads deep.  A first test in FP32 on the axes' distances (pair_near.hpp, on boxes
+// up to PAIRS_AXIS cells an axis) leaves the distance itself to the near ones.
 constexpr int PAIRS_DIRECT = 2048, PDIR_P = 16;
 struct PairsDirect {
     PGrid PG;
@@ -339,17 +339,12 @@ __device__ __forceinline__ void pairs_direct(const Dev &D, const PairsDirect &A,
     }
     const int Qp = Q0 + (int)threadIdx.x;
     const double *y = D.ptab + (long long)min(Qp, D.np - 1) * P_STRIDE;
-    const float y0 = (float)y[P_X], y1 = (float)y[P_X + 1], y2 = (float)y[P_X + 2],
-                yr = (float)(y[P_R] + PG.reach) + 0.5f;
+    const float y0 = (float)y[P_X], y1 = (float)y[P_X + 1], y2 = (float)y[P_X + 2], yr = reach_of(y[P_R], PG.reach);
     __syncthreads();
-    auto apart = [&](float d, int k) {
-        d = fabsf(d);
-        return PG.per[k] ? fminf(d, (float)PG.n[k] - d) : d;
-    };
     for (int p = 0; p < n; ++p) {
-        const float d0 = apart(y0 - c[p][0], 0), d1 = apart(y1 - c[p][1], 1), d2 = apart(y2 - c[p][2], 2);
-        const float r = c[p][3] + yr;
-        if (P0 + p < Qp && Qp < D.np && d0 * d0 + d1 * d1 + d2 * d2 < r * r)
+        const float d0 = axis_apart(y0, c[p][0], PG.n[0], PG.per[0]), d1 = axis_apart(y1, c[p][1], PG.n[1], PG.per[1]),
+                    d2 = axis_apart(y2, c[p][2], PG.n[2], PG.per[2]);
+        if (P0 + p < Qp && Qp < D.np && pair_near(d0, d1, d2, c[p][3] + yr))
             pair_test(D, PG, L, P0 + p, D.ptab + (long long)(P0 + p) * P_STRIDE, Qp, y, A.pcap);
     }
     pairs_flush(D, L, A.pcap);
