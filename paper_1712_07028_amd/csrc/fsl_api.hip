@@ -487,23 +487,15 @@ bool joined_phases(const fsl_ctx *c) {
     return c->D.np > 0 && c->D.np <= INT_BLOCK_MAX && direct_pairs(c) && !c->profiling;
 }
 
-// face forces of the state at t and a small table's candidate pairs (positions at t)
+// face forces of the state at t and, joined, a small table's candidate pairs (positions at t)
 template <int ST>
 int enqueue_before(fsl_ctx *c) {
     Dev &D = c->D;
-    const bool faces = c->FS.n > 0 && D.wallF, pairs = direct_pairs(c);
-    const PairsDirect PD = pairs_direct_of(c->PG, c->L.pcap, D.np);
+    const bool faces = c->FS.n > 0 && D.wallF;
+    const PairsDirect PD = joined_phases(c) ? pairs_direct_of(c->PG, c->L.pcap, D.np) : PairsDirect{};
     const int nb = faces ? grid_for(c->FS.start[c->FS.n] / c->FS.n, 256, 512) : 0;
-    const int nf = nb * c->FS.n;
-    if (faces && pairs && joined_phases(c)) {
-        hipLaunchKernelGGL(k_before<ST>, dim3(nf + PD.n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, nb, PD);
-    } else {
-        if (faces) hipLaunchKernelGGL(k_before<ST>, dim3(nf), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, nb, PD);
-        if (pairs) {
-            ProfScope ps(c, 3);
-            hipLaunchKernelGGL(k_before<ST>, dim3(PD.n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, 0, PD);
-        }
-    }
+    const int n = nb * c->FS.n + PD.n;
+    if (n) hipLaunchKernelGGL(k_before<ST>, dim3(n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, nb, PD);
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -512,14 +504,17 @@ SolidArgs solid_args_of(const fsl_ctx *c) {
     return solid_args(c->L.pcap, c->D.np, !c->G.per[0] || !c->G.per[1] || !c->G.per[2]);
 }
 
-// joined: the links between spheres went with the lattice update
+// joined: the candidate pairs and the links between spheres went before
 template <int ST>
 int enqueue_pair_forces(fsl_ctx *c, bool joined) {
     Dev &D = c->D;
     const int np = D.np;
     ProfScope ps(c, 3);
     // candidate pairs (positions at t): particle-particle links and lubrication
-    if (!direct_pairs(c)) {
+    if (!joined && direct_pairs(c)) {
+        const PairsDirect PD = pairs_direct_of(c->PG, c->L.pcap, np);
+        hipLaunchKernelGGL(k_before<ST>, dim3(PD.n), dim3(256), 0, c->st, c->G, c->Ph, D, c->FS, 0, PD);
+    } else if (!joined) {
         hipLaunchKernelGGL(k_grid_zero, dim3(grid_for(c->ncell)), dim3(256), 0, c->st, D, c->ncell);
         hipLaunchKernelGGL(k_grid_count, dim3(grid_for(np)), dim3(256), 0, c->st, D, c->PG);
         const int chunk = std::max(256, (c->ncell + 1023) / 1024 + 255) / 256 * 256;
@@ -595,9 +590,9 @@ int enqueue_steps(fsl_ctx *c, int n) {
         int rc = enqueue_before<ST>(c);
         if (rc) return rc;
         const bool joined = joined_phases(c);
-        if (D.kappa && c->gas) {  // curvature of the interface at t for the Laplace jump
+        if (D.kappa) {  // curvature of the interface at t for the Laplace jump
             ProfScope ps(c, 6);
-            enqueue_curvature(c, D.counters + C_NKT);
+            if (c->gas) enqueue_curvature(c, D.counters + C_NKT);
         }
         if (!c->rhow_ok && D.rhow) {  // densities of the current populations for rho_w
             hipLaunchKernelGGL(k_rhow_fill<ST>, dim3(grid_for(c->G.N, 256, 8192)), dim3(256), 0, c->st, c->G,
@@ -624,6 +619,8 @@ int enqueue_steps(fsl_ctx *c, int n) {
         if (conv && !both) {
             rc = enqueue_conversions<ST>(c);
             if (rc) return rc;
+        } else if (!conv) {  // the phases that a box without gas leaves out count all the same
+            ProfScope conversions(c, 1), bubbles(c, 2), splitting(c, 7);
         }
         if (D.np > 0) {
             rc = enqueue_pair_forces<ST>(c, joined);
