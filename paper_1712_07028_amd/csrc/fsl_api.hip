@@ -442,10 +442,6 @@ int enqueue_conversions(fsl_ctx *c) {
     return FSL_OK;
 }
 
-// blocks of the uncover pass: 32 lanes per node, and a sphere leaves about half a node per
-// step (pi R^2 times its velocity)
-int uncover_blocks(const fsl_ctx *c, int block) { return std::min(256, std::max(2, c->D.np / 2 * 32 / block)); }
-
 // threads per sphere (a power of two's exponent) for the passes over spheres' nodes: as
 // many as leave the launch within what the device holds at once (half a million threads)
 int team_shift(int np) { return np <= 512 ? 10 : np <= 2048 ? 8 : np <= 4096 ? 7 : 6; }
@@ -468,9 +464,12 @@ int enqueue_coverage_step(fsl_ctx *c) {
     const int sh = team_shift(np);
     const dim3 g = team_grid(np, sh), b = team_block(sh);
     hipLaunchKernelGGL(k_cov_claim, g, b, 0, c->st, c->G, D, 0, sh);
-    hipLaunchKernelGGL(k_cov_scan<ST>, g, b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, sh);
-    const int ub = uncover_blocks(c, b.x);
-    hipLaunchKernelGGL(k_unc<ST>, dim3(ub + g.x), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, ub, sh);
+    const bool finish = np <= INT_BLOCK_MAX;  // in the same launch, by as many blocks as run together
+    hipLaunchKernelGGL(k_cov_scan<ST>, g, b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, sh, (int)finish);
+    if (!finish) hipLaunchKernelGGL(k_cov_apply<ST>, dim3(LIST_BLOCKS), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt);
+    const int ub = finish ? (b.x > 256 ? SYNC_BIG : SYNC_BLOCKS) : LIST_BLOCKS;
+    hipLaunchKernelGGL(k_unc<ST>, dim3(ub + g.x), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, ub, sh, (int)finish);
+    if (!finish) hipLaunchKernelGGL(k_unc_finish, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, D, D.phi_nxt);
     LAUNCHCHK(c);
     return FSL_OK;
 }
@@ -655,7 +654,8 @@ int enqueue_coverage_full(fsl_ctx *c) {
     if (Dv.np > 0) hipLaunchKernelGGL(k_cov_claim, team_grid(Dv.np, sh), team_block(sh), 0, c->st, c->G, Dv, 1, sh);
     hipLaunchKernelGGL(k_cov_scan_dense, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, c->G, Dv);
     hipLaunchKernelGGL(k_cov_apply<ST>, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, c->Ph, Dv, Dv.phi_cur);
-    hipLaunchKernelGGL(k_unc<ST>, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, c->Ph, Dv, Dv.phi_cur, LIST_BLOCKS, 6);
+    hipLaunchKernelGGL(k_unc<ST>, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, c->Ph, Dv, Dv.phi_cur, LIST_BLOCKS, 6, 0);
+    hipLaunchKernelGGL(k_unc_finish, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, Dv, Dv.phi_cur);
     hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(c->G.N, 256, 4096)), dim3(256), 0, c->st, Dv.claim,
                        c->G.N, CLAIM_NONE);
     LAUNCHCHK(c);

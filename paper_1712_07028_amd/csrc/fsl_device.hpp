@@ -75,10 +75,10 @@ enum Counter {
     C_NKT,    // tiles listed for the curvature
     C_BAR,    // arrivals at the grid barriers of the fused conversion phases
     C_BARS,   // ... of the fused labelling
+    C_BARU,   // ... of the uncover pass
     C_DONEC,  // blocks of the last conversion phase that are done
     C_DONEB,  // blocks of the bubble pass that are done
-    C_NUGAS,  // nodes uncovered as gas
-    C_DONEU,  // blocks of the uncover pass that are done
+    C_NUGAS,  // some node was uncovered as gas
     C_DONES,  // blocks of a splitting phase that are done
     C_COUNT
 };
@@ -174,7 +174,7 @@ struct Dev {
     int *lF, *lE0, *lE, *lNG, *lNL;  // conversion lists
     int *lCov, *lUnc;                // coverage events (cell, particle) pairs
     double *uncRho;                  // per uncover event: decided density
-    int *uncDec;                     // per uncover event: type | bubble << 8
+    int *uncDec;                     // per uncover event: the type decided
     int2 *merges, *pairs;
     int *counters, *counters_nxt;    // this step's set of counters and the next step's
     int *bused;                      // number of bubble ids in use

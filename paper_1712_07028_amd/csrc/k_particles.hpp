@@ -1080,10 +1080,13 @@ __device__ __forceinline__ double cover_cell(const Geom &G, const Phys &Ph, cons
 }
 
 // Walks the union of the old and new bounding boxes: nodes that the sphere covers become
-// its nodes at once, nodes that it leaves are marked (CV_UNC) and listed for k_unc.  The
-// ledger takes the covered mass summed per wave.
+// its nodes at once (apply) or are listed for k_cov_apply, nodes that it leaves are marked
+// (CV_UNC) and listed for k_unc.  The ledger takes the covered mass summed per wave.  Covering
+// at once saves small tables a launch; on large ones the populations of a covered cell are read
+// by a few lanes of each wave in turn (23,328 spheres, 99,000 cells a step: 2.71 ms against 1.28
+// and 0.07 apart).
 template <int ST>
-__global__ void k_cov_scan(Geom G, Phys Ph, Dev D, double *phi, int sh) {
+__global__ void k_cov_scan(Geom G, Phys Ph, Dev D, double *phi, int sh, int apply) {
     const Team T(blockIdx.x, sh);
     const int P = T.P;
     if (P >= D.np) return;
@@ -1103,7 +1106,7 @@ __global__ void k_cov_scan(Geom G, Phys Ph, Dev D, double *phi, int sh) {
     auto events = [&](bool cov, bool unc, int c) {
         wave_push2(cov, c, P, D.lCov, D.counters + C_NCOVER, D.capEv, D.err);
         wave_push2(unc, c, P, D.lUnc, D.counters + C_NUNCOVER, D.capEv, D.err);
-        if (cov) led += cover_cell<ST>(G, Ph, D, c, P, phi);
+        if (cov && apply) led += cover_cell<ST>(G, Ph, D, c, P, phi);
         if (unc) D.cv[c] = CV_UNC;
     };
     if (cov_claims(D, t)) {
@@ -1178,9 +1181,8 @@ __global__ void k_cov_scan_dense(Geom G, Dev D) {
     }
 }
 
-// the covered nodes of a whole new table; the ledger takes the mass summed per wave (one
-// atomic per wave): every wave of the block takes the same rounds, so the sums see whole
-// waves
+// the listed covered nodes; the ledger takes the mass summed per wave (one atomic per wave):
+// every wave of the block takes the same rounds, so the sums see whole waves
 template <int ST>
 __global__ void k_cov_apply(Geom G, Phys Ph, Dev D, double *phi) {
     const int n = event_len(D, C_NCOVER);
@@ -1195,9 +1197,50 @@ __global__ void k_cov_apply(Geom G, Phys Ph, Dev D, double *phi) {
 
 // Uncovered nodes (32 lanes each, lane q the neighbour along q): the decision with the cell
 // types after covering, every uncovered node still solid (its mark says so, whatever type
-// it shows by then), and the cell's new state.  The block that finishes last makes
+// it shows by then), and the cell's new state.  When all are decided, uncover_finish makes
 // interface cells of those that came to lie next to gas uncovered in this step (the
 // closure; only if there is any) and clears the marks.
+// the new state of node c, left by its sphere in event e, with nli liquid or interface neighbours
+// of densities rs in sum and the bubble of its first gas neighbour (-1: none)
+template <int ST>
+__device__ __forceinline__ void uncover_cell(const Geom &G, const Phys &Ph, const Dev &D, double *phi, int e, int c,
+                                             int nli, double rs, int bub) {
+    const int type = nli > 0 ? (bub >= 0 ? IFC : LIQ) : (bub >= 0 ? GAS : LIQ);
+    const double rb = nli > 0 ? rs / nli : 1.0;
+    D.uncDec[e] = type;
+    D.uncRho[e] = rb;
+    D.pid[c] = -1;
+    D.flags[c] = (uint8_t)type;
+    if (type == GAS) {
+        D.bub[c] = (uint16_t)bub;
+        phi[c] = 0.0;
+        __hip_atomic_store(D.counters + C_NUGAS, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+    const int P = D.lUnc[2 * e + 1];
+    float u0 = 0.f, u1 = 0.f, u2 = 0.f;
+    if ((unsigned)P < (unsigned)D.np) {
+        int x, y, z;
+        cell_xyz(G, c, x, y, z);
+        const double *t = D.ptab + (long long)P * P_STRIDE;
+        double rx = min_img(x - t[P_X], G.nx, G.per[0]), ry = min_img(y - t[P_X + 1], G.ny, G.per[1]),
+               rz = min_img(z - t[P_X + 2], G.nz, G.per[2]);
+        u0 = (float)(t[P_U] + (t[P_W + 1] * rz - t[P_W + 2] * ry));
+        u1 = (float)(t[P_U + 1] + (t[P_W + 2] * rx - t[P_W] * rz));
+        u2 = (float)(t[P_U + 2] + (t[P_W] * ry - t[P_W + 1] * rx));
+    }
+    store_equilibrium<ST>(G, Ph, D.fB, c, rb - 1.0, u0, u1, u2);
+    // the density of the stored populations, for rho_w (Eq. bbrule) in the next launch
+    if (D.rhow != nullptr && D.st_cur >= 0)
+        D.rhow[c] = rhow_word((float)cell_rho<ST>(G, D, Ph, D.fB, c), D.st_cur);
+    unsafeAtomicAdd(D.ledger, -rb);
+    phi[c] = 1.0;
+    if (type == IFC) {
+        D.m[c] = rb;
+        D.bub[c] = (uint16_t)bub;
+    }
+}
+
 template <int ST>
 __device__ __forceinline__ void uncover(const Geom &G, const Phys &Ph, const Dev &D, double *phi, const Items &W) {
     const int n = event_len(D, C_NUNCOVER);
@@ -1217,49 +1260,39 @@ __device__ __forceinline__ void uncover(const Geom &G, const Phys &Ph, const Dev
             const double rq = W.from(r, q);
             if ((ml >> q) & 1u) rs += rq;
         }
-        if (!has || W.q != 0) continue;
-        const int nli = __popc(ml);
-        const int type = nli > 0 ? (mg ? IFC : LIQ) : (mg ? GAS : LIQ);
-        const double rb = nli > 0 ? rs / nli : 1.0;
-        D.uncDec[e] = type;
-        D.uncRho[e] = rb;
-        D.pid[c] = -1;
-        D.flags[c] = (uint8_t)type;
-        if (type == GAS) {
-            D.bub[c] = (uint16_t)bub;
-            phi[c] = 0.0;
-            atomicAdd(D.counters + C_NUGAS, 1);
-            continue;
+        if (has && W.q == 0) uncover_cell<ST>(G, Ph, D, phi, e, c, __popc(ml), rs, mg ? bub : -1);
+    }
+}
+// ... a thread to a node, for lists that fill the device several times over: 32 lanes have one
+// neighbour each, most of them without populations to read (the 12.2 M nodes of a replaced table:
+// 27 ms against 76)
+template <int ST>
+__device__ __forceinline__ void uncover_each(const Geom &G, const Phys &Ph, const Dev &D, double *phi, int thread,
+                                             int nthreads) {
+    const int n = event_len(D, C_NUNCOVER);
+    for (int e = thread; e < n; e += nthreads) {
+        const int c = D.lUnc[2 * e];
+        int x, y, z, nli = 0, bub = -1;
+        cell_xyz(G, c, x, y, z);
+        double rs = 0.0;
+        for (int q = 1; q < Q; ++q) {
+            const int nb = nbr_idx(G, x, y, z, q, 1);
+            if (nb < 0 || (D.cv[nb] & CV_UNC)) continue;
+            const uint8_t f = D.flags[nb];
+            if (f == LIQ || f == IFC) {
+                rs += cell_rho<ST>(G, D, Ph, D.fB, nb);
+                ++nli;
+            } else if (f == GAS && bub < 0) {
+                bub = D.bub[nb];
+            }
         }
-        const int P = D.lUnc[2 * e + 1];
-        float u0 = 0.f, u1 = 0.f, u2 = 0.f;
-        if ((unsigned)P < (unsigned)D.np) {
-            int x, y, z;
-            cell_xyz(G, c, x, y, z);
-            const double *t = D.ptab + (long long)P * P_STRIDE;
-            double rx = min_img(x - t[P_X], G.nx, G.per[0]), ry = min_img(y - t[P_X + 1], G.ny, G.per[1]),
-                   rz = min_img(z - t[P_X + 2], G.nz, G.per[2]);
-            u0 = (float)(t[P_U] + (t[P_W + 1] * rz - t[P_W + 2] * ry));
-            u1 = (float)(t[P_U + 1] + (t[P_W + 2] * rx - t[P_W] * rz));
-            u2 = (float)(t[P_U + 2] + (t[P_W] * ry - t[P_W + 1] * rx));
-        }
-        store_equilibrium<ST>(G, Ph, D.fB, c, rb - 1.0, u0, u1, u2);
-        // the density of the stored populations, for rho_w (Eq. bbrule) in the next launch
-        if (D.rhow != nullptr && D.st_cur >= 0)
-            D.rhow[c] = rhow_word((float)cell_rho<ST>(G, D, Ph, D.fB, c), D.st_cur);
-        unsafeAtomicAdd(D.ledger, -rb);
-        phi[c] = 1.0;
-        if (type == IFC) {
-            D.m[c] = rb;
-            D.bub[c] = (uint16_t)bub;
-        }
+        uncover_cell<ST>(G, Ph, D, phi, e, c, nli, rs, bub);
     }
 }
 
-// an uncovered liquid cell next to gas becomes interface.  One block.
-__device__ __forceinline__ void uncover_closure(const Geom &G, const Dev &D, double *phi) {
+// an uncovered liquid cell next to gas becomes interface
+__device__ __forceinline__ void uncover_closure(const Geom &G, const Dev &D, double *phi, const Items &W) {
     const int n = event_len(D, C_NUNCOVER);
-    const Items W(0, 1);
     ITEM_LOOP(W, e, n) {
         const bool has = e < n && D.uncDec[e < n ? e : 0] == LIQ;
         const int c = has ? D.lUnc[2 * e] : 0;
@@ -1273,18 +1306,43 @@ __device__ __forceinline__ void uncover_closure(const Geom &G, const Dev &D, dou
     }
 }
 
-// the first unc_blocks blocks take the uncovered nodes, the others (threads by sphere as
-// in k_cov_claim) take back the claims, which the scan before was the last to read
+// closure and marks, by the blocks of W together; neither touches what the other reads
+__device__ __forceinline__ void uncover_finish(const Geom &G, const Dev &D, double *phi, const Items &W, int block,
+                                               int nblk) {
+    const int n = event_len(D, C_NUNCOVER);
+    if (__hip_atomic_load(D.counters + C_NUGAS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0)
+        uncover_closure(G, D, phi, W);
+    // new gas stays marked for the splitting test
+    for (int e = block * blockDim.x + threadIdx.x; e < n; e += nblk * blockDim.x)
+        D.cv[D.lUnc[2 * e]] = D.uncDec[e] == GAS ? CV_GAD : 0;
+}
+// A launch of its own where the nodes may be many (large tables, a table that is replaced):
+// 23,328 spheres of radius 5 moving at 0.05 through the surface of a 512 x 512 x 256 pool take
+// 1.6 ms of coverage a step, and replacing the table (12.2 M nodes) 27 ms; 11.4 ms and 1.3 s when
+// the block that finished last did this for all nodes.
+__global__ __launch_bounds__(256) void k_unc_finish(Geom G, Dev D, double *phi) {
+    uncover_finish(G, D, phi, Items(blockIdx.x, gridDim.x), blockIdx.x, gridDim.x);
+}
+
+// The first unc_blocks blocks take the uncovered nodes, the others (threads by sphere as
+// in k_cov_claim) take back the claims, which the scan before was the last to read.
+// finish: as many of the former as the nodes fill, two to a half wave, go on to uncover_finish
+// after a grid barrier (small tables); else k_unc_finish follows.
 template <int ST>
-__global__ __launch_bounds__(1024) void k_unc(Geom G, Phys Ph, Dev D, double *phi, int unc_blocks, int sh) {
+__global__ __launch_bounds__(1024) void k_unc(Geom G, Phys Ph, Dev D, double *phi, int unc_blocks, int sh, int finish) {
     if ((int)blockIdx.x < unc_blocks) {
-        uncover<ST>(G, Ph, D, phi, Items(blockIdx.x, unc_blocks));
-        if (!last_block(D.counters + C_DONEU, unc_blocks)) return;
-        const int ng = __hip_atomic_load(D.counters + C_NUGAS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (ng > 0) uncover_closure(G, D, phi);
-        const int n = event_len(D, C_NUNCOVER);
-        // new gas stays marked for the splitting test
-        for (int e = threadIdx.x; e < n; e += blockDim.x) D.cv[D.lUnc[2 * e]] = D.uncDec[e] == GAS ? CV_GAD : 0;
+        const int per = (int)(blockDim.x >> 4);
+        const int nblk = min(unc_blocks, max(1, (event_len(D, C_NUNCOVER) + per - 1) / per));
+        if ((int)blockIdx.x >= nblk) return;
+        const Items W(blockIdx.x, nblk);
+        if (!finish && event_len(D, C_NUNCOVER) > 4 * W.ngrp) {
+            uncover_each<ST>(G, Ph, D, phi, blockIdx.x * blockDim.x + threadIdx.x, nblk * blockDim.x);
+            return;
+        }
+        uncover<ST>(G, Ph, D, phi, W);
+        if (!finish) return;
+        GridBarrier{D.counters + C_BARU, nblk, 0, D.err}.wait();
+        uncover_finish(G, D, phi, W, blockIdx.x, nblk);
         return;
     }
     const Team T(blockIdx.x - unc_blocks, sh);
