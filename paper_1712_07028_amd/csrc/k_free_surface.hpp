@@ -165,8 +165,50 @@ __device__ __forceinline__ int lane_nbr(const Geom &G, int c, int q, bool has) {
     return a + G.nx * (b + G.ny * d);
 }
 
-template <int ST>
-__device__ __forceinline__ void conv_closure(const Geom &G, const Phys &Ph, const Dev &D, const Items &W) {
+// the lists that the closure phase makes
+enum { L_E, L_NL, L_NG, L_N };
+__device__ __forceinline__ int *conv_list(const Dev &D, int k) { return k == L_E ? D.lE : k == L_NL ? D.lNL : D.lNG; }
+__device__ __forceinline__ int *conv_count(const Dev &D, int k) {
+    return D.counters + (k == L_E ? C_NE : k == L_NL ? C_NNL : C_NNG);
+}
+// The entries of a block gathered in LDS, for launches of many blocks: one atomic per wave and
+// round on three counters of one line queues (tens of thousands of listed cells on a 512 x 512
+// surface that 23,328 spheres cross: 611 us a launch against 50).
+struct ListBuf {
+    static constexpr int CAP = 512;
+    int n[L_N], base[L_N], buf[L_N][CAP];
+    __device__ __forceinline__ void open() {
+        if (threadIdx.x < L_N) n[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    __device__ __forceinline__ void push(const Dev &D, int k, bool pred, int value) {
+        const unsigned long long mask = __ballot(pred);
+        if (!mask) return;
+        const int leader = __ffsll((long long)mask) - 1;
+        int at = 0;
+        if ((int)lane_id() == leader) at = atomicAdd(&n[k], __popcll(mask));
+        at = __shfl(at, leader) + __popcll(mask & ((1ull << lane_id()) - 1ull));
+        if (pred && at < CAP) buf[k][at] = value;
+        wave_append(pred && at >= CAP, value, conv_list(D, k), conv_count(D, k), D.cap, D.err);
+    }
+    __device__ __forceinline__ void close(const Dev &D) {
+        __syncthreads();
+        if (threadIdx.x < L_N) {
+            const int m = min(n[threadIdx.x], CAP);
+            base[threadIdx.x] = m ? atomicAdd(conv_count(D, threadIdx.x), m) : 0;
+        }
+        __syncthreads();
+        for (int k = 0; k < L_N; ++k)
+            for (int i = threadIdx.x; i < min(n[k], CAP); i += blockDim.x) {
+                if (base[k] + i < D.cap) conv_list(D, k)[base[k] + i] = buf[k][i];
+                else atomicOr(D.err, ERR_CAP);
+            }
+    }
+};
+
+// push(k, pred, value): appends to list k; every lane of the wave calls it
+template <int ST, typename Push>
+__device__ __forceinline__ void conv_closure(const Geom &G, const Phys &Ph, const Dev &D, const Items &W, Push &&push) {
     const int nF = list_len(D, C_NF), nE = list_len(D, C_NE0);
     ITEM_LOOP(W, i, nE) {
         const bool has = i < nE;
@@ -175,9 +217,9 @@ __device__ __forceinline__ void conv_closure(const Geom &G, const Phys &Ph, cons
         const uint8_t nm = n >= 0 ? D.cv[n] : 0, nf = n >= 0 ? D.flags[n] : WALL;
         const bool keep = has && W.any(nm == CV_F) == 0u;
         if (keep && W.q == 0) cv_or(D.cv, c, CV_E);
-        wave_append(keep && W.q == 0, c, D.lE, D.counters + C_NE, D.cap, D.err);
+        push(L_E, keep && W.q == 0, c);
         const bool won = keep && nf == LIQ && !(cv_or(D.cv, n, CV_NEWL) & CV_NEWL);
-        wave_append(won, n, D.lNL, D.counters + C_NNL, D.cap, D.err);
+        push(L_NL, won, n);
         if (won) D.m[n] = cell_rho<ST>(G, D, Ph, D.fB, n);
     }
     ITEM_LOOP(W, j, nF) {
@@ -185,7 +227,7 @@ __device__ __forceinline__ void conv_closure(const Geom &G, const Phys &Ph, cons
         const int c = has ? D.lF[j] : 0;
         const int n = lane_nbr(G, c, W.q, has);
         const bool won = n >= 0 && D.flags[n] == GAS && !(cv_or(D.cv, n, CV_NEWG) & CV_NEWG);
-        wave_append(won, n, D.lNG, D.counters + C_NNG, D.cap, D.err);
+        push(L_NG, won, n);
         if (won) D.m[n] = 0.0;
     }
 }
@@ -325,7 +367,11 @@ __device__ __forceinline__ void merge_bubbles(const Dev &D) {
 // The phases as one launch each (large boxes: any number of listed cells) ...
 template <int ST>
 __global__ __launch_bounds__(256) void k_conv_closure(Geom G, Phys Ph, Dev D) {
-    conv_closure<ST>(G, Ph, D, Items(blockIdx.x, gridDim.x));
+    __shared__ ListBuf L;
+    L.open();
+    conv_closure<ST>(G, Ph, D, Items(blockIdx.x, gridDim.x),
+                     [&](int k, bool pred, int value) { L.push(D, k, pred, value); });
+    L.close(D);
 }
 template <int ST>
 __global__ __launch_bounds__(256) void k_conv_change(Geom G, Phys Ph, Dev D) {
@@ -346,7 +392,9 @@ __device__ __forceinline__ void conversions(const Geom &G, const Phys &Ph, const
     if ((int)blockIdx.x >= nblk) return;
     GridBarrier B{D.counters + C_BAR, nblk, 0, D.err};
     const Items W(blockIdx.x, nblk);
-    conv_closure<ST>(G, Ph, D, W);
+    conv_closure<ST>(G, Ph, D, W, [&](int k, bool pred, int value) {
+        wave_append(pred, value, conv_list(D, k), conv_count(D, k), D.cap, D.err);
+    });
     B.wait();
     conv_change<ST>(G, Ph, D, W);
     B.wait();
