@@ -295,9 +295,15 @@ void set_phys(fsl_ctx *c) {
     }
     c->Ph.open_atm = f.open_atmosphere != 0;
     c->Ph.inv = 1.0f / c->Ph.scale;
-    // FSL_WIDE_OFFSETS=1 takes the 64-bit form on any box (a test of that form)
-    const char *wide = getenv("FSL_WIDE_OFFSETS");
-    c->Ph.wide = c->G.S * 4 * esize(f.storage) > (1ll << 32) || (wide && wide[0] == '1');
+    // 2^28 cells in FP32 (the 512 x 512 x 1024 column) and 2^29 in 16 bits keep byte offsets, up to
+    // 2^30 offsets in elements fit (FP32 pool of 512 x 512 x 1300, us a launch: 10,455 against
+    // 10,650 in 64 bits, with 80,000 spheres 13,573 and 13,900).  FSL_WIDE_OFFSETS=1 takes the 64-bit form on any box, =pair the form
+    // between (tests of those forms).
+    c->Ph.wide = c->G.S * 4 * esize(f.storage) <= (1ll << 32) ? 0 : c->G.S < (1ll << 30) ? 1 : 2;
+    if (const char *wide = getenv("FSL_WIDE_OFFSETS")) {
+        if (wide[0] == '1') c->Ph.wide = 2;
+        if (wide[0] == 'p') c->Ph.wide = std::max(c->Ph.wide, 1);
+    }
 }
 
 // one lattice update of every cell: the marching pass over the liquid cells, then the

@@ -161,8 +161,9 @@ struct Phys {
                        // then take the general path
     int slip[3];       // the faces of axis a are free-slip
     int open_atm;      // bubble 0 is held at its density (pressure outlet)
-    int wide;          // the march takes 64-bit addresses (boxes where the byte offset within
-                       // a pair of opposite planes, below four planes, leaves 32 bits)
+    int wide;          // offsets that leave 32 bits: 0 none, 1 the byte offset within a pair of
+                       // opposite planes (below four planes; that of one plane and the pair's in
+                       // elements fit), 2 the pair's in elements as well
 };
 
 struct Dev {

@@ -302,7 +302,7 @@ __device__ __forceinline__ bool collide_store(const Phys &Ph, const float (&fi)[
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             // NT: the march; byte offsets of 32 bits from the plane (see Phys::wide)
-            if (NT && !Ph.wide) __builtin_nontemporal_store(out[q], at_byte(B + q * S, c * (unsigned)sizeof(T)));
+            if (NT && Ph.wide < 2) __builtin_nontemporal_store(out[q], at_byte(B + q * S, c * (unsigned)sizeof(T)));
             else if (NT) __builtin_nontemporal_store(out[q], B + q * S + c);
             else B[q * S + c] = out[q];
         }
@@ -1069,23 +1069,40 @@ __device__ __forceinline__ void march_cell(MarchLds &L, int sm1, int s0, int sp1
         // opp(q) share the base of the lower one.
         if (in_mask(act)) {  // lanes without a liquid cell load nothing
             const unsigned c4 = (unsigned)c * ES, S4 = (unsigned)S * ES;
-            if (!M.Ph.wide) {
+            const bool plain = (link | wx0 | wx1 | wy0 | wy1 | wz0 | wz1) == 0ull;
+            const int wide = M.Ph.wide;
+            if (plain && wide < 2) {
                 fi[0] = SS::dec(*at_byte(A, c4), inv);
-                if ((link | wx0 | wx1 | wy0 | wy1 | wz0 | wz1) == 0ull) {
-                    for_dirs([&](auto qc) {
-                        constexpr int q = decltype(qc)::value;
-                        fi[q] = SS::dec(*at_byte(A + q * S, c4 + (unsigned)src_off<q>(so) * ES), inv);
-                    });
-                } else {
-                    for_dirs([&](auto qc) {
-                        constexpr int q = decltype(qc)::value;
-                        constexpr int lo = q < opp(q) ? q : opp(q);
-                        const unsigned pull = c4 + (unsigned)src_off<q>(so) * ES + (unsigned)(q - lo) * S4;
-                        unsigned o = in_mask(bounce(qc)) ? c4 + (unsigned)(opp(q) - lo) * S4 : pull;
-                        __asm__("" : "+v"(o));
-                        fi[q] = SS::dec(*at_byte(A + lo * S, o), inv);
-                    });
-                }
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    fi[q] = SS::dec(*at_byte(A + q * S, c4 + (unsigned)src_off<q>(so) * ES), inv);
+                });
+            } else if (wide == 0) {
+                fi[0] = SS::dec(*at_byte(A, c4), inv);
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    constexpr int lo = q < opp(q) ? q : opp(q);
+                    const unsigned pull = c4 + (unsigned)src_off<q>(so) * ES + (unsigned)(q - lo) * S4;
+                    unsigned o = in_mask(bounce(qc)) ? c4 + (unsigned)(opp(q) - lo) * S4 : pull;
+                    __asm__("" : "+v"(o));
+                    fi[q] = SS::dec(*at_byte(A + lo * S, o), inv);
+                });
+            } else if (wide == 1) {
+                fi[0] = SS::ld(A + (unsigned)c, inv);
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    constexpr int lo = q < opp(q) ? q : opp(q);
+                    const unsigned pull = (unsigned)(c + src_off<q>(so)) + (unsigned)(q - lo) * (unsigned)S;
+                    unsigned o = in_mask(bounce(qc)) ? (unsigned)c + (unsigned)(opp(q) - lo) * (unsigned)S : pull;
+                    __asm__("" : "+v"(o));
+                    fi[q] = SS::ld(A + lo * S + o, inv);
+                });
+            } else if (plain) {
+                fi[0] = SS::ld(A + (unsigned)c, inv);
+                for_dirs([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    fi[q] = SS::ld(A + q * S + (unsigned)(c + src_off<q>(so)), inv);
+                });
             } else {
                 fi[0] = SS::ld(A + (unsigned)c, inv);
                 for_dirs([&](auto qc) {
