@@ -1326,12 +1326,12 @@ __global__ __launch_bounds__(256) void k_unc_finish(Geom G, Dev D, double *phi) 
 
 // The first unc_blocks blocks take the uncovered nodes, the others (threads by sphere as
 // in k_cov_claim) take back the claims, which the scan before was the last to read.
-// finish: as many of the former as the nodes fill, two to a half wave, go on to uncover_finish
+// finish: as many of the former as the nodes fill, one to a half wave, go on to uncover_finish
 // after a grid barrier (small tables); else k_unc_finish follows.
 template <int ST>
 __global__ __launch_bounds__(1024) void k_unc(Geom G, Phys Ph, Dev D, double *phi, int unc_blocks, int sh, int finish) {
     if ((int)blockIdx.x < unc_blocks) {
-        const int per = (int)(blockDim.x >> 4);
+        const int per = (int)(blockDim.x >> 5);
         const int nblk = min(unc_blocks, max(1, (event_len(D, C_NUNCOVER) + per - 1) / per));
         if ((int)blockIdx.x >= nblk) return;
         const Items W(blockIdx.x, nblk);
