@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/fsl.h"
+#include "sync_rule.hpp"
 #include "k_init.hpp"
 #include "k_particles.hpp"
 #include "k_split.hpp"
@@ -188,6 +189,11 @@ struct fsl_ctx {
     int ncell;
     int tilesX, tilesY, nTiles;
     int cus;  // compute units of the device
+    // blocks of each launch with grid barriers that may wait for one another (sync_blocks); 0: a
+    // launch per phase
+    struct {
+        int conv, conv_int[2], split, unc[2];
+    } sync;
     int profiling;
     int have_prev;  // a previous step's hydrodynamic force exists (particle update)
     int stamp;      // stamp of the next stream-collide launch (>= 1)
@@ -385,6 +391,24 @@ template <int ST> int enqueue_bubbles(fsl_ctx *c, double *phi, int init, int tes
 bool fused_phases(const fsl_ctx *c) { return c->G.N <= (1ll << 22); }
 
 template <int ST>
+void set_sync(fsl_ctx *c) {
+    auto of = [&](auto kernel, int threads, int want) {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, threads, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            per_cu = 0;
+        }
+        return sync_blocks(want, c->cus, per_cu);
+    };
+    c->sync.conv = of(k_conversions<ST>, 1024, SYNC_BIG);
+    c->sync.conv_int[0] = of(k_conv_integrate<ST, 1>, 1024, SYNC_BIG);
+    c->sync.conv_int[1] = of(k_conv_integrate<ST, 2>, 1024, SYNC_BIG);
+    c->sync.split = of(k_split, 256, SYNC_BLOCKS);
+    c->sync.unc[0] = of(k_unc<ST>, 256, SYNC_BLOCKS);
+    c->sync.unc[1] = of(k_unc<ST>, 1024, SYNC_BIG);
+}
+
+template <int ST>
 int enqueue_bubbles(fsl_ctx *c, double *phi, int init, int test) {
     ProfScope ps(c, 2);
     Dev &D = c->D;
@@ -406,8 +430,8 @@ int enqueue_split(fsl_ctx *c, const double *phi, int force) {
     // a forced labelling (setting up a state, or a table set from outside) keeps a launch per
     // phase: without gas 90 x 53 x 71 cells take 0.14 ms less than in one launch (its 128 blocks
     // walk the whole box six times); with gas on 128^3 it is 1.3 against 1.0 ms, once per state
-    if (fused_phases(c) && !force) {
-        hipLaunchKernelGGL(k_split, dim3(SYNC_BLOCKS), b, 0, c->st, c->G, D, B, phi, force, c->Ph.open_atm);
+    if (fused_phases(c) && !force && c->sync.split) {
+        hipLaunchKernelGGL(k_split, dim3(c->sync.split), b, 0, c->st, c->G, D, B, phi, force, c->Ph.open_atm);
     } else {
         hipLaunchKernelGGL(k_split_start, gn, b, 0, c->st, c->G, D, B, force);
         hipLaunchKernelGGL(k_ccl_union, gn, b, 0, c->st, c->G, D, B, force);
@@ -437,8 +461,8 @@ int enqueue_conversions(fsl_ctx *c) {
     ProfScope ps(c, 1);
     Dev &D = c->D;
     dim3 g(LIST_BLOCKS), b(256);
-    if (fused_phases(c)) {
-        hipLaunchKernelGGL(k_conversions<ST>, dim3(SYNC_BIG), dim3(1024), 0, c->st, c->G, c->Ph, D);
+    if (fused_phases(c) && c->sync.conv) {
+        hipLaunchKernelGGL(k_conversions<ST>, dim3(c->sync.conv), dim3(1024), 0, c->st, c->G, c->Ph, D);
     } else {
         hipLaunchKernelGGL(k_conv_closure<ST>, g, b, 0, c->st, c->G, c->Ph, D);
         hipLaunchKernelGGL(k_conv_change<ST>, g, b, 0, c->st, c->G, c->Ph, D);
@@ -470,10 +494,11 @@ int enqueue_coverage_step(fsl_ctx *c) {
     const int sh = team_shift(np);
     const dim3 g = team_grid(np, sh), b = team_block(sh);
     hipLaunchKernelGGL(k_cov_claim, g, b, 0, c->st, c->G, D, 0, sh);
-    const bool finish = np <= INT_BLOCK_MAX;  // in the same launch, by as many blocks as run together
+    const int usync = c->sync.unc[b.x > 256];
+    const bool finish = np <= INT_BLOCK_MAX && usync;  // in the same launch
     hipLaunchKernelGGL(k_cov_scan<ST>, g, b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, sh, (int)finish);
     if (!finish) hipLaunchKernelGGL(k_cov_apply<ST>, dim3(LIST_BLOCKS), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt);
-    const int ub = finish ? (b.x > 256 ? SYNC_BIG : SYNC_BLOCKS) : LIST_BLOCKS;
+    const int ub = finish ? usync : LIST_BLOCKS;
     hipLaunchKernelGGL(k_unc<ST>, dim3(ub + g.x), b, 0, c->st, c->G, c->Ph, D, D.phi_nxt, ub, sh, (int)finish);
     if (!finish) hipLaunchKernelGGL(k_unc_finish, dim3(LIST_BLOCKS), dim3(256), 0, c->st, c->G, D, D.phi_nxt);
     LAUNCHCHK(c);
@@ -554,10 +579,11 @@ int enqueue_integration(fsl_ctx *c, bool conversions) {
         if (c->cfg.boundary[a] == FSL_NOSLIP) wmask |= 1 << a;
     if (np <= INT_BLOCK_MAX) {
         const IntArgs A{ns, mu, c->cfg.contact_k, c->L.pcap, {c->cfg.g[0], c->cfg.g[1], c->cfg.g[2]}, c->have_prev, wmask};
-        const dim3 g(int_blocks(np)), gc(SYNC_BIG + int_blocks(np)), b(1024);
+        const int nc = c->sync.conv_int[np > 1024];
+        const dim3 g(int_blocks(np)), gc(nc + int_blocks(np)), b(1024);
         if (conversions) {
-            if (np <= 1024) hipLaunchKernelGGL((k_conv_integrate<ST, 1>), gc, b, 0, c->st, c->G, c->Ph, D, A);
-            else hipLaunchKernelGGL((k_conv_integrate<ST, 2>), gc, b, 0, c->st, c->G, c->Ph, D, A);
+            if (np <= 1024) hipLaunchKernelGGL((k_conv_integrate<ST, 1>), gc, b, 0, c->st, c->G, c->Ph, D, A, nc);
+            else hipLaunchKernelGGL((k_conv_integrate<ST, 2>), gc, b, 0, c->st, c->G, c->Ph, D, A, nc);
         } else {
             if (np <= 1024) hipLaunchKernelGGL(k_integrate<1>, g, b, 0, c->st, c->G, D, A);
             else hipLaunchKernelGGL(k_integrate<2>, g, b, 0, c->st, c->G, D, A);
@@ -620,7 +646,8 @@ int enqueue_steps(fsl_ctx *c, int n) {
         } else {
             c->rhow_ok = 1;
         }
-        const bool conv = c->gas, both = conv && joined && c->cfg.integrate && fused_phases(c);
+        const bool conv = c->gas, both = conv && joined && c->cfg.integrate && fused_phases(c) &&
+                                            c->sync.conv_int[D.np > 1024];
         if (conv && !both) {
             rc = enqueue_conversions<ST>(c);
             if (rc) return rc;
@@ -984,6 +1011,10 @@ static int init_ctx(const fsl_config *cfg, const Layout &L, char *d_ws, char *d_
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
         c->cus = cus;
+        by_storage(c, [&](auto st) {
+            set_sync<decltype(st)::value>(c);
+            return FSL_OK;
+        });
     }
     c->profiling = 0;
     for (int k = 0; k < NPROF; ++k) { c->prof_ms[k] = 0; c->prof_n[k] = 0; }

@@ -312,10 +312,9 @@ __device__ __forceinline__ void block_phase() {
 }
 
 // A barrier between two phases over the first nblk blocks of a launch.  The callers launch
-// at most SYNC_BLOCKS blocks of 256 threads (or SYNC_BIG of 1,024), a sixteenth of what the device holds, so the
-// blocks come to run together whatever else is running (kernels in other streams end, and
-// sixteen launches of this kind at once would still fit); one block needs no device
-// barrier.  bar counts arrivals since the step's counters were cleared, target the
+// at most SYNC_BLOCKS blocks of 256 threads (or SYNC_BIG of 1,024), and no more than an eighth of
+// what the device holds of that kernel (sync_rule.hpp, from its occupancy), so the blocks come
+// to run together whatever else is running; one block needs no device barrier.  bar counts arrivals since the step's counters were cleared, target the
 // arrivals the next barrier waits for.  Every wave's stores have left the wave before its
 // block arrives; one thread releases them to the device and acquires the others'.  The
 // wait is bounded: a launch that lost a block reports an error instead of hanging.

@@ -983,11 +983,11 @@ __global__ __launch_bounds__(1024) void k_integrate(Geom G, Dev D, IntArgs A) {
     integrate<NPT>(G, D, A, blockIdx.x);
 }
 // ... beside the conversions of the step, which neither read nor write the sphere table (the
-// first SYNC_BIG blocks; apart 18 and 23 us on a bed of 128^3, together 34)
+// first nconv blocks; apart 18 and 23 us on a bed of 128^3, together 34)
 template <int ST, int NPT>
-__global__ __launch_bounds__(1024) void k_conv_integrate(Geom G, Phys Ph, Dev D, IntArgs A) {
-    if ((int)blockIdx.x < SYNC_BIG) conversions<ST>(G, Ph, D, SYNC_BIG);
-    else integrate<NPT>(G, D, A, blockIdx.x - SYNC_BIG);
+__global__ __launch_bounds__(1024) void k_conv_integrate(Geom G, Phys Ph, Dev D, IntArgs A, int nconv) {
+    if ((int)blockIdx.x < nconv) conversions<ST>(G, Ph, D, nconv);
+    else integrate<NPT>(G, D, A, blockIdx.x - nconv);
 }
 
 // ---- coverage update --------------------------------------------------------------
