@@ -431,7 +431,7 @@ int enqueue_split(fsl_ctx *c, const double *phi, int force) {
     // phase: without gas 90 x 53 x 71 cells take 0.14 ms less than in one launch (its 128 blocks
     // walk the whole box six times); with gas on 128^3 it is 1.3 against 1.0 ms, once per state
     if (fused_phases(c) && !force && c->sync.split) {
-        hipLaunchKernelGGL(k_split, dim3(c->sync.split), b, 0, c->st, c->G, D, B, phi, force, c->Ph.open_atm);
+        hipLaunchKernelGGL(k_split, dim3(c->sync.split), b, 0, c->st, c->G, D, B, phi, c->Ph.open_atm);
     } else {
         hipLaunchKernelGGL(k_split_start, gn, b, 0, c->st, c->G, D, B, force);
         hipLaunchKernelGGL(k_ccl_union, gn, b, 0, c->st, c->G, D, B, force);
@@ -1121,10 +1121,10 @@ int fsl_init_static(const fsl_config *cfg, void *d_state, size_t *bytes, void *h
 
 }  // extern "C"
 
-// Steps as a HIP graph: launch-bound small boxes issue about 60 kernels per step.  Two
-// steps are captured (lattice and fill-level buffers swap back, and the stored-density
-// parities alternate as in eager steps); the host state that the capture advanced is
-// restored, and each replay advances it by two steps.
+// Steps as a HIP graph: small boxes issue a few launches of some microseconds each, faster than
+// the host issues them.  Two steps are captured (lattice and fill-level buffers swap back, and
+// the stored-density parities alternate as in eager steps); the host state that the capture
+// advanced is restored, and each replay advances it by two steps.
 template <int ST>
 static int capture_pair(fsl_ctx *c) {
     const Dev D0 = c->D;

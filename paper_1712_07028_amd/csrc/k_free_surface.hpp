@@ -114,12 +114,6 @@ __device__ __forceinline__ int list_len(const Dev &D, int which) {
     return n < D.cap ? n : D.cap;
 }
 
-__device__ __forceinline__ void list_push(const Dev &D, int *list, int which, int v) {
-    int s = atomicAdd(D.counters + which, 1);
-    if (s < D.cap) list[s] = v;
-    else atomicOr(D.err, ERR_CAP);
-}
-
 #define GRID_STRIDE(i, n) for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += gridDim.x * blockDim.x)
 
 // root of a bubble id through the merge table; ids outside the table map to 0
@@ -577,39 +571,13 @@ __device__ __forceinline__ void bubble_finalize(const Dev &D, int init, int open
 // ---- surface tension: interface curvature (end of Sec. 2.2) ----------------------
 // The fill level as the curvature sees it: liquid and particle nodes 1 (perfect
 // wetting), gas 0, interface cells their fill level; a position beyond a wall takes
-// the nearest cell inside the box, a periodic one wraps.
-__device__ __forceinline__ int st_axis(int v, int n, int per) {
-    if (per) return v < 0 ? v + n : (v >= n ? v - n : v);
-    return v < 0 ? 0 : (v >= n ? n - 1 : v);
-}
-__device__ __forceinline__ double st_fill(const Geom &G, const Dev &D, const double *phi, int i, int j, int k) {
-    i = st_axis(i, G.nx, G.per[0]);
-    j = st_axis(j, G.ny, G.per[1]);
-    k = st_axis(k, G.nz, G.per[2]);
-    const long long c = i + (long long)G.nx * (j + (long long)G.ny * k);
-    const uint8_t f = D.flags[c];
-    return f == GAS ? 0.0 : (f == IFC ? phi[c] : 1.0);
-}
+// the nearest cell inside the box, a periodic one wraps (k_curv_tiles).
+
 // Parker-Youngs weighted central differences over the 3x3x3 block: a cell displaced
 // along the axis of the derivative counts 4, 2 or 1 for 0, 1 or 2 nonzero
 // transverse offsets (sum 16, distance 2)
 __device__ __forceinline__ double st_w(int a, int b) {
     return (a == 0 && b == 0) ? 4.0 : ((a == 0 || b == 0) ? 2.0 : 1.0);
-}
-__device__ void st_normal(const Geom &G, const Dev &D, const double *phi, int i, int j, int k, double n[3]) {
-    n[0] = n[1] = n[2] = 0.0;
-    for (int dz = -1; dz <= 1; ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (!dx && !dy && !dz) continue;
-                const double v = st_fill(G, D, phi, i + dx, j + dy, k + dz);
-                if (dx) n[0] += dx * st_w(dy, dz) * v;
-                if (dy) n[1] += dy * st_w(dx, dz) * v;
-                if (dz) n[2] += dz * st_w(dx, dy) * v;
-            }
-    n[0] *= 1.0 / 32.0;
-    n[1] *= 1.0 / 32.0;
-    n[2] *= 1.0 / 32.0;
 }
 // kappa = -(1/2) div(n/|n|) at every interface cell: the mean curvature, so that
 // 2 sigma kappa is the Laplace jump (a gas bubble of radius R has kappa = -1/R).

@@ -333,16 +333,15 @@ __device__ __forceinline__ void split_mass(const Dev &D, const SplitBuf &B, Mass
 
 // The labelling and the split in one launch (small boxes, where six more launches cost more
 // than the step has to spare): the blocks return after clearing the marks when there is
-// nothing to do.  force: label regardless of the test (initial state, new tables or
-// particles).
-__global__ __launch_bounds__(256) void k_split(Geom G, Dev D, SplitBuf B, const double *phi, int force, int open) {
+// nothing to do.
+__global__ __launch_bounds__(256) void k_split(Geom G, Dev D, SplitBuf B, const double *phi, int open) {
     __shared__ union {
         PlanLds P;
         MassLds S;
         BubbleLds V;
     } L;
     const Threads T{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x};
-    const bool run = force || D.counters[C_SPLIT] != 0;
+    const bool run = D.counters[C_SPLIT] != 0;
     split_clear(D, T);
     if (!run) return;
     GridBarrier GB{D.counters + C_BARS, (int)gridDim.x, 0, D.err};
@@ -367,7 +366,8 @@ __global__ __launch_bounds__(256) void k_split(Geom G, Dev D, SplitBuf B, const 
 
 // The same as a launch per phase, for boxes where the labelling wants the whole device (a
 // phase of a few values goes to the block that finishes the one before it); each returns
-// at once when there is nothing to do.
+// at once when there is nothing to do.  force: label regardless of the test (initial state,
+// new tables or particles).
 __global__ void k_split_start(Geom G, Dev D, SplitBuf B, int force) {
     const Threads T{blockIdx.x * (long long)blockDim.x + threadIdx.x, (long long)gridDim.x * blockDim.x};
     split_clear(D, T);
