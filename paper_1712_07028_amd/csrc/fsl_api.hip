@@ -327,11 +327,12 @@ void launch_stream_collide_mw(fsl_ctx *c, const Dev &Dv, const SolidArgs &SA) {
     // ones on large boxes.  Powers of two beyond 2 are left out, 6 % slower where the box is
     // one too (384 x 256 x 512, us: 3: 1564, 4: 1631, 6: 1518, 8: 1609, 10: 1519, 12: 1513, 14: 1529,
     // 16: 1605), and so are odd numbers, 2 to 4 % slower on the 512 x 512 x 1024 column (ms, 10 to
-    // 15: 10.29, 10.57, 10.17, 10.49, 10.12, 10.45).
+    // 15: 10.29, 10.57, 10.17, 10.49, 10.12, 10.45).  Not so on 512 x 512 x 1024 without spheres
+    // (ms, 8: 7.97, 10: 8.25, 14: 8.29, 16: 7.96; 8.59 with 16 before the masks).
     // With spheres a lane sums its links over a block's planes, so that their number decides
     // the last bits of the forces: it depends on the box alone then, the largest power of two
     // up to 16 that leaves 2,048 blocks (column 16 planes, 10.3 ms a launch against 10.1 with
-    // 14; 128^3 bed 4 planes, 111 us against 106 with 3).
+    // 14; 128^3 bed 4 planes, 111 us against 106 with 3, all with the sums of a block in a table).
     const long long cols = (long long)c->tilesX * c->tilesY, dev = 4ll * c->cus;
     auto blocks = [&](int k) { return cols * ((c->G.nz + k - 1) / k); };
     int nzc = 1;

@@ -383,7 +383,40 @@ __device__ __forceinline__ double wave_sum(double v) {
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), 63);
     return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-// The same by halves of the wave (32, 16, ... 1).  The links between spheres and at faces take
+// Seven such sums at once, each in the tree of wave_sum (lanes pairwise by bit 0, 1, ... 5 of
+// their number; the order of a pair does not matter).  In the first three rounds a lane
+// keeps half of what it holds and hands the other half to its partner, so that four, two and
+// one additions stand for seven each; lane ln ends with the sum of component wave_part(ln) (7: none).
+// Every lane of the wave must be active.
+__device__ __forceinline__ int wave_part(int ln) { return 4 * (ln & 1) + (ln & 2) + ((ln >> 2) & 1); }
+template <typename X> __device__ __forceinline__ double wave_swap(double v, X &&x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)x((int)(unsigned)b), hi = (unsigned)x((int)(unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sums7(const double (&v)[7]) {
+    const int ln = (int)lane_id();
+    auto dpp1 = [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, false); };   // quad_perm [1,0,3,2]
+    auto dpp2 = [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, false); };   // quad_perm [2,3,0,1]
+    auto swz4 = [](int x) { return __builtin_amdgcn_ds_swizzle(x, 0x101F); };                     // lane ^ 4
+    auto dpp8 = [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, false); };  // row_ror:8
+    auto swz16 = [](int x) { return __builtin_amdgcn_ds_swizzle(x, 0x401F); };                    // lane ^ 16
+    const bool b0 = ln & 1, b1 = ln & 2, b2 = ln & 4;
+    double r[4], s[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double h = k < 3 ? v[k < 3 ? k + 4 : 0] : 0.0;
+        r[k] = (b0 ? h : v[k]) + wave_swap(b0 ? v[k] : h, dpp1);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) s[k] = (b1 ? r[k + 2] : r[k]) + wave_swap(b1 ? r[k] : r[k + 2], dpp2);
+    double t = (b2 ? s[1] : s[0]) + wave_swap(b2 ? s[0] : s[1], swz4);
+    t += wave_swap(t, dpp8);
+    t += wave_swap(t, swz16);
+    t += __shfl_xor(t, 32);
+    return t;
+}
+// One sum by halves of the wave (32, 16, ... 1).  The links between spheres and at faces take
 // this tree: the last bits of a force depend on it.
 __device__ __forceinline__ double wave_sum_halves(double v) {
 #pragma unroll

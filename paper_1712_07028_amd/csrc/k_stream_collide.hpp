@@ -673,9 +673,10 @@ __device__ __forceinline__ int kconst(int q) {
 // 4.4 TB/s of traffic; so what is the same for the wave is worked on masks in scalar
 // registers: which cells are marched, and for each direction which lanes bounce back and
 // from what.  A mask is then the condition of a select or of a masked block without any
-// per-lane bit work.  512 x 512 x 1024 cells with 1e5 spheres: 10.8 ms a launch per lane, 10.2 ms
-// with masks (49.6 GB, 4.9 TB/s, what a large copy reaches); 128^3 with 1,400: 115 and 107 us.
-constexpr int NZC = 16;  // planes per block at most
+// per-lane bit work.  512 x 512 x 1024 cells without spheres, 16 planes a block: 8.59 ms a launch
+// per lane, 7.96 ms with masks.  With 1e5 spheres the sums of the links weigh more: 11.07 and
+// 11.05 ms; 128^3 with 1,400: 117.5 and 116.5 us.
+constexpr int NZC = 16;  // planes per block at most, with spheres
 #ifndef WPE_MARCH
 #define WPE_MARCH 4
 #endif
@@ -811,8 +812,8 @@ __device__ __forceinline__ void lds_add(double *p, double v) {
 // The order of a sphere's link sums is fixed within a wave: a lane sums its own cells plane by
 // plane, the lanes join in a fixed tree, and only what waves add to the sphere comes in any
 // order.  Sums of the whole block in a table in LDS, which its 256 lanes add to as they come,
-// save the lanes' atomics (512 x 512 x 1024 column 114.3 against 121.7 ms for ten steps, 128^3
-// bed 15.5 against 16.2 ms for fifty) but change the last bits of every force, and the
+// save atomics and trees (512 x 512 x 1024 column 10.46 against 11.05 ms a launch, 128^3 bed 106
+// against 116 us) but change the last bits of every force, and the
 // constant parts of the links, which cancel over a sphere, make that the same way in every
 // step: within 50 steps a 16-bit population rounds differently and the states part.
 
@@ -828,7 +829,8 @@ __device__ __forceinline__ void macc_lane_flush(const Dev &D, MarchLds &L, int t
 }
 
 // the lanes' remaining sums at the end of a march, segmented by sphere: one FP64 atomic
-// instruction per (wave, sphere).  Every lane of the wave must be active.
+// instruction per (wave, sphere).  Every lane of the wave must be active.  Seven sums one by one
+// cost the column 0.2 ms a launch, 128^3 with 1,400 spheres 7 us.
 __device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L) {
     const int t = threadIdx.x;
     int key = L.accP[t];
@@ -843,12 +845,10 @@ __device__ __forceinline__ void macc_wave_flush(const Dev &D, const MarchLds &L)
         const bool mine = key == k0;
         double s[7];
 #pragma unroll
-        for (int k = 0; k < 7; ++k) s[k] = wave_sum(mine ? a[k] : 0.0);
-        const int ln = (int)lane_id();
-        if (ln < 7) {
-            const double v = ln == 0 ? s[0] : ln == 1 ? s[1] : ln == 2 ? s[2] : ln == 3 ? s[3] : ln == 4 ? s[4] : ln == 5 ? s[5] : s[6];
-            unsafeAtomicAdd(D.pacc + acc_at(k0, blockIdx.x & (ACC_COPIES - 1)) + ln, v);
-        }
+        for (int k = 0; k < 7; ++k) s[k] = mine ? a[k] : 0.0;
+        const double v = wave_sums7(s);
+        const int ln = (int)lane_id(), k = wave_part(ln);
+        if (ln < 8 && k < 7) unsafeAtomicAdd(D.pacc + acc_at(k0, blockIdx.x & (ACC_COPIES - 1)) + k, v);
         if (mine) key = -1;
     }
 }
